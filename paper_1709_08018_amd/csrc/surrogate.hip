@@ -1,64 +1,19 @@
-// surrogate.hip -- training and inference kernels of the occupancy surrogate
-// (include/kl_surrogate.h): a BF16 matrix-core GEMM with FP32 accumulation,
-// the column forms of the transposed convolutions (col2im / im2col), and
-// the loss, optimiser, gate and IoU kernels, with their host orchestration.
-//
-// Activations are stored pixel-major: a layer with C channels on an H x W
-// grid for B sets is a (B*H*W) x C row-major matrix, so a transposed
-// convolution is one GEMM into "columns" Col = X K (K read as
-// Cin x (Cout*4*4)) followed by a gather that sums, for every output pixel,
-// the column entries of the input pixels that reach it.
+// surrogate.hip -- inference kernels of the occupancy surrogate
+// (include/kl_surrogate.h), its optimiser, gate and IoU kernels, the BF16
+// matrix-core GEMM with FP32 accumulation, and the entry points.  A training
+// step's loss and gradient are in surrogate_train.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 
-#include "kl_internal.hpp"
-#include "kl_surrogate.h"
+#include "surrogate.hpp"
 
 namespace kl {
 namespace sur {
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kImg = KL_SUR_IMG;
-
-// parameter layout (offsets in floats)
-struct Layout {
-    size_t W1, b1, W2, b2, K1, c1, K2, c2, K3, c3, K4, c4, total;
-};
-static Layout layout() {
-    Layout L;
-    size_t o = 0;
-    L.W1 = o; o += 4 * 256;
-    L.b1 = o; o += 256;
-    L.W2 = o; o += 256 * 256;
-    L.b2 = o; o += 256;
-    L.K1 = o; o += 16 * 64 * 16;
-    L.c1 = o; o += 64;
-    L.K2 = o; o += 64 * 32 * 16;
-    L.c2 = o; o += 32;
-    L.K3 = o; o += 32 * 16 * 16;
-    L.c3 = o; o += 16;
-    L.K4 = o; o += 16 * 1 * 16;
-    L.c4 = o; o += 1;
-    L.total = o;
-    return L;
-}
-
 // ------------------------------------------------------------------ GEMM
-// FP32 -> bfloat16, round to nearest even
-__device__ __forceinline__ unsigned short to_bf16(float x) {
-    uint32_t u = __float_as_uint(x);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
-
-// the value of x rounded to bfloat16, as FP32
-__device__ __forceinline__ float bf16_value(float x) { return __uint_as_float((uint32_t)to_bf16(x) << 16); }
-
 struct GemmArgs {
     int M, N, K;
     const float* A;
@@ -181,163 +136,6 @@ static hipError_t gemm(int M, int N, int K, const float* A, int64_t lam, int64_t
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ layer glue
-__global__ void features_kernel(const kl_c64* ta, const kl_c64* tb, int B, float* u) {
-    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < B; b += gridDim.x * blockDim.x) {
-        u[4 * b + 0] = (float)((ta[b].re - 2.4) / 0.6);
-        u[4 * b + 1] = (float)(ta[b].im / 0.3);
-        u[4 * b + 2] = (float)((tb[b].re - 2.4) / 0.6);
-        u[4 * b + 3] = (float)(tb[b].im / 0.3);
-    }
-}
-
-// h2 (B x 256, feature c*16 + q) <-> x0 ((B*16) x 16, row b*16 + q, column c)
-__global__ void h2_to_x0_kernel(const float* h2, float* x0, int B) {
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < B * 256; e += gridDim.x * blockDim.x) {
-        const int b = e / 256, f = e % 256, c = f / 16, q = f % 16;
-        x0[(b * 16 + q) * 16 + c] = h2[e];
-    }
-}
-__global__ void x0_to_h2_kernel(const float* x0, float* h2, int B) {
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < B * 256; e += gridDim.x * blockDim.x) {
-        const int b = e / 256, f = e % 256, c = f / 16, q = f % 16;
-        h2[e] = x0[(b * 16 + q) * 16 + c];
-    }
-}
-
-struct ConvShape {
-    int Hin, Hout, Co, s, p;  // square grids, 4 x 4 kernel
-};
-
-// Y[(b, oy, ox), o] = bias[o] + sum over taps (ky, kx) with oy = s*iy - p + ky,
-// ox = s*ix - p + kx of Col[(b, iy, ix), o*16 + ky*4 + kx]; optional relu.
-__global__ void col2im_kernel(const float* __restrict__ col, const float* __restrict__ bias, float* __restrict__ y,
-                              int B, ConvShape c, int relu) {
-    const int64_t n = (int64_t)B * c.Hout * c.Hout * c.Co;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    const int o = (int)(e % c.Co);
-    int64_t t = e / c.Co;
-    const int ox = (int)(t % c.Hout);
-    t /= c.Hout;
-    const int oy = (int)(t % c.Hout);
-    const int b = (int)(t / c.Hout);
-    float sum = 0.f;
-    for (int ky = 0; ky < 4; ++ky) {
-        const int ty = oy + c.p - ky;
-        if (ty < 0 || ty % c.s) continue;
-        const int iy = ty / c.s;
-        if (iy >= c.Hin) continue;
-        for (int kx = 0; kx < 4; ++kx) {
-            const int tx = ox + c.p - kx;
-            if (tx < 0 || tx % c.s) continue;
-            const int ix = tx / c.s;
-            if (ix >= c.Hin) continue;
-            sum += col[(((int64_t)b * c.Hin + iy) * c.Hin + ix) * (c.Co * 16) + o * 16 + ky * 4 + kx];
-        }
-    }
-    sum += bias[o];
-    y[e] = relu ? fmaxf(sum, 0.f) : sum;
-    }
-}
-
-// dCol[(b, iy, ix), o*16 + ky*4 + kx] = dY[(b, s*iy - p + ky, s*ix - p + kx), o], 0 outside
-__global__ void im2col_kernel(const float* __restrict__ dy, float* __restrict__ dcol, int B, ConvShape c) {
-    const int64_t n = (int64_t)B * c.Hin * c.Hin * c.Co * 16;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    const int tap = (int)(e % 16);
-    const int o = (int)((e / 16) % c.Co);
-    int64_t t = e / (16 * c.Co);
-    const int ix = (int)(t % c.Hin);
-    t /= c.Hin;
-    const int iy = (int)(t % c.Hin);
-    const int b = (int)(t / c.Hin);
-    const int oy = c.s * iy - c.p + tap / 4, ox = c.s * ix - c.p + tap % 4;
-    float v = 0.f;
-    if (oy >= 0 && oy < c.Hout && ox >= 0 && ox < c.Hout)
-        v = dy[(((int64_t)b * c.Hout + oy) * c.Hout + ox) * c.Co + o];
-    dcol[e] = v;
-    }
-}
-
-__global__ void relu_mask_kernel(float* d, const float* y, int64_t n) {
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
-        if (!(y[e] > 0.f)) d[e] = 0.f;
-}
-
-// Column sums of an M x C row-major matrix (C divides 256), two stages, fixed order.
-__global__ void colsum_stage1(const float* __restrict__ x, int64_t M, int C, int64_t rows_per_block,
-                              float* __restrict__ partial) {
-    __shared__ float red[256];
-    const int c = threadIdx.x % C, j = threadIdx.x / C, S = 256 / C;
-    const int64_t r0 = blockIdx.x * rows_per_block;
-    const int64_t r1 = std::min(M, r0 + rows_per_block);
-    float acc = 0.f;
-    for (int64_t r = r0 + j; r < r1; r += S) acc += x[r * C + c];
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    if (threadIdx.x < C) {
-        float sum = 0.f;
-        for (int q = 0; q < S; ++q) sum += red[q * C + threadIdx.x];
-        partial[(int64_t)blockIdx.x * C + threadIdx.x] = sum;
-    }
-}
-// one workgroup per column: strided partial sums, then a fixed tree
-__global__ void colsum_stage2(const float* __restrict__ partial, int blocks, int C, float* __restrict__ out,
-                              int accumulate) {
-    __shared__ float red[256];
-    const int c = blockIdx.x;
-    float sum = 0.f;
-    for (int b = threadIdx.x; b < blocks; b += 256) sum += partial[(int64_t)b * C + c];
-    red[threadIdx.x] = sum;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[c] = accumulate ? out[c] + red[0] : red[0];
-}
-
-static hipError_t colsum(const float* x, int64_t M, int C, float* out, float* partial, hipStream_t s) {
-    int blocks = (int)std::min<int64_t>(1024, (M + 255) / 256);
-    if (blocks < 1) blocks = 1;
-    const int64_t rpb = (M + blocks - 1) / blocks;
-    hipLaunchKernelGGL(colsum_stage1, dim3(blocks), dim3(256), 0, s, x, M, C, rpb, partial);
-    hipLaunchKernelGGL(colsum_stage2, dim3(C), dim3(256), 0, s, partial, blocks, C, out, 0);
-    return hipGetLastError();
-}
-
-// BCE with logits: loss terms (summed in two fixed-order stages) and dz = (sigmoid(z) - t) / n
-__global__ void bce_kernel(const float* __restrict__ z, const uint8_t* __restrict__ t, int64_t n,
-                           float* __restrict__ dz, float* __restrict__ partial) {
-    __shared__ float red[256];
-    float acc = 0.f;
-    const float inv = 1.0f / (float)n;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const float x = z[e], y = t[e] ? 1.f : 0.f;
-        acc += fmaxf(x, 0.f) - x * y + log1pf(expf(-fabsf(x)));
-        dz[e] = (1.f / (1.f + expf(-x)) - y) * inv;
-    }
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
-__global__ void loss_final_kernel(const float* partial, int blocks, int64_t n, float* loss) {
-    __shared__ float red[256];
-    float s = 0.f;
-    for (int b = threadIdx.x; b < blocks; b += 256) s += partial[b];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *loss = red[0] / (float)n;
-}
-
 __global__ void adam_kernel(float* p, const float* g, float* m, float* v, int64_t n, float lr, float bc1, float bc2) {
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
@@ -428,9 +226,6 @@ __global__ void iou_kernel(const float* __restrict__ z, const uint8_t* __restric
 //     so that the lanes of a wave read consecutive words), and each logit
 //     sums its four column entries.
 // Products: v_mfma_f32_16x16x32_bf16 (16x16x16 where K is 16), FP32 accumulation.
-typedef unsigned short bf16_t;
-typedef short bf16x8 __attribute__((ext_vector_type(8)));
-
 constexpr int kFwdThreads = 512;                      // 8 waves
 constexpr int kY1S = 64 + 8, kY2S = 32 + 8;           // bf16 per pixel: 16-byte rows, padded against bank conflicts
 constexpr int kY1Bytes = 18 * 18 * kY1S * 2;          // 16^2 grid with a zero border
@@ -440,19 +235,6 @@ constexpr int kRingW = 66;                            // x = -1 .. 64, the ends 
 constexpr int kRingBytes = kRing * kRingW * 16 * 4;
 constexpr int kFwdLds = kY2Bytes + kY1Bytes + 256 * 2 + 256 * 2 + 16;
 static_assert(kRingBytes <= kY1Bytes, "the column ring reuses the y1 space");
-
-// packed bfloat16 weights: a lane's k values adjacent
-constexpr size_t kK1p = 1024 * 16;          // [n = o*16 + ky*4 + kx][c]
-constexpr size_t kK2p = 4 * 8 * 32 * 32;    // [phase][k step][o][32 k]; k step = tap * 2 + channel half
-constexpr size_t kK3p = 4 * 4 * 16 * 32;    // [phase][tap][o][32 c]
-constexpr size_t kK4p = 16 * 16;            // [tap = ky*4 + kx][c]
-constexpr size_t kW2p = 16 * 8 * 16 * 32;   // [o / 16][k step][o % 16][32 k]
-constexpr size_t kPackedElems = kK1p + kK2p + kK3p + kK4p + kW2p;
-
-// Stride-2, pad-1 transposed convolution: for output phase p (0 even, 1
-// odd) and tap a (0, 1), the input offset and kernel index.
-__device__ __forceinline__ int tap_dy(int p, int a) { return p ? (a ? 0 : 1) : (a ? -1 : 0); }
-__device__ __forceinline__ int tap_k(int p, int a) { return p ? (a ? 2 : 0) : (a ? 3 : 1); }
 
 struct PackArgs {
     const float *W2, *K1, *K2, *K3, *K4;
@@ -498,12 +280,6 @@ struct FwdArgs {
 
 __device__ __forceinline__ bf16x4 frag4(const bf16_t* p) { return *(const bf16x4*)p; }
 __device__ __forceinline__ bf16x8 frag8(const bf16_t* p) { return *(const bf16x8*)p; }
-__device__ __forceinline__ f32x4 mma16(bf16x4 a, bf16x4 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x4 mma32(bf16x8 a, bf16x8 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
 __device__ __forceinline__ bf16x4 relu_bf16(f32x4 d, const float* bias) {
     bf16x4 r;
 #pragma unroll
@@ -699,81 +475,6 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(const FwdArgs a) {
 
 static unsigned grid_for(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(8192, (n + 255) / 256)); }
 
-// ------------------------------------------------------------------ workspace
-struct WS {
-    float *u, *h1, *h2, *x0, *col1, *y1, *col2, *y2, *col3, *y3, *col4, *logits, *dlogits, *dy3, *dy2, *dy1, *dx0,
-        *dh2, *dh1, *partial, *loss;
-    bf16_t* packed;   // decoder weights of the fused inference path
-    size_t bytes;
-};
-
-static const ConvShape kC1{4, 16, 64, 4, 0}, kC2{16, 32, 32, 2, 1}, kC3{32, 64, 16, 2, 1}, kC4{64, 128, 1, 2, 1};
-
-static WS carve(void* base, int B) {
-    WS w;
-    size_t o = 0;
-    auto take = [&](size_t nfloat) {
-        float* p = base ? (float*)((char*)base + o) : nullptr;
-        o += ((nfloat * sizeof(float) + 255) / 256) * 256;
-        return p;
-    };
-    const size_t b = (size_t)B;
-    w.u = take(b * 4);
-    w.h1 = take(b * 256);
-    w.h2 = take(b * 256);
-    w.x0 = take(b * 256);
-    w.col1 = take(b * 16 * 1024);
-    w.y1 = take(b * 256 * 64);
-    w.col2 = take(b * 256 * 512);
-    w.y2 = take(b * 1024 * 32);
-    w.col3 = take(b * 1024 * 256);
-    w.y3 = take(b * 4096 * 16);
-    w.col4 = take(b * 4096 * 16);
-    w.logits = take(b * kImg * kImg);
-    w.dlogits = take(b * kImg * kImg);
-    w.dy3 = take(b * 4096 * 16);
-    w.dy2 = take(b * 1024 * 32);
-    w.dy1 = take(b * 256 * 64);
-    w.dx0 = take(b * 256);
-    w.dh2 = take(b * 256);
-    w.dh1 = take(b * 256);
-    w.partial = take(1024 * 256);
-    w.loss = take(64);
-    w.packed = (bf16_t*)take((kPackedElems + 1) / 2);
-    w.bytes = o;
-    return w;
-}
-
-#define CHECK_HIP(x)                                  \
-    do {                                              \
-        hipError_t e_ = (x);                          \
-        if (e_ != hipSuccess) return e_;              \
-    } while (0)
-
-// forward pass into w (logits into `logits`)
-static hipError_t forward(const float* P, const kl_c64* ta, const kl_c64* tb, int B, float* logits, const WS& w,
-                          hipStream_t s) {
-    const Layout L = layout();
-    hipLaunchKernelGGL(features_kernel, dim3((B + 255) / 256), dim3(256), 0, s, ta, tb, B, w.u);
-    CHECK_HIP(gemm(B, 256, 4, w.u, 4, 1, P + L.W1, 256, 1, w.h1, 256, P + L.b1, 1, 0, s));
-    CHECK_HIP(gemm(B, 256, 256, w.h1, 256, 1, P + L.W2, 256, 1, w.h2, 256, P + L.b2, 1, 0, s));
-    hipLaunchKernelGGL(h2_to_x0_kernel, dim3(grid_for(B * 256)), dim3(256), 0, s, w.h2, w.x0, B);
-    // C1: (B*16) x 16 -> col1 (B*16) x 1024 -> y1 (B*256) x 64
-    CHECK_HIP(gemm(B * 16, 1024, 16, w.x0, 16, 1, P + L.K1, 1024, 1, w.col1, 1024, nullptr, 0, 0, s));
-    hipLaunchKernelGGL(col2im_kernel, dim3(grid_for((int64_t)B * 256 * 64)), dim3(256), 0, s, w.col1, P + L.c1,
-                       w.y1, B, kC1, 1);
-    CHECK_HIP(gemm(B * 256, 512, 64, w.y1, 64, 1, P + L.K2, 512, 1, w.col2, 512, nullptr, 0, 0, s));
-    hipLaunchKernelGGL(col2im_kernel, dim3(grid_for((int64_t)B * 1024 * 32)), dim3(256), 0, s, w.col2, P + L.c2,
-                       w.y2, B, kC2, 1);
-    CHECK_HIP(gemm(B * 1024, 256, 32, w.y2, 32, 1, P + L.K3, 256, 1, w.col3, 256, nullptr, 0, 0, s));
-    hipLaunchKernelGGL(col2im_kernel, dim3(grid_for((int64_t)B * 4096 * 16)), dim3(256), 0, s, w.col3, P + L.c3,
-                       w.y3, B, kC3, 1);
-    CHECK_HIP(gemm(B * 4096, 16, 16, w.y3, 16, 1, P + L.K4, 16, 1, w.col4, 16, nullptr, 0, 0, s));
-    hipLaunchKernelGGL(col2im_kernel, dim3(grid_for((int64_t)B * kImg * kImg)), dim3(256), 0, s, w.col4, P + L.c4,
-                       logits, B, kC4, 0);
-    return hipGetLastError();
-}
-
 // Inference forward: the weights packed once per call, then the whole network
 // per set in one kernel.
 static hipError_t forward_fused(const float* P, const kl_c64* ta, const kl_c64* tb, int B, float* logits,
@@ -789,52 +490,6 @@ static hipError_t forward_fused(const float* P, const kl_c64* ta, const kl_c64* 
     const FwdArgs f{ta, tb, P + L.W1, P + L.b1, P + L.b2, w2, k1, k2, k3, k4, P + L.c1, P + L.c2, P + L.c3, P + L.c4,
                     logits, B};
     hipLaunchKernelGGL(forward_kernel, dim3(std::min(B, 1024)), dim3(kFwdThreads), 0, s, f);
-    return hipGetLastError();
-}
-
-// Backward of one transposed convolution: d_out (masked already) ->
-// dbias, dK, d_in.  x_in: the layer input (Hin grid, Ci channels).
-static hipError_t conv_backward(const float* dout, const float* x_in, const float* K, int Ci, ConvShape c, int B,
-                                float* dcol, float* dK, float* dbias, float* din, const WS& w, hipStream_t s) {
-    const int64_t rows_out = (int64_t)B * c.Hout * c.Hout;
-    const int64_t rows_in = (int64_t)B * c.Hin * c.Hin;
-    CHECK_HIP(colsum(dout, rows_out, c.Co, dbias, w.partial, s));
-    hipLaunchKernelGGL(im2col_kernel, dim3(grid_for(rows_in * c.Co * 16)), dim3(256), 0, s, dout, dcol, B, c);
-    const int N = c.Co * 16;
-    // dK (Ci x N) = x_in^T (Ci x rows_in) dcol (rows_in x N)
-    CHECK_HIP(gemm(Ci, N, (int)rows_in, x_in, 1, Ci, dcol, N, 1, dK, N, nullptr, 0, 0, s));
-    // d_in (rows_in x Ci) = dcol (rows_in x N) K^T (N x Ci)
-    if (din) CHECK_HIP(gemm((int)rows_in, Ci, N, dcol, N, 1, K, 1, N, din, Ci, nullptr, 0, 0, s));
-    return hipGetLastError();
-}
-
-static hipError_t loss_grad(const float* P, const kl_c64* ta, const kl_c64* tb, const uint8_t* targets, int B,
-                            float* G, float* loss, const WS& w, hipStream_t s) {
-    const Layout L = layout();
-    CHECK_HIP(forward(P, ta, tb, B, w.logits, w, s));
-    const int64_t npx = (int64_t)B * kImg * kImg;
-    const int bce_blocks = (int)std::min<int64_t>(1024, (npx + 255) / 256);
-    hipLaunchKernelGGL(bce_kernel, dim3(bce_blocks), dim3(256), 0, s, w.logits, targets, npx, w.dlogits, w.partial);
-    hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(256), 0, s, w.partial, bce_blocks, npx, loss);
-    // C4 (no activation): d_out = dlogits
-    CHECK_HIP(conv_backward(w.dlogits, w.y3, P + L.K4, 16, kC4, B, w.col4, G + L.K4, G + L.c4, w.dy3, w, s));
-    hipLaunchKernelGGL(relu_mask_kernel, dim3(grid_for((int64_t)B * 4096 * 16)), dim3(256), 0, s, w.dy3, w.y3,
-                       (int64_t)B * 4096 * 16);
-    CHECK_HIP(conv_backward(w.dy3, w.y2, P + L.K3, 32, kC3, B, w.col3, G + L.K3, G + L.c3, w.dy2, w, s));
-    hipLaunchKernelGGL(relu_mask_kernel, dim3(grid_for((int64_t)B * 1024 * 32)), dim3(256), 0, s, w.dy2, w.y2,
-                       (int64_t)B * 1024 * 32);
-    CHECK_HIP(conv_backward(w.dy2, w.y1, P + L.K2, 64, kC2, B, w.col2, G + L.K2, G + L.c2, w.dy1, w, s));
-    hipLaunchKernelGGL(relu_mask_kernel, dim3(grid_for((int64_t)B * 256 * 64)), dim3(256), 0, s, w.dy1, w.y1,
-                       (int64_t)B * 256 * 64);
-    CHECK_HIP(conv_backward(w.dy1, w.x0, P + L.K1, 16, kC1, B, w.col1, G + L.K1, G + L.c1, w.dx0, w, s));
-    hipLaunchKernelGGL(x0_to_h2_kernel, dim3(grid_for(B * 256)), dim3(256), 0, s, w.dx0, w.dh2, B);
-    hipLaunchKernelGGL(relu_mask_kernel, dim3(grid_for(B * 256)), dim3(256), 0, s, w.dh2, w.h2, (int64_t)B * 256);
-    CHECK_HIP(colsum(w.dh2, B, 256, G + L.b2, w.partial, s));
-    CHECK_HIP(gemm(256, 256, B, w.h1, 1, 256, w.dh2, 256, 1, G + L.W2, 256, nullptr, 0, 0, s));   // h1^T dh2
-    CHECK_HIP(gemm(B, 256, 256, w.dh2, 256, 1, P + L.W2, 1, 256, w.dh1, 256, nullptr, 0, 0, s));  // dh2 W2^T
-    hipLaunchKernelGGL(relu_mask_kernel, dim3(grid_for(B * 256)), dim3(256), 0, s, w.dh1, w.h1, (int64_t)B * 256);
-    CHECK_HIP(colsum(w.dh1, B, 256, G + L.b1, w.partial, s));
-    CHECK_HIP(gemm(4, 256, B, w.u, 1, 4, w.dh1, 256, 1, G + L.W1, 256, nullptr, 0, 0, s));          // u^T dh1
     return hipGetLastError();
 }
 

@@ -1,0 +1,114 @@
+// surrogate.hpp -- declarations shared by the surrogate's inference kernels
+// (surrogate.hip) and its training kernels (surrogate_train.hip): the layout
+// of the parameter vector and of the workspace, and the matrix-core helpers.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <stdint.h>
+
+#include "kl_internal.hpp"
+#include "kl_surrogate.h"
+
+namespace kl {
+namespace sur {
+
+typedef unsigned short bf16_t;
+typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef short bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kImg = KL_SUR_IMG;
+
+// parameter layout (offsets in floats)
+struct Layout {
+    size_t W1, b1, W2, b2, K1, c1, K2, c2, K3, c3, K4, c4, total;
+};
+inline Layout layout() {
+    Layout L;
+    size_t o = 0;
+    L.W1 = o; o += 4 * 256;
+    L.b1 = o; o += 256;
+    L.W2 = o; o += 256 * 256;
+    L.b2 = o; o += 256;
+    L.K1 = o; o += 16 * 64 * 16;
+    L.c1 = o; o += 64;
+    L.K2 = o; o += 64 * 32 * 16;
+    L.c2 = o; o += 32;
+    L.K3 = o; o += 32 * 16 * 16;
+    L.c3 = o; o += 16;
+    L.K4 = o; o += 16 * 1 * 16;
+    L.c4 = o; o += 1;
+    L.total = o;
+    return L;
+}
+
+// FP32 -> bfloat16, round to nearest even
+__device__ __forceinline__ bf16_t to_bf16(float x) {
+    uint32_t u = __float_as_uint(x);
+    u += 0x7FFFu + ((u >> 16) & 1u);
+    return (bf16_t)(u >> 16);
+}
+
+// the value of x rounded to bfloat16, as FP32
+__device__ __forceinline__ float bf16_value(float x) { return __uint_as_float((uint32_t)to_bf16(x) << 16); }
+
+// D = A B + C on the matrix cores, one wave.  A (16 x K): lane l holds row
+// l % 16, K / 4 consecutive k from (K / 4) (l / 16); B (K x 16) likewise by
+// column; D (16 x 16): lane l holds column l % 16, rows 4 (l / 16) .. + 3.
+__device__ __forceinline__ f32x4 mma16(bf16x4 a, bf16x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mma32(bf16x8 a, bf16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// Stride-2, pad-1 transposed convolution: for output phase p (0 even, 1
+// odd) and tap a (0, 1), the input offset and kernel index.
+__device__ __forceinline__ int tap_dy(int p, int a) { return p ? (a ? 0 : 1) : (a ? -1 : 0); }
+__device__ __forceinline__ int tap_k(int p, int a) { return p ? (a ? 2 : 0) : (a ? 3 : 1); }
+
+// packed bfloat16 weights of the fused inference path: a lane's k values adjacent
+constexpr size_t kK1p = 1024 * 16;          // [n = o*16 + ky*4 + kx][c]
+constexpr size_t kK2p = 4 * 8 * 32 * 32;    // [phase][k step][o][32 k]; k step = tap * 2 + channel half
+constexpr size_t kK3p = 4 * 4 * 16 * 32;    // [phase][tap][o][32 c]
+constexpr size_t kK4p = 16 * 16;            // [tap = ky*4 + kx][c]
+constexpr size_t kW2p = 16 * 8 * 16 * 32;   // [o / 16][k step][o % 16][32 k]
+constexpr size_t kPackedElems = kK1p + kK2p + kK3p + kK4p + kW2p;
+
+// packed bfloat16 weights of a training step (offsets in elements): the
+// forward products' left operands, then the backward ones', which are the
+// parameters' own order
+constexpr size_t kT1f = 0;                       // [tap][o 64][c 16]
+constexpr size_t kT2f = kT1f + 16 * 64 * 16;     // [phase][tap][o 32][c 64]
+constexpr size_t kT3f = kT2f + 16 * 32 * 64;     // [phase][tap][o 16][c 32]
+constexpr size_t kT4f = kT3f + 16 * 16 * 32;     // [tap][c 16]
+constexpr size_t kT1b = kT4f + 16 * 16;          // K1 [c 16][o 64][tap]
+constexpr size_t kT2b = kT1b + 16 * 64 * 16;     // K2 [c 64][o 32][tap]
+constexpr size_t kT3b = kT2b + 64 * 32 * 16;     // K3 [c 32][o 16][tap]
+constexpr size_t kT4b = kT3b + 32 * 16 * 16;     // K4 [c 16][tap]
+constexpr size_t kT2w = kT4b + 16 * 16;          // W2 [i][j], 256 x 256
+constexpr size_t kTrainPacked = kT2w + 256 * 256;
+
+// Workgroups of the training kernels that keep a weight gradient in their
+// registers over several sets, each leaving one partial sum.
+constexpr int kParts3 = 512, kParts2 = 64, kParts1 = 64;
+// floats of one workgroup's partial sums: the last two layers' (loss, bias 4,
+// bias 3 at 2 .. 17, K4 at 32 .. 287), and K3 with bias 2
+constexpr int kPart34 = 288, kPart3 = 32 * 256 + 32, kPart2 = 64 * 512, kPart1 = 16 * 1024;
+
+struct WS {
+    float *u, *h1, *h2, *x0, *y1, *y2, *y3, *logits, *dlogits, *dy3, *dy2, *dy1, *dx0, *dh2, *dh1;
+    // partial sums: last two layers (8 a set), K3 and bias 2, bias 1 (2 a set, 64 each), K2, K1
+    float *p34, *p3, *pc1, *p2, *p1;
+    bf16_t* packed;   // packed weights of one pass, forward or training
+    size_t bytes;
+};
+
+WS carve(void* base, int B);
+
+hipError_t loss_grad(const float* P, const kl_c64* ta, const kl_c64* tb, const uint8_t* targets, int B, float* G,
+                     float* loss, const WS& w, hipStream_t s);
+
+}  // namespace sur
+}  // namespace kl

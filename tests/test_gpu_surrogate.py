@@ -359,3 +359,43 @@ def test_gated_scan_keeps_accepted_predictions_and_renders_the_rest():
     for i in range(len(accepted)):
         want = pred[i] if accepted[i] else occ[64 + i]
         assert torch.equal(scan_occ[i], want), i
+
+
+@pytest.mark.parametrize("B", [1, 33, 70, 130])
+def test_training_batches_with_several_sum_chains_and_passes(B):
+    """Batches whose input gradients are summed in several chains (1: two for
+    dy2 and four for dy1; 33: four for dy1; 70: three, of unequal length),
+    and whose weight gradients stay in a workgroup's registers over more than
+    one pass (70: K2 and K1; 130: K3 too).  Input gradients of the first,
+    middle and last set, and weight gradients of a few output channels over
+    every set, against the reference on the GPU's own inputs, within
+    gamma(n) of the terms' magnitudes (as the layer-by-layer test).  The sums
+    have a fixed order: a second step repeats bit for bit."""
+    flat = _params(2).astype(np.float32).astype(np.float64)
+    P = N.unflatten(flat)
+    ta, tb = _sets(B, 15)
+    targets = (np.random.default_rng(4).random((B, 128, 128)) < 0.05).astype(np.uint8)
+    ws = kl.sur_workspace(B)
+    loss, grad = kl.sur_loss_grad(_dev(flat), ta, tb, _dev(targets, torch.uint8), workspace=ws)
+    T = {n: kl.sur_workspace_tensor(ws, B, n).cpu().numpy().astype(np.float64) for n in kl.SUR_TENSORS}
+    G = N.unflatten(grad.cpu().numpy().astype(np.float64))
+    bf, A = N.bf16, np.abs
+    sets = sorted({0, B // 2, B - 1})
+    for n, xin, Hi, Ci, din, dname, Ho, Co, picks in ((2, "y2", 32, 32, "dy2", "dy3", 64, 16, (0, 7, 15)),
+                                                      (1, "y1", 16, 64, "dy1", "dy2", 32, 32, (0, 13, 31)),
+                                                      (0, "x0", 4, 16, "dx0", "dy1", 16, 64, (0, 63))):
+        K, c, st, pd = N.CONVS[n]
+        d, x = _nchw(T[dname], B, Ho, Co), _nchw(T[xin], B, Hi, Ci)
+        dx, _, _ = N.convT_backward(x[sets], P[K], d[sets], st, pd, rnd=bf)
+        Sx, _, _ = N.convT_backward(A(bf(x[sets])), A(bf(P[K])), A(bf(d[sets])), st, pd)
+        mask = x[sets] > 0 if n else 1.0
+        _close(din, _nchw(T[din], B, Hi, Ci)[sets], dx * mask, Sx * mask, Co * 16)
+        picks = list(picks)
+        _, dK, db = N.convT_backward(x, P[K][:, picks], d[:, picks], st, pd, rnd=bf)
+        _, SK, _ = N.convT_backward(A(bf(x)), A(bf(P[K][:, picks])), A(bf(d[:, picks])), st, pd)
+        _close("grad " + K, G[K][:, picks], dK, SK, B * Hi * Hi)
+        _close("grad " + c, G[c], d.sum(axis=(0, 2, 3)), A(d).sum(axis=(0, 2, 3)), B * Ho * Ho)
+    h1, dh2 = T["h1"].reshape(B, 256), T["dh2"].reshape(B, 256)
+    _close("grad W2", G["W2"], bf(h1).T @ bf(dh2), A(bf(h1)).T @ A(bf(dh2)), B)
+    loss2, grad2 = kl.sur_loss_grad(_dev(flat), ta, tb, _dev(targets, torch.uint8))
+    assert torch.equal(loss, loss2) and torch.equal(grad, grad2)
