@@ -158,24 +158,49 @@ __global__ void predict_occupancy_kernel(const float* z, uint64_t n, uint8_t* o)
         o[e] = z[e] > 0.f ? 1 : 0;
 }
 
-// one block per set: mean binary entropy of sigmoid(z)
-__global__ void uncertainty_kernel(const float* __restrict__ z, float* __restrict__ out) {
-    __shared__ float red[256];
+// One workgroup per set: mean binary entropy of sigmoid(z).  Bound by its
+// arithmetic (8.4 M logits at 512 sets), so a set takes sixteen waves, which
+// fill a CU's schedulers at two sets a CU, and a logit one exponential and
+// one reciprocal: with e = e^-|x| and s = e / (2 + e),
+//   H(sigmoid(x)) = log(1 + e) + |x| e / (1 + e),   log(1 + e) = 2 atanh(s),
+// the atanh by its power series to s^15 (s <= 1/3: truncated below 2e-9 of
+// its value).  512 sets: 11.9 us; with four waves a set, log1pf, and a
+// second exponential 43 us, with sixteen waves and log1pf 27 us.
+__device__ __forceinline__ float binary_entropy(float x) {
+    const float a = fabsf(x), e = expf(-a), p = 1.f + e, q = 2.f + e, pq = p * q;
+    float r = __builtin_amdgcn_rcpf(pq);   // 2 <= pq <= 6; one Newton step to full precision
+    r = fmaf(r, fmaf(-pq, r, 1.f), r);
+    const float s = e * (p * r), z = s * s;
+    float c = 1.f / 15.f;
+    c = fmaf(c, z, 1.f / 13.f);
+    c = fmaf(c, z, 1.f / 11.f);
+    c = fmaf(c, z, 1.f / 9.f);
+    c = fmaf(c, z, 1.f / 7.f);
+    c = fmaf(c, z, 1.f / 5.f);
+    c = fmaf(c, z, 1.f / 3.f);
+    return fmaf(2.f * s, c * z, 2.f * s) + a * (e * (q * r));
+}
+
+constexpr int kUncThreads = 1024;
+
+__global__ __launch_bounds__(kUncThreads) void uncertainty_kernel(const float* __restrict__ z, float* __restrict__ out) {
+    __shared__ float red[kUncThreads / 64];
     const float* zs = z + (int64_t)blockIdx.x * kImg * kImg;
     float acc = 0.f;
-    for (int e = threadIdx.x; e < kImg * kImg; e += 256) {
-        const float x = zs[e];
-        // H(sigmoid(x)) = log(1 + e^-|x|) + |x| sigmoid(-|x|)
-        const float a = fabsf(x);
-        acc += log1pf(expf(-a)) + a / (1.f + expf(a));
+#pragma unroll
+    for (int q = 0; q < kImg * kImg / (4 * kUncThreads); ++q) {
+        const f32x4 x = load4(zs + 4 * (q * kUncThreads + (int)threadIdx.x));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc += binary_entropy(x[v]);
     }
-    red[threadIdx.x] = acc;
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x / 64] = acc;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        float sum = 0.f;
+        for (int w = 0; w < kUncThreads / 64; ++w) sum += red[w];
+        out[blockIdx.x] = sum / (float)(kImg * kImg);
     }
-    if (threadIdx.x == 0) out[blockIdx.x] = red[0] / (float)(kImg * kImg);
 }
 
 __global__ void iou_kernel(const float* __restrict__ z, const uint8_t* __restrict__ pred,
@@ -202,294 +227,265 @@ __global__ void iou_kernel(const float* __restrict__ z, const uint8_t* __restric
     if (threadIdx.x == 0) out[blockIdx.x] = ru[0] == 0 ? 1.f : (float)ri[0] / (float)ru[0];
 }
 
-// ------------------------------------------------------------------ fused forward (inference)
-// The whole network for one set in one workgroup, every activation held in
-// LDS as bfloat16 -- the rounding the training path applies when it reads
-// them as GEMM operands:
-//   * u -> h1 (4 -> 256): four products per output on the vector ALUs;
-//   * h1 -> h2 (256 -> 256): W2^T h1 on the matrix cores, h1 the only
-//     non-zero column of the right operand;
-//   * convT k4 s4 p0 (16 -> 64 channels, 4^2 -> 16^2): no two taps of one
-//     input pixel overlap, so it is one product x0 (16 pixels x 16) K1
-//     (16 x 1024) scattered to the output pixels;
+// ------------------------------------------------------------------ forward (inference)
+// Two launches, activations in LDS as bfloat16 -- the rounding the training
+// path applies when it reads them as product operands.
+//
+// forward_mlp_kernel: the linear layers of 16 sets a workgroup (u -> h1, four
+// products per output on the vector ALUs; h1 -> h2 on the matrix cores, the
+// sets in the columns), and in further workgroups the packed weights.
+//
+// forward_kernel: the transposed convolutions of one set's strip of 32 logit
+// rows (y3 rows 16 s - 1 .. 16 s + 16, y2 rows 8 s - 1 .. 8 s + 8, y1 rows
+// 4 s - 1 .. 4 s + 4; a neighbour's rows are formed again, 1.2 times the
+// products of a whole set):
+//   * convT k4 s4 p0 (16 -> 64 channels, 4^2 -> 16^2): one product per tap
+//     and 16 channels, K1 by the 16 input pixels;
 //   * convT k4 s2 p1: output pixel (2m + py, 2n + px) gathers the input
 //     pixels (m + dy, n + dx) over two row taps and two column taps fixed by
-//     the phase (py, px) (tap_dy, tap_k below), so each of the four phases is
-//     a 2 x 2 convolution: Cout x (4 taps * Cin) weights times (4 taps *
-//     Cin) x (16 pixels) read straight from the padded input in LDS, one tap
-//     and 32 channels per product step.  Taken this way round, a lane ends up
+//     the phase (py, px) (tap_dy, tap_k), so each of the four phases is a
+//     2 x 2 convolution: Cout x (4 taps * Cin) weights times (4 taps * Cin) x
+//     (16 pixels) read straight from the padded input in LDS, one tap and 32
+//     channels per product step.  Taken this way round, a lane ends up
 //     holding four consecutive channels of one output pixel;
 //   * the last layer (16 -> 1 channel) in column form: col = y3 K4 (16 taps
 //     per pixel).  A lane's four channels of y3 are exactly its operand of
-//     that product, so y3 never leaves the registers; the columns of four
-//     y3 rows at a time go to a ring of nine zero-padded LDS rows (tap-major,
-//     so that the lanes of a wave read consecutive words), and each logit
-//     sums its four column entries.
+//     that product, so y3 never leaves the registers; the columns go to ten
+//     zero-padded LDS rows (tap-major, so that the lanes of a wave read
+//     consecutive words) in two passes of ten and eight y3 rows, and each
+//     logit sums its four column entries.
 // Products: v_mfma_f32_16x16x32_bf16 (16x16x16 where K is 16), FP32 accumulation.
-constexpr int kFwdThreads = 512;                      // 8 waves
+//
+// What bounds it: the latency of its LDS reads and products between the six
+// barriers of a strip (the products alone take 10 us at 512 sets).  Strips
+// keep the LDS of a workgroup at 71 KB, so two share a CU and fill each
+// other's waits, and a small batch spreads over four times the CUs; one
+// workgroup a set (140 KB) had 40 barriers a set and began each with the
+// loads of the linear layers.  512 sets: 42.5 + 5.2 us (strips, linear
+// layers), before 55.9 + 4.7 us; one set: 9.5 + 3.9 against 25.5 + 3.7 us.
+// Four waves with their weights in registers (250) read an operand row once
+// for both column phases and twice over the rows; eight waves of 128
+// registers, one phase each, read LDS 2.4 times as much and took 61 us.
+constexpr int kFwdThreads = 256;                      // 4 waves
 constexpr int kY1S = 64 + 8, kY2S = 32 + 8;           // bf16 per pixel: 16-byte rows, padded against bank conflicts
-constexpr int kY1Bytes = 18 * 18 * kY1S * 2;          // 16^2 grid with a zero border
-constexpr int kY2Bytes = 34 * 34 * kY2S * 2;          // 32^2 grid with a zero border
-constexpr int kRing = 9;                              // column rows m0-1 .. m0+7 never share a slot
-constexpr int kRingW = 66;                            // x = -1 .. 64, the ends zero
-constexpr int kRingBytes = kRing * kRingW * 16 * 4;
-constexpr int kFwdLds = kY2Bytes + kY1Bytes + 256 * 2 + 256 * 2 + 16;
-static_assert(kRingBytes <= kY1Bytes, "the column ring reuses the y1 space");
-
-struct PackArgs {
-    const float *W2, *K1, *K2, *K3, *K4;
-    bf16_t* out;
-};
-
-__global__ void pack_weights_kernel(const PackArgs a) {
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < kPackedElems; e += (size_t)gridDim.x * blockDim.x) {
-        float v;
-        size_t i = e;
-        if (i < kK1p) {
-            const int n = (int)(i / 16), c = (int)(i % 16);
-            v = a.K1[(c * 64 + n / 16) * 16 + n % 16];
-        } else if ((i -= kK1p) < kK2p) {
-            const int kk = (int)(i % 32), o = (int)((i / 32) % 32), ks = (int)((i / 1024) % 8), ph = (int)(i / 8192);
-            const int tap = ks >> 1, c = (ks & 1) * 32 + kk;
-            const int ky = tap_k(ph >> 1, tap >> 1), kx = tap_k(ph & 1, tap & 1);
-            v = a.K2[((c * 32 + o) * 4 + ky) * 4 + kx];
-        } else if ((i -= kK2p) < kK3p) {
-            const int c = (int)(i % 32), o = (int)((i / 32) % 16), tap = (int)((i / 512) % 4), ph = (int)(i / 2048);
-            const int ky = tap_k(ph >> 1, tap >> 1), kx = tap_k(ph & 1, tap & 1);
-            v = a.K3[((c * 16 + o) * 4 + ky) * 4 + kx];
-        } else if ((i -= kK3p) < kK4p) {
-            const int tap = (int)(i / 16), c = (int)(i % 16);
-            v = a.K4[c * 16 + tap];
-        } else {
-            i -= kK4p;
-            const int kk = (int)(i % 32), oo = (int)((i / 32) % 16), ks = (int)((i / 512) % 8), mt = (int)(i / 4096);
-            v = a.W2[(ks * 32 + kk) * 256 + mt * 16 + oo];
-        }
-        a.out[e] = to_bf16(v);
-    }
-}
+constexpr int kY2Bytes = 10 * 34 * kY2S * 2;          // rows 8 s - 1 .. 8 s + 8, x = -1 .. 32, the ends zero
+constexpr int kColRows = 10;                          // y3 row 16 s - 1 + li in slot li % 10
+constexpr int kColW = 68;                             // pixel x at entry x + 2, x = -1 .. 64, the ends zero
+constexpr int kColBytes = kColRows * 16 * kColW * 4;
+static_assert(6 * 18 * kY1S * 2 <= kColBytes, "the columns reuse the y1 space");
+constexpr int kFwdGrid = 512;                         // two workgroups a CU
 
 struct FwdArgs {
     const kl_c64 *ta, *tb;
-    const float *W1, *b1, *b2;                     // FP32 parameters
-    const bf16_t *w2, *k1, *k2, *k3, *k4;          // packed weights
-    const float *c1, *c2, *c3, *c4;                // biases
+    const float* P;
+    Layout L;
+    bf16_t *packed, *x0;
     float* logits;                                 // B x 128 x 128
     int B;
 };
 
-__device__ __forceinline__ bf16x4 frag4(const bf16_t* p) { return *(const bf16x4*)p; }
-__device__ __forceinline__ bf16x8 frag8(const bf16_t* p) { return *(const bf16x8*)p; }
-__device__ __forceinline__ bf16x4 relu_bf16(f32x4 d, const float* bias) {
-    bf16x4 r;
+__device__ __forceinline__ bf16x4 relu_bf16(f32x4 d, f32x4 bias) { return round4(relu4(add4(d, bias))); }
+
+__global__ __launch_bounds__(256) void forward_mlp_kernel(const FwdArgs a, int mlp_blocks) {
+    __shared__ __align__(16) bf16_t h1s[16 * 264];
+    __shared__ float us[16][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    if ((int)blockIdx.x >= mlp_blocks) {
+        const int stride = (int)(gridDim.x - mlp_blocks) * 256;
+        for (int e = ((int)blockIdx.x - mlp_blocks) * 256 + tid; e < kForwardPacked; e += stride)
+            a.packed[e] = to_bf16(packed_weight(a.P, a.L, e));
+        return;
+    }
+    const int b0 = ((int)blockIdx.x / 4) * 16;
+    if (tid < 16) {
+        const int b = min(b0 + tid, a.B - 1);
+        us[tid][0] = bf16_value((float)((a.ta[b].re - 2.4) / 0.6));
+        us[tid][1] = bf16_value((float)(a.ta[b].im / 0.3));
+        us[tid][2] = bf16_value((float)((a.tb[b].re - 2.4) / 0.6));
+        us[tid][3] = bf16_value((float)(a.tb[b].im / 0.3));
+    }
+    // rows o of W2^T, 16 a wave: the loads run while h1 is formed
+    const int o0 = (((int)blockIdx.x % 4) * 4 + wave) * 16;
+    bf16x8 w[8];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) r[v] = (short)to_bf16(fmaxf(d[v] + bias[v], 0.f));
-    return r;
+    for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[ks][k] = (short)to_bf16(a.P[a.L.W2 + (ks * 32 + 8 * lq + k) * 256 + o0 + lr]);
+    float w1[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w1[k] = bf16_value(a.P[a.L.W1 + k * 256 + tid]);
+    const float b1 = a.P[a.L.b1 + tid];
+    __syncthreads();
+#pragma unroll 4
+    for (int q = 0; q < 16; ++q) {
+        float acc = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc = fmaf(us[q][k], w1[k], acc);
+        h1s[q * 264 + tid] = to_bf16(fmaxf(acc + b1, 0.f));
+    }
+    __syncthreads();
+    f32x4 d = kZero4;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) d = mma32(w[ks], lds8(h1s + lr * 264 + ks * 32 + 8 * lq), d);
+    if (b0 + lr < a.B) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int o = o0 + 4 * lq + v;   // feature c * 16 + q -> x0 pixel q, channel c
+            a.x0[((size_t)(b0 + lr) * 16 + o % 16) * 16 + o / 16] = to_bf16(fmaxf(d[v] + a.P[a.L.b2 + o], 0.f));
+        }
+    }
 }
 
-// One workgroup per set, sets dealt round robin over the grid.
-__global__ __launch_bounds__(kFwdThreads) void forward_kernel(const FwdArgs a) {
-    __shared__ __align__(16) unsigned char dsm[kFwdLds];
-    bf16_t* y2p = (bf16_t*)dsm;                                // [34][34][kY2S]
-    bf16_t* y1p = (bf16_t*)(dsm + kY2Bytes);                   // [18][18][kY1S]
-    bf16_t* h1s = (bf16_t*)(dsm + kY2Bytes + kY1Bytes);        // [256]
-    bf16_t* x0s = h1s + 256;                                   // [16 pixels][16 channels]
-    float* us = (float*)(x0s + 256);                           // [4]
-    float* ring = (float*)(dsm + kY2Bytes);                    // [kRing][16 taps][kRingW], once y1 is consumed
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lr = lane & 15, lq = lane >> 4;
-    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+// Strips dealt round robin over the grid: 4 a set.  Four waves, all weights
+// in registers: a wave takes one output row parity of each stride-2 layer
+// (and 16 of the channels, or half of the columns), so the three shifted
+// operands it reads of an input row serve both column phases, and the row's
+// next use, one output row on, finds them in registers.
+__global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void forward_kernel(const FwdArgs a) {
+    __shared__ __align__(16) unsigned char dsm[kY2Bytes + kColBytes];
+    bf16_t* y2p = (bf16_t*)dsm;                                // [10][34][kY2S]
+    bf16_t* y1p = (bf16_t*)(dsm + kY2Bytes);                   // [6][18][kY1S]
+    float* col = (float*)(dsm + kY2Bytes);                     // [kColRows][16 taps][kColW], once y1 is consumed
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lq = lane >> 4, half = wave & 1, py = wave >> 1;
 
-    // weights that stay in registers
-    const int ph2 = wave >> 1;                 // convT 2: phase, output rows 8 (wave & 1) .. + 8
-    bf16x8 w2[2][8];
+    bf16x4 w1[4][4];    // convT 1: taps (wave, kx), 16 channels each
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int kx = 0; kx < 4; ++kx)
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) w2[t][ks] = frag8(a.k2 + ((ph2 * 8 + ks) * 32 + 16 * t + lr) * 32 + 8 * lq);
-    // convT 3 tiles of this wave: row r3 of each group of four, column phase px3, halves 0 and 1;
-    // the row phase is r3 & 1 because groups start at multiples of four
-    const int r3 = wave >> 1, px3 = wave & 1, ph3 = (r3 & 1) * 2 + px3;
-    bf16x8 w3[4];
+        for (int ct = 0; ct < 4; ++ct) w1[kx][ct] = loadw(a.packed + kT1f + ((4 * wave + kx) * 64 + 16 * ct + lr) * 16 + 4 * lq);
+    bf16x8 w2[2][8];    // convT 2: both column phases, (tap, channel half); output channels 16 half ..
+    bf16x8 w3[2][4];    // convT 3: both column phases, tap; columns 2 (16 half + lr) + px
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) w3[ks] = frag8(a.k3 + ((ph3 * 4 + ks) * 16 + lr) * 32 + 8 * lq);
-    const bf16x4 w4 = frag4(a.k4 + lr * 16 + 4 * lq);
-    float b2c[2][4], b3c[4];
+    for (int px = 0; px < 2; ++px) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        b2c[0][v] = a.c2[4 * lq + v];
-        b2c[1][v] = a.c2[16 + 4 * lq + v];
-        b3c[v] = a.c3[4 * lq + v];
+        for (int ks = 0; ks < 8; ++ks)
+            w2[px][ks] = loadw8(a.packed + kT2f + (((2 * py + px) * 4 + (ks >> 1)) * 32 + 16 * half + lr) * 64 + (ks & 1) * 32 + 8 * lq);
+#pragma unroll
+        for (int tap = 0; tap < 4; ++tap) w3[px][tap] = loadw8(a.packed + kT3f + (((2 * py + px) * 4 + tap) * 16 + lr) * 32 + 8 * lq);
     }
-    const float b4 = a.c4[0];
-
-    for (int i = tid; i < kY2Bytes / 4; i += kFwdThreads) ((uint32_t*)y2p)[i] = 0u;   // border stays zero
-
-    for (int b = blockIdx.x; b < a.B; b += gridDim.x) {
-        for (int i = tid; i < kY1Bytes / 4; i += kFwdThreads) ((uint32_t*)y1p)[i] = 0u;
-        if (tid == 0) {
-            us[0] = (float)((a.ta[b].re - 2.4) / 0.6);
-            us[1] = (float)(a.ta[b].im / 0.3);
-            us[2] = (float)((a.tb[b].re - 2.4) / 0.6);
-            us[3] = (float)(a.tb[b].im / 0.3);
-        }
-        __syncthreads();
-        // h1 = relu(u W1 + b1), operands rounded to bfloat16
-        if (tid < 256) {
-            float acc = 0.f;
+    const bf16x4 w4 = loadw(a.packed + kT4f + lr * 16 + 4 * lq);
+    f32x4 bias1[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) acc = fmaf(bf16_value(us[k]), bf16_value(a.W1[k * 256 + tid]), acc);
-            h1s[tid] = to_bf16(fmaxf(acc + a.b1[tid], 0.f));
+    for (int ct = 0; ct < 4; ++ct) bias1[ct] = load4(a.P + a.L.c1 + 16 * ct + 4 * lq);
+    const f32x4 bias2 = load4(a.P + a.L.c2 + 16 * half + 4 * lq), bias3 = load4(a.P + a.L.c3 + 4 * lq);
+    const float bias4 = a.P[a.L.c4];
+
+    if (tid < 10 * 2 * 5) {   // the ends of the y2 rows stay zero
+        const int g = tid % 5, e = (tid / 5) & 1, r = tid / 10;
+        ((uint4*)(y2p + (r * 34 + (e ? 33 : 0)) * kY2S))[g] = make_uint4(0, 0, 0, 0);
+    }
+    for (int unit = blockIdx.x; unit < 4 * a.B; unit += gridDim.x) {
+        const int b = unit >> 2, s = unit & 3;
+        const bf16x4 x = loadw(a.x0 + ((size_t)b * 16 + lr) * 16 + 4 * lq);
+        // y1 rows 4 s - 1 .. 4 s + 4: the row beyond the grid and the ends zero
+        if (tid < 6 * 2 * 9) {
+            const int g = tid % 9, e = (tid / 9) & 1, r = tid / 18;
+            ((uint4*)(y1p + (r * 18 + (e ? 17 : 0)) * kY1S))[g] = make_uint4(0, 0, 0, 0);
         }
-        __syncthreads();
-        // h2 = relu(h1 W2 + b2): rows o of W2^T, 16 per tile, two tiles per wave; column 0 = h1
+        if ((s == 0 || s == 3) && tid >= 256 - 16 * 9)
+            ((uint4*)(y1p + ((s ? 5 : 0) * 18 + 1) * kY1S))[tid - (256 - 16 * 9)] = make_uint4(0, 0, 0, 0);
         {
-            f32x4 d[2] = {zero4, zero4};
+            const int i = lr >> 2, j = lr & 3, row = 4 * i + wave - (4 * s - 1);
+            const bool in = row >= 0 && row < 6;
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks) {
-                bf16x8 hb = {0, 0, 0, 0, 0, 0, 0, 0};
-                if (lr == 0) hb = frag8(h1s + ks * 32 + 8 * lq);
+            for (int kx = 0; kx < 4; ++kx)
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    d[u] = mma32(frag8(a.w2 + (((2 * wave + u) * 8 + ks) * 16 + lr) * 32 + 8 * lq), hb, d[u]);
-            }
-            if (lr == 0) {
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int o = 16 * (2 * wave + u) + 4 * lq + v;   // feature c*16 + q -> x0 pixel q, channel c
-                        x0s[(o % 16) * 16 + o / 16] = to_bf16(fmaxf(d[u][v] + a.b2[o], 0.f));
-                    }
-            }
+                for (int ct = 0; ct < 4; ++ct) {
+                    const bf16x4 y = relu_bf16(mma16(w1[kx][ct], x, kZero4), bias1[ct]);
+                    if (in) *(bf16x4*)(y1p + (row * 18 + 4 * j + kx + 1) * kY1S + 16 * ct + 4 * lq) = y;
+                }
         }
         __syncthreads();
-
-        // convT 1: N tile t = output channel t (16 taps); rows = the 16 input pixels
+        // y2 rows 8 s - 1 .. 8 s + 8 of this wave's parity: local rows 2 t + 1 - py, from the local
+        // y1 rows t + 1 (first row tap) and t (second)
         {
-            const bf16x4 ax = frag4(x0s + lr * 16 + 4 * lq);
-            const int ky = lr >> 2, kx = lr & 3;
-            for (int t = wave; t < 64; t += kFwdThreads / 64) {
-                const f32x4 d = mma16(ax, frag4(a.k1 + (16 * t + lr) * 16 + 4 * lq), zero4);
-                const float bias = a.c1[t];
+            bf16x8 f[2][3][2];   // [row & 1][shift -1, 0, 1][channel half]
+            auto rows = [&](int r) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int p = 4 * lq + v, i = p >> 2, j = p & 3;
-                    y1p[((4 * i + ky + 1) * 18 + 4 * j + kx + 1) * kY1S + t] = to_bf16(fmaxf(d[v] + bias, 0.f));
+                for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) f[r & 1][dx][h] = lds8(y1p + (r * 18 + lr + dx) * kY1S + 32 * h + 8 * lq);
+            };
+            rows(0);
+#pragma unroll
+            for (int t = 0; t < 5; ++t) {
+                rows(t + 1);
+                const int r = 2 * t + 1 - py, Y = 8 * s - 1 + r;
+                f32x4 d[2] = {kZero4, kZero4};
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+                    for (int px = 0; px < 2; ++px)
+                        d[px] = mma32(w2[px][ks], f[(t + 1 - (ks >> 2)) & 1][tap_dy(px, (ks >> 1) & 1) + 1][ks & 1], d[px]);
+#pragma unroll
+                for (int px = 0; px < 2; ++px) {
+                    bf16x4 y = relu_bf16(d[px], bias2);
+                    if (Y < 0 || Y >= 32) y = bf16x4{0, 0, 0, 0};
+                    *(bf16x4*)(y2p + (r * 34 + 2 * lr + px + 1) * kY2S + 16 * half + 4 * lq) = y;
                 }
             }
         }
         __syncthreads();
-
-        // convT 2, phase ph2: tile = output row 2m + py, columns 2n + px for n = lane's lr
-        {
-            const int py = ph2 >> 1, px = ph2 & 1;
-            for (int mi = 0; mi < 8; ++mi) {
-                const int m = 8 * (wave & 1) + mi;
-                bf16x8 ay[8];
+        for (int i = tid; i < kColRows * 16 * 2; i += kFwdThreads) col[(i >> 1) * kColW + ((i & 1) ? 66 : 1)] = 0.f;
+        // y3 rows li = 0 .. 9, then 10 .. 17 (row 16 s - 1 + li), and the logits they complete
+        bf16x8 f[2][3];   // [row & 1][shift]
+        auto rows = [&](int r) {
 #pragma unroll
-                for (int ks = 0; ks < 8; ++ks) {
-                    const int tap = ks >> 1;
-                    const int iy = m + tap_dy(py, tap >> 1) + 1, ix = lr + tap_dy(px, tap & 1) + 1;
-                    ay[ks] = frag8(y1p + (iy * 18 + ix) * kY1S + (ks & 1) * 32 + 8 * lq);
-                }
-                f32x4 d0 = zero4, d1 = zero4;
+            for (int dx = 0; dx < 3; ++dx) f[r & 1][dx] = lds8(y2p + (r * 34 + 16 * half + lr + dx) * kY2S + 8 * lq);
+        };
+        rows(0);
 #pragma unroll
-                for (int ks = 0; ks < 8; ++ks) {
-                    d0 = mma32(w2[0][ks], ay[ks], d0);
-                    d1 = mma32(w2[1][ks], ay[ks], d1);
-                }
-                // keep that order: the 8 LDS reads, then the 16 products
-                __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);
-                bf16_t* dst = y2p + ((2 * m + py + 1) * 34 + 2 * lr + px + 1) * kY2S + 4 * lq;
-                *(bf16x4*)dst = relu_bf16(d0, b2c[0]);
-                *(bf16x4*)(dst + 16) = relu_bf16(d1, b2c[1]);
-            }
-        }
-        __syncthreads();
-        // the ring: row -1 (slot 0) zero, the end pixels of every row zero
-        for (int i = tid; i < kRingW * 16; i += kFwdThreads) ring[i] = 0.f;
-        for (int i = tid; i < (kRing - 1) * 16 * 2; i += kFwdThreads) {
-            const int slot = 1 + i / 32, tap = (i / 2) % 16, end = i & 1;
-            ring[(slot * 16 + tap) * kRingW + (end ? kRingW - 1 : 0)] = 0.f;
-        }
-
-        // groups of four y3 rows m0 .. m0 + 3 (slot of row m: (m + 1) mod kRing);
-        // the 17th group only closes the last logit row
-        for (int g = 0; g <= 16; ++g) {
-            const int m0 = 4 * g;
-            if (g < 16) {
-                const int Y = m0 + r3, m = Y >> 1, py = Y & 1;
-                bf16x8 ay[2][4];
+        for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    const int iy = m + tap_dy(py, ks >> 1) + 1;
+            for (int t = pass ? 5 : 0; t < (pass ? 9 : 5); ++t) {
+                rows(t + 1);
+                const int li = 2 * t + 1 - py, Y = 16 * s - 1 + li;
+                f32x4 d[2] = {kZero4, kZero4}, c[2];
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int ix = 16 * h + lr + tap_dy(px3, ks & 1) + 1;
-                        ay[h][ks] = frag8(y2p + (iy * 34 + ix) * kY2S + 8 * lq);
-                    }
-                }
-                f32x4 d[2] = {zero4, zero4};
+                for (int tap = 0; tap < 4; ++tap)
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks)
+                    for (int px = 0; px < 2; ++px)
+                        d[px] = mma32(w3[px][tap], f[(t + 1 - (tap >> 1)) & 1][tap_dy(px, tap & 1) + 1], d[px]);
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) d[h] = mma32(w3[ks], ay[h][ks], d[h]);
-                __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-                float* row = ring + ((Y + 1) % kRing) * 16 * kRingW;
+                for (int px = 0; px < 2; ++px) c[px] = mma16(w4, relu_bf16(d[px], bias3), kZero4);   // taps 4 lq .. + 3
+                const bool in = Y >= 0 && Y < 64;
+                float* row = col + (li % kColRows) * 16 * kColW + 2 * (16 * half + lr) + 2;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const f32x4 c = mma16(w4, relu_bf16(d[h], b3c), zero4);   // taps 4 lq + v of pixel x
-                    const int x = 2 * (16 * h + lr) + px3;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) row[(4 * lq + v) * kRingW + x + 1] = c[v];
-                }
-            } else {
-                for (int i = tid; i < kRingW * 16; i += kFwdThreads) ring[(65 % kRing) * kRingW * 16 + i] = 0.f;  // row 64
+                for (int v = 0; v < 4; ++v)
+                    *(float2*)(row + (4 * lq + v) * kColW) = make_float2(in ? c[0][v] : 0.f, in ? c[1][v] : 0.f);
             }
             __syncthreads();
-            // logit row Z = 2 m0 - 1 + tid / 64 (those in range), columns 2u and 2u + 1 for u = tid % 64:
-            // X = 2u takes pixels u (kx 1) and u - 1 (kx 3), X = 2u + 1 pixels u + 1 (kx 0) and u (kx 2)
-            {
-                const int Z = 2 * m0 - 1 + (tid >> 6), u = tid & 63;
-                if (Z >= 0 && Z < 128) {
-                    float e0 = 0.f, e1 = 0.f;
+            // logit rows 32 s + 16 pass .. + 15, columns 2u and 2u + 1: X = 2u takes pixels u
+            // (kx 1) and u - 1 (kx 3), X = 2u + 1 pixels u + 1 (kx 0) and u (kx 2)
 #pragma unroll
-                    for (int ra = 0; ra < 2; ++ra) {
-                        // taps (ky, 0..3) of y3 row (Z >> 1) + dy; ring x = pixel + 1
-                        const float* t = ring + ((((Z >> 1) + tap_dy(Z & 1, ra) + 1) % kRing) * 16 +
-                                                 4 * tap_k(Z & 1, ra)) * kRingW + u;
-                        e0 += t[kRingW + 1] + t[3 * kRingW];
-                        e1 += t[2] + t[2 * kRingW + 1];
-                    }
-                    float2 out = {e0 + b4, e1 + b4};
-                    *(float2*)(a.logits + ((int64_t)b * 128 + Z) * 128 + 2 * u) = out;
+            for (int q = 0; q < 4; ++q) {
+                const int zl = 16 * pass + 4 * q + wave, Z = 32 * s + zl, u = lane;
+                float e0 = 0.f, e1 = 0.f;
+#pragma unroll
+                for (int ra = 0; ra < 2; ++ra) {
+                    // taps (ky, 0..3) of y3 row (Z >> 1) + dy; pixel x is column entry x + 2
+                    const int li = (zl >> 1) + 1 + tap_dy(Z & 1, ra);
+                    const float* t = col + ((li % kColRows) * 16 + 4 * tap_k(Z & 1, ra)) * kColW + u + 1;
+                    e0 += t[kColW + 1] + t[3 * kColW];
+                    e1 += t[2] + t[2 * kColW + 1];
                 }
+                *(float2*)(a.logits + ((int64_t)b * 128 + Z) * 128 + 2 * u) = make_float2(e0 + bias4, e1 + bias4);
             }
+            __syncthreads();   // the next rows, or the next strip's y1, overwrite the columns
         }
-        __syncthreads();   // the next set's y1 clear overwrites the ring
     }
 }
 
 static unsigned grid_for(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(8192, (n + 255) / 256)); }
 
-// Inference forward: the weights packed once per call, then the whole network
-// per set in one kernel.
+// Inference forward: linear layers and packed weights, then the strips.
 static hipError_t forward_fused(const float* P, const kl_c64* ta, const kl_c64* tb, int B, float* logits,
                                 const WS& w, hipStream_t s) {
-    const Layout L = layout();
-    const PackArgs pa{P + L.W2, P + L.K1, P + L.K2, P + L.K3, P + L.K4, w.packed};
-    hipLaunchKernelGGL(pack_weights_kernel, dim3(grid_for((int64_t)kPackedElems)), dim3(256), 0, s, pa);
-    const bf16_t* k1 = w.packed;
-    const bf16_t* k2 = k1 + kK1p;
-    const bf16_t* k3 = k2 + kK2p;
-    const bf16_t* k4 = k3 + kK3p;
-    const bf16_t* w2 = k4 + kK4p;
-    const FwdArgs f{ta, tb, P + L.W1, P + L.b1, P + L.b2, w2, k1, k2, k3, k4, P + L.c1, P + L.c2, P + L.c3, P + L.c4,
-                    logits, B};
-    hipLaunchKernelGGL(forward_kernel, dim3(std::min(B, 1024)), dim3(kFwdThreads), 0, s, f);
+    const FwdArgs f{ta, tb, P, layout(), w.packed, w.x0h, logits, B};
+    const int mlp = 4 * ((B + 15) / 16);
+    hipLaunchKernelGGL(forward_mlp_kernel, dim3(mlp + 112), dim3(256), 0, s, f, mlp);
+    hipLaunchKernelGGL(forward_kernel, dim3(std::min(4 * B, kFwdGrid)), dim3(kFwdThreads), 0, s, f);
     return hipGetLastError();
 }
 
@@ -609,7 +605,7 @@ int kl_sur_predict_occupancy(const float* logits, uint64_t n, uint8_t* occ_out, 
 
 int kl_sur_uncertainty(const float* logits, int batch, float* out, void* stream) {
     if (batch <= 0 || !logits || !out) return sur_fail(KL_EINVAL, "bad uncertainty arguments");
-    hipLaunchKernelGGL(uncertainty_kernel, dim3(batch), dim3(256), 0, (hipStream_t)stream, logits, out);
+    hipLaunchKernelGGL(uncertainty_kernel, dim3(batch), dim3(kUncThreads), 0, (hipStream_t)stream, logits, out);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? KL_OK : sur_fail(KL_EDEVICE, hipGetErrorString(e));
 }

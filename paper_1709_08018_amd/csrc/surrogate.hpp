@@ -68,27 +68,77 @@ __device__ __forceinline__ f32x4 mma32(bf16x8 a, bf16x8 b, f32x4 c) {
 __device__ __forceinline__ int tap_dy(int p, int a) { return p ? (a ? 0 : 1) : (a ? -1 : 0); }
 __device__ __forceinline__ int tap_k(int p, int a) { return p ? (a ? 2 : 0) : (a ? 3 : 1); }
 
-// packed bfloat16 weights of the fused inference path: a lane's k values adjacent
-constexpr size_t kK1p = 1024 * 16;          // [n = o*16 + ky*4 + kx][c]
-constexpr size_t kK2p = 4 * 8 * 32 * 32;    // [phase][k step][o][32 k]; k step = tap * 2 + channel half
-constexpr size_t kK3p = 4 * 4 * 16 * 32;    // [phase][tap][o][32 c]
-constexpr size_t kK4p = 16 * 16;            // [tap = ky*4 + kx][c]
-constexpr size_t kW2p = 16 * 8 * 16 * 32;   // [o / 16][k step][o % 16][32 k]
-constexpr size_t kPackedElems = kK1p + kK2p + kK3p + kK4p + kW2p;
+// Packed bfloat16 weights (offsets in elements), rounded once a pass in the
+// order the products read them: the forward products' left operands, then,
+// for a training step, the backward ones', which are the parameters' own
+// order.
+constexpr int kT1f = 0;                       // [tap][o 64][c 16]
+constexpr int kT2f = kT1f + 16 * 64 * 16;     // [phase][tap][o 32][c 64]
+constexpr int kT3f = kT2f + 16 * 32 * 64;     // [phase][tap][o 16][c 32]
+constexpr int kT4f = kT3f + 16 * 16 * 32;     // [tap][c 16]
+constexpr int kForwardPacked = kT4f + 16 * 16;
+constexpr int kT1b = kForwardPacked;          // K1 [c 16][o 64][tap]
+constexpr int kT2b = kT1b + 16 * 64 * 16;     // K2 [c 64][o 32][tap]
+constexpr int kT3b = kT2b + 64 * 32 * 16;     // K3 [c 32][o 16][tap]
+constexpr int kT4b = kT3b + 32 * 16 * 16;     // K4 [c 16][tap]
+constexpr int kT2w = kT4b + 16 * 16;          // W2 [i][j], 256 x 256
+constexpr int kTrainPacked = kT2w + 256 * 256;
 
-// packed bfloat16 weights of a training step (offsets in elements): the
-// forward products' left operands, then the backward ones', which are the
-// parameters' own order
-constexpr size_t kT1f = 0;                       // [tap][o 64][c 16]
-constexpr size_t kT2f = kT1f + 16 * 64 * 16;     // [phase][tap][o 32][c 64]
-constexpr size_t kT3f = kT2f + 16 * 32 * 64;     // [phase][tap][o 16][c 32]
-constexpr size_t kT4f = kT3f + 16 * 16 * 32;     // [tap][c 16]
-constexpr size_t kT1b = kT4f + 16 * 16;          // K1 [c 16][o 64][tap]
-constexpr size_t kT2b = kT1b + 16 * 64 * 16;     // K2 [c 64][o 32][tap]
-constexpr size_t kT3b = kT2b + 64 * 32 * 16;     // K3 [c 32][o 16][tap]
-constexpr size_t kT4b = kT3b + 32 * 16 * 16;     // K4 [c 16][tap]
-constexpr size_t kT2w = kT4b + 16 * 16;          // W2 [i][j], 256 x 256
-constexpr size_t kTrainPacked = kT2w + 256 * 256;
+// Packed element e of the parameters P.
+__device__ __forceinline__ float packed_weight(const float* P, const Layout& L, int e) {
+    if (e < kT2f) {
+        const int c = e % 16, o = (e / 16) % 64, tap = e / 1024;
+        return P[L.K1 + (c * 64 + o) * 16 + tap];
+    }
+    if (e < kT3f) {
+        const int i = e - kT2f, c = i % 64, o = (i / 64) % 32, tap = (i / 2048) % 4, ph = i / 8192;
+        return P[L.K2 + ((c * 32 + o) * 4 + tap_k(ph >> 1, tap >> 1)) * 4 + tap_k(ph & 1, tap & 1)];
+    }
+    if (e < kT4f) {
+        const int i = e - kT3f, c = i % 32, o = (i / 32) % 16, tap = (i / 512) % 4, ph = i / 2048;
+        return P[L.K3 + ((c * 16 + o) * 4 + tap_k(ph >> 1, tap >> 1)) * 4 + tap_k(ph & 1, tap & 1)];
+    }
+    if (e < kT1b) {
+        const int i = e - kT4f;
+        return P[L.K4 + (i % 16) * 16 + i / 16];
+    }
+    if (e < kT2b) return P[L.K1 + (e - kT1b)];
+    if (e < kT3b) return P[L.K2 + (e - kT2b)];
+    if (e < kT4b) return P[L.K3 + (e - kT3b)];
+    if (e < kT2w) return P[L.K4 + (e - kT4b)];
+    return P[L.W2 + (e - kT2w)];
+}
+
+// Vectors of global memory, 4-byte aligned: callers may pass any float array
+typedef float f32x4g __attribute__((ext_vector_type(4), aligned(4)));
+typedef short bf16x4g __attribute__((ext_vector_type(4), aligned(4)));
+typedef short bf16x8g __attribute__((ext_vector_type(8), aligned(4)));
+
+__device__ __forceinline__ f32x4 load4(const float* p) { return *(const f32x4g*)p; }
+__device__ __forceinline__ void store4(float* p, f32x4 v) { *(f32x4g*)p = v; }
+__device__ __forceinline__ bf16x4 loadw(const bf16_t* p) { return *(const bf16x4g*)p; }
+__device__ __forceinline__ bf16x8 loadw8(const bf16_t* p) { return *(const bf16x8g*)p; }
+__device__ __forceinline__ bf16x4 lds4(const bf16_t* p) { return *(const bf16x4*)p; }   // 8-byte aligned LDS
+__device__ __forceinline__ bf16x8 lds8(const bf16_t* p) { return *(const bf16x8*)p; }   // 16-byte aligned LDS
+
+// two values rounded to bfloat16 (nearest even): v_cvt_pk_bf16_f32, one
+// instruction where to_bf16's integer form takes ten
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bfloat2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bfloat2));
+}
+__device__ __forceinline__ bf16x4 round4(f32x4 v) {
+    const uint2 u = {pack2(v[0], v[1]), pack2(v[2], v[3])};
+    return __builtin_bit_cast(bf16x4, u);
+}
+
+constexpr f32x4 kZero4 = {0.f, 0.f, 0.f, 0.f};
+
+__device__ __forceinline__ f32x4 add4(f32x4 a, f32x4 b) { return a + b; }
+__device__ __forceinline__ f32x4 relu4(f32x4 a) {
+    return f32x4{fmaxf(a[0], 0.f), fmaxf(a[1], 0.f), fmaxf(a[2], 0.f), fmaxf(a[3], 0.f)};
+}
 
 // Workgroups of the training kernels that keep a weight gradient in their
 // registers over several sets, each leaving one partial sum.
@@ -102,6 +152,7 @@ struct WS {
     // partial sums: last two layers (8 a set), K3 and bias 2, bias 1 (2 a set, 64 each), K2, K1
     float *p34, *p3, *pc1, *p2, *p1;
     bf16_t* packed;   // packed weights of one pass, forward or training
+    bf16_t* x0h;      // the inference path's input of the first transposed convolution: b x 16 pixels x 16 channels
     size_t bytes;
 };
 

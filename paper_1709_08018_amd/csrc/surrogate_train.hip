@@ -12,7 +12,7 @@
 // What bounds it: the FP32 tensors a step leaves in the workspace (1.1 MB a
 // set, written once and read once or twice, 143 MB written at 128 sets) and
 // the latency of ten dependent launches; the products are 14 GFLOP.  A step
-// of 128 sets takes 160 us; with column matrices in memory (a GEMM into
+// of 128 sets takes 159 us; with column matrices in memory (a GEMM into
 // them or out of them per layer, 560 MB of columns) it took 1371 us.
 //
 // Sums that feed another rounding keep one fixed order (below, per kernel):
@@ -29,20 +29,6 @@ namespace sur {
 
 namespace {
 
-// 4-byte aligned vectors for global memory: callers may pass any float array
-typedef float f32x4g __attribute__((ext_vector_type(4), aligned(4)));
-typedef short bf16x4g __attribute__((ext_vector_type(4), aligned(4)));
-
-__device__ __forceinline__ f32x4 load4(const float* p) { return *(const f32x4g*)p; }
-__device__ __forceinline__ void store4(float* p, f32x4 v) { *(f32x4g*)p = v; }
-__device__ __forceinline__ bf16x4 loadw(const bf16_t* p) { return *(const bf16x4g*)p; }
-__device__ __forceinline__ bf16x4 lds4(const bf16_t* p) { return *(const bf16x4*)p; }   // 8-byte aligned LDS
-
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) { return (uint32_t)to_bf16(lo) | ((uint32_t)to_bf16(hi) << 16); }
-__device__ __forceinline__ bf16x4 round4(f32x4 v) {
-    const uint2 u = {pack2(v[0], v[1]), pack2(v[2], v[3])};
-    return __builtin_bit_cast(bf16x4, u);
-}
 // two consecutive LDS dwords as four bfloat16 values
 __device__ __forceinline__ bf16x4 lds_taps(const uint32_t* p) {
     const uint2 u = {p[0], p[1]};
@@ -55,12 +41,6 @@ __device__ __forceinline__ bf16x4 lds_stride2(const uint32_t* p, uint32_t sel) {
     return __builtin_bit_cast(bf16x4, u);
 }
 
-constexpr f32x4 kZero4 = {0.f, 0.f, 0.f, 0.f};
-
-__device__ __forceinline__ f32x4 add4(f32x4 a, f32x4 b) { return a + b; }
-__device__ __forceinline__ f32x4 relu4(f32x4 a) {
-    return f32x4{fmaxf(a[0], 0.f), fmaxf(a[1], 0.f), fmaxf(a[2], 0.f), fmaxf(a[3], 0.f)};
-}
 // g where the activation y is positive, else 0
 __device__ __forceinline__ f32x4 mask4(f32x4 g, f32x4 y) {
     f32x4 r;
@@ -104,37 +84,12 @@ int sum_chunk(int rows, int Co) {
 // others round the weights to bfloat16 in the order the products read them.
 __global__ __launch_bounds__(256) void prologue_kernel(const TrainArgs a, int mlp_blocks) {
     __shared__ __align__(16) bf16_t h1s[16 * 264];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if ((int)blockIdx.x >= mlp_blocks) {
-        const float *K1 = a.P + a.L.K1, *K2 = a.P + a.L.K2, *K3 = a.P + a.L.K3, *K4 = a.P + a.L.K4;
         const int stride = (int)(gridDim.x - mlp_blocks) * 256;
-        for (int e = ((int)blockIdx.x - mlp_blocks) * 256 + tid; e < (int)kTrainPacked; e += stride) {
-            float v;
-            if (e < (int)kT2f) {
-                const int c = e % 16, o = (e / 16) % 64, tap = e / 1024;
-                v = K1[(c * 64 + o) * 16 + tap];
-            } else if (e < (int)kT3f) {
-                const int i = e - (int)kT2f, c = i % 64, o = (i / 64) % 32, tap = (i / 2048) % 4, ph = i / 8192;
-                v = K2[((c * 32 + o) * 4 + tap_k(ph >> 1, tap >> 1)) * 4 + tap_k(ph & 1, tap & 1)];
-            } else if (e < (int)kT4f) {
-                const int i = e - (int)kT3f, c = i % 32, o = (i / 32) % 16, tap = (i / 512) % 4, ph = i / 2048;
-                v = K3[((c * 16 + o) * 4 + tap_k(ph >> 1, tap >> 1)) * 4 + tap_k(ph & 1, tap & 1)];
-            } else if (e < (int)kT1b) {
-                const int i = e - (int)kT4f;
-                v = K4[(i % 16) * 16 + i / 16];
-            } else if (e < (int)kT2b) {
-                v = K1[e - (int)kT1b];
-            } else if (e < (int)kT3b) {
-                v = K2[e - (int)kT2b];
-            } else if (e < (int)kT4b) {
-                v = K3[e - (int)kT3b];
-            } else if (e < (int)kT2w) {
-                v = K4[e - (int)kT4b];
-            } else {
-                v = a.P[a.L.W2 + (e - (int)kT2w)];
-            }
-            a.w.packed[e] = to_bf16(v);
-        }
+        for (int e = ((int)blockIdx.x - mlp_blocks) * 256 + tid; e < kTrainPacked; e += stride)
+            a.w.packed[e] = to_bf16(packed_weight(a.P, a.L, e));
         return;
     }
     const int b0 = ((int)blockIdx.x / 4) * 16, nb = (int)blockIdx.x % 4;
@@ -196,7 +151,8 @@ constexpr int kY1P = 64 + 8, kY2P = 32 + 8;   // bf16 per pixel in LDS, padded a
 
 __global__ __launch_bounds__(256) void conv12_kernel(const TrainArgs a) {
     __shared__ __align__(16) bf16_t y1s[6 * 18 * kY1P];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = (int)blockIdx.x >> 2, s = (int)blockIdx.x & 3;
     const bf16_t* T = a.w.packed;
     for (int i = tid; i < 6 * 18 * kY1P / 8; i += 256) ((uint4*)y1s)[i] = make_uint4(0, 0, 0, 0);
@@ -273,7 +229,8 @@ __global__ __launch_bounds__(512) void conv34_kernel(const TrainArgs a) {
     bf16_t* y3t = (bf16_t*)(lds + kStripBytes);              // [16][kY3T], once the columns are consumed
     float* red = (float*)(lds + kStripBytes + 16 * kY3T * 2);   // [8][256] and [8][32]
     static_assert(16 * kY3T * 2 + (8 * 256 + 8 * 32) * 4 <= 10 * 16 * kColW * 4, "scratch in the columns' space");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = (int)blockIdx.x >> 3, s = (int)blockIdx.x & 7;
     const bf16_t* T = a.w.packed;
 
@@ -431,7 +388,8 @@ __global__ __launch_bounds__(512) void back3_kernel(const TrainArgs a) {
     __shared__ __align__(16) uint32_t pl[16 * kD3P];
     __shared__ __align__(16) bf16_t y2t[32 * kY2T];
     __shared__ float red[8 * 32];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bf16_t* T = a.w.packed + kT3b;
     const int ky = lr >> 2, kx = lr & 3;
     const uint32_t sel = (kx & 1) ? 0x07060302u : 0x05040100u;
@@ -532,7 +490,8 @@ constexpr int kD2W = 18;                      // dwords of a dy2 plane row: entr
 __global__ __launch_bounds__(512) void back2_kernel(const TrainArgs a) {
     __shared__ __align__(16) uint32_t pl[32 * 18 * kD2W];
     __shared__ float red[2 * 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = (int)blockIdx.x >> 1, s = (int)blockIdx.x & 1;
     const int ct = wave & 3, r0 = 4 * (wave >> 2);
     bf16x4 w[32];
@@ -586,7 +545,8 @@ constexpr int kY1T = 256 + 8;
 __global__ __launch_bounds__(512) void grad2_kernel(const TrainArgs a) {
     __shared__ __align__(16) uint32_t pl[8 * 34 * kD2W];
     __shared__ __align__(16) bf16_t y1t[64 * kY1T];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int o0 = 8 * (int)blockIdx.y, ky = lr >> 2, kx = lr & 3;
     const uint32_t sel = (kx & 1) ? 0x07060302u : 0x05040100u;
     f32x4 g[4] = {kZero4, kZero4, kZero4, kZero4};
@@ -630,7 +590,8 @@ __global__ __launch_bounds__(512) void grad2_kernel(const TrainArgs a) {
 __global__ __launch_bounds__(512) void back1_kernel(const TrainArgs a) {
     __shared__ __align__(16) uint32_t pl[64 * (kY1T / 2)];
     __shared__ float dx[8 * 256];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bf16_t* plh = (const bf16_t*)pl;
     bf16x4 w[8];
 #pragma unroll
@@ -682,7 +643,8 @@ __global__ __launch_bounds__(512) void back1_kernel(const TrainArgs a) {
 // dh1 = (dh2 W2^T) masked by h1: 16 sets by 64 columns a workgroup, each
 // column tile the sum of its two halves of k.
 __global__ __launch_bounds__(256) void back_mlp_kernel(const TrainArgs a) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b0 = ((int)blockIdx.x / 4) * 16, n = (((int)blockIdx.x % 4) * 4 + wave) * 16 + lr;
     const int br = min(b0 + lr, a.B - 1);
     const float* dh2 = a.w.dh2 + (size_t)br * 256 + 4 * lq;
@@ -722,7 +684,8 @@ struct FinishArgs {
 
 __global__ __launch_bounds__(256) void finish_kernel(const TrainArgs a, const FinishArgs f, float* G) {
     __shared__ float red[256];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int blk = blockIdx.x;
     if (blk >= f.seg_blocks) {
         // x^T d over the sets, one 16 x 16 tile a wave: W2 (h1, dh2), W1 (u, dh1)
@@ -810,7 +773,8 @@ WS carve(void* base, int B) {
     w.pc1 = take(2 * b * 64);
     w.p2 = take((size_t)std::min(B, kParts2) * kPart2);
     w.p1 = take((size_t)std::min(B, kParts1) * kPart1);
-    w.packed = (bf16_t*)take((std::max(kPackedElems, kTrainPacked) + 1) / 2);
+    w.packed = (bf16_t*)take(((size_t)kTrainPacked + 1) / 2);
+    w.x0h = (bf16_t*)take(b * 128);
     w.bytes = o;
     return w;
 }

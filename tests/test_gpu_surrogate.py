@@ -399,3 +399,16 @@ def test_training_batches_with_several_sum_chains_and_passes(B):
     _close("grad W2", G["W2"], bf(h1).T @ bf(dh2), A(bf(h1)).T @ A(bf(dh2)), B)
     loss2, grad2 = kl.sur_loss_grad(_dev(flat), ta, tb, _dev(targets, torch.uint8))
     assert torch.equal(loss, loss2) and torch.equal(grad, grad2)
+
+
+def test_uncertainty_over_the_logits_range():
+    """Images of one logit each, from 0 to where e^-|x| underflows: the mean
+    entropy is that logit's, within 64 FP32 roundings (some 25 in the value,
+    and 38 additions of equal terms) and FP32's smallest normal number."""
+    x = np.array([0.0, 1e-6, -1e-3, 0.1, -0.7, 1.0, -3.0, 8.0, -16.0, 40.0, -80.0, 200.0, -3e38], np.float32)
+    u = kl.sur_uncertainty(_dev(np.broadcast_to(x[:, None, None], (len(x), 128, 128)))).cpu().numpy().astype(np.float64)
+    a = np.abs(x.astype(np.float64))
+    e = np.exp(-a)
+    ref = np.log1p(e) + a * (e / (1 + e))
+    assert (np.abs(u - ref) <= 64 * U32 * ref + 2.0 ** -126).all(), (u, ref)
+    assert np.isnan(kl.sur_uncertainty(_dev(np.full((1, 128, 128), np.nan))).item())
