@@ -49,7 +49,9 @@ __device__ void build_next6(uint16_t* next6) {
 }
 
 // Byte path (any depth, any destination): one word per thread, staged as
-// bytes, 256 words a tile, written as one contiguous byte range.
+// bytes, 256 words a tile, written as one contiguous byte range.  It serves
+// depths 1 .. 3 (36 words at most) and destinations that are not 16-byte
+// aligned.
 __device__ __forceinline__ void put_letters(uint64_t& lo, uint64_t& hi, int pos, uint64_t bits) {
     const int sh = 2 * pos;   // pos <= 39, bits < 2^12
     if (sh < 64) {
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(256) void decode_bytes_kernel(uint64_t first, uint6
     }
 }
 
-// Packed path: depths 16 .. 32 into a 16-byte aligned destination, one
+// Packed path: depths 4 .. 40 into a 16-byte aligned destination, one
 // kernel per depth D, so that every digit group, position and shift is a
 // constant.  The letters of a tile are staged in LDS as one stream, 2 bits a
 // letter, 16 letters a dword, in the order of the output bytes: dword i of
@@ -137,9 +139,10 @@ __global__ __launch_bounds__(256) void decode_bytes_kernel(uint64_t first, uint6
 //   * A thread takes K consecutive words, 2 D K bits of the stream: a whole
 //     number of dwords (K = 8 for even D, 16 for odd D).
 //   * The digits split into the first letter, HIGH groups of six, and a low
-//     part of LOW digits (3 .. 8: the short group, widened by six when it
-//     has fewer than three digits), so that the low part takes 3^LOW >= 27 >
-//     K values and carries out of it at most once among a thread's words.
+//     part of LOW digits (3 .. 9: the short group, widened by six when it
+//     has fewer than three digits, or at depth 40, so that the letters above
+//     it fit 64 bits), so that the low part takes 3^LOW >= 27 > K values and
+//     carries out of it at most once among a thread's words.
 //     The thread unranks its first word once, forms the letters above the
 //     low part for its high digits and for those plus one, and per word
 //     reads the low part's letters from the table and picks the high
@@ -147,6 +150,11 @@ __global__ __launch_bounds__(256) void decode_bytes_kernel(uint64_t first, uint6
 //   * A piece spreads its 16 letters to 16 bytes: bytes q of x and of
 //     x >> 4 go to bytes 0 and 2 of a dword, and (v | v << 6) & 0x03030303
 //     moves letters 1 and 3 of the four into bytes 1 and 3.
+// What bounds it: the HBM writes, D bytes a word (5.4 TB/s at depth 18 and
+// 2^26 words); below some 20 MB the build of the table in every workgroup
+// and the launch.  Every word but a few of depth 13 (27.6 MB): 9.9 us,
+// on the byte path 24.2; 2^20 words of depth 37 (38.8 MB): 10.3 us
+// against 24.2; 16,000,001 words of depth 15: 38.3 against 144.5 us.
 constexpr uint32_t pow3u(int e) {
     uint32_t v = 1;
     for (int i = 0; i < e; ++i) v *= 3;
@@ -157,20 +165,22 @@ template <int D>
 struct PackedDecode {
     static constexpr int N = D - 1;                         // base-3 digits after the first letter
     static constexpr int P = N % 6;
-    static constexpr int LOW = P >= 3 ? P : P + 6;          // digits of the low part
+    static constexpr int LOW = P >= 3 && D < 40 ? P : P + 6; // digits of the low part
     static constexpr uint32_t RADIX = pow3u(LOW);
     static constexpr int HIGH = (N - LOW) / 6;              // groups of six above it
     static constexpr int LOWPOS = 1 + 6 * HIGH;             // position of its first letter
     static constexpr int K = D % 2 ? 16 : 8;                // words per thread
     static constexpr int SEG = D * K / 16;                  // stream dwords per thread
     static constexpr uint32_t TILE = 256u * K;              // words per tile
-    static_assert(D >= 16 && D <= 32 && HIGH >= 2 && RADIX > (uint32_t)K && 2 * D <= 64, "packed decode layout");
+    static constexpr int GROUPS = HIGH > 0 ? HIGH : 1;      // array size
+    static_assert(D >= 4 && D <= 40 && LOW >= 3 && LOW <= 9 && RADIX > (uint32_t)K && 2 * LOWPOS <= 64,
+                  "packed decode layout");
 };
 
 // Letters 0 .. LOWPOS - 1 (first letter and the HIGH groups, g[HIGH - 1]
 // most significant), and the last of them.
-template <int HIGH>
-__device__ __forceinline__ uint64_t high_letters(uint32_t f, const uint32_t (&g)[HIGH], const uint16_t* next6,
+template <int HIGH, int N>
+__device__ __forceinline__ uint64_t high_letters(uint32_t f, const uint32_t (&g)[N], const uint16_t* next6,
                                                  uint32_t& last) {
     uint64_t L = f;
     uint32_t prev = f;
@@ -186,8 +196,8 @@ __device__ __forceinline__ uint64_t high_letters(uint32_t f, const uint32_t (&g)
 
 // Letters of the low part (2 LOW bits) of word k of a thread, from the
 // table entry e of its first six digits (LOW <= 6: the entry's last 6 - LOW
-// letters, of padding digits, are cut off; LOW = 7, 8: a second entry gives
-// the last LOW - 6 letters).
+// letters, of padding digits, are cut off; LOW = 7 .. 9: a second entry
+// gives the last LOW - 6 letters).
 template <int LOW>
 __device__ __forceinline__ uint32_t low_letters(const uint16_t* next6, uint32_t e, uint32_t l2) {
     const uint32_t a = next6[e];
@@ -213,6 +223,22 @@ __device__ __forceinline__ uint4 spread16(uint32_t x) {
     return make_uint4(spread_quarter(x, y, 0), spread_quarter(x, y, 1), spread_quarter(x, y, 2), spread_quarter(x, y, 3));
 }
 
+// f(integral_constant k) for each k of the sequence
+template <typename F, int... K>
+__device__ __forceinline__ void each_word(F&& f, std::integer_sequence<int, K...>) {
+    (f(std::integral_constant<int, K>{}), ...);
+}
+
+// ORs the BITS low bits of v into a thread's segment, from bit AT on.
+template <int AT, int BITS, int SEG>
+__device__ __forceinline__ void put_bits(uint32_t (&seg)[SEG], uint64_t v) {
+#pragma unroll
+    for (int j = AT / 32; j <= (AT + BITS - 1) / 32; ++j) {
+        const int sh = 32 * j - AT;
+        seg[j] |= sh >= 0 ? (uint32_t)(v >> sh) : (uint32_t)(v << -sh);
+    }
+}
+
 template <int D>
 __global__ __launch_bounds__(256) void decode_packed_kernel(uint64_t first, uint64_t count, uint8_t* __restrict__ out) {
     using L = PackedDecode<D>;
@@ -232,7 +258,7 @@ __global__ __launch_bounds__(256) void decode_packed_kernel(uint64_t first, uint
             const uint64_t r = first + tfirst + w0;
             const uint64_t h = r / L::RADIX;
             const uint32_t l0 = (uint32_t)(r - h * L::RADIX);
-            uint32_t g[L::HIGH], g1[L::HIGH], f;
+            uint32_t g[L::GROUPS], g1[L::GROUPS], f;
             if constexpr (L::HIGH <= 3) {   // h < 4 * 729^3 < 2^32
                 uint32_t x = (uint32_t)h;
 #pragma unroll
@@ -263,8 +289,8 @@ __global__ __launch_bounds__(256) void decode_packed_kernel(uint64_t first, uint
             }
             const uint32_t f1 = f + c < 3u ? f + c : 3u;
             uint32_t prev0, prev1;
-            const uint64_t H0 = high_letters<L::HIGH>(f, g, next6, prev0);
-            const uint64_t H1 = high_letters<L::HIGH>(f1, g1, next6, prev1);
+            const uint64_t H0 = high_letters<L::HIGH, L::GROUPS>(f, g, next6, prev0);
+            const uint64_t H1 = high_letters<L::HIGH, L::GROUPS>(f1, g1, next6, prev1);
             // Table entry of the low part's first six digits: before the
             // wrap e0 + k S (S = 3^(6 - LOW), or per six-digit step for LOW >
             // 6), after it e1 + k S, so a word's entry is a select plus a
@@ -278,10 +304,10 @@ __global__ __launch_bounds__(256) void decode_packed_kernel(uint64_t first, uint
             uint32_t seg[L::SEG];
 #pragma unroll
             for (int j = 0; j < L::SEG; ++j) seg[j] = 0;
-#pragma unroll
-            for (int k = 0; k < L::K; ++k) {
-                // words past the range's end are formed too (from clamped
-                // digits) and never written out
+            // words past the range's end are formed too (from clamped digits)
+            // and never written out
+            auto word = [&](auto kc) {
+                constexpr int k = decltype(kc)::value;
                 const bool wrap = l0 >= L::RADIX - (uint32_t)k;
                 uint32_t lowb;
                 if constexpr (L::LOW <= 6) {
@@ -291,14 +317,15 @@ __global__ __launch_bounds__(256) void decode_packed_kernel(uint64_t first, uint
                     const uint32_t h6 = l / R2;
                     lowb = low_letters<L::LOW>(next6, (wrap ? e1 : e0) + h6, l - h6 * R2);
                 }
-                const uint64_t W = (wrap ? H1 : H0) | ((uint64_t)lowb << (2 * L::LOWPOS));
-                const int s = 2 * D * k;   // the word's first bit in the thread's segment
-#pragma unroll
-                for (int j = s / 32; j <= (s + 2 * D - 1) / 32; ++j) {
-                    const int sh = 32 * j - s;
-                    seg[j] |= sh >= 0 ? (uint32_t)(W >> sh) : (uint32_t)(W << -sh);
+                constexpr int at = 2 * D * k;   // the word's first bit in the thread's segment
+                if constexpr (D <= 32) {
+                    put_bits<at, 2 * D>(seg, (wrap ? H1 : H0) | ((uint64_t)lowb << (2 * L::LOWPOS)));
+                } else {
+                    put_bits<at, 2 * L::LOWPOS>(seg, wrap ? H1 : H0);
+                    put_bits<at + 2 * L::LOWPOS, 2 * L::LOW>(seg, lowb);
                 }
-            }
+            };
+            each_word(word, std::make_integer_sequence<int, L::K>{});
             uint32_t* mine = stream + tid * L::SEG;
 #pragma unroll
             for (int j = 0; j < L::SEG; ++j) mine[j] = seg[j];
@@ -320,31 +347,34 @@ __global__ __launch_bounds__(256) void decode_packed_kernel(uint64_t first, uint
     }
 }
 
+constexpr int kPackedMin = 4, kPackedDepths = KL_MAX_DEPTH + 1 - kPackedMin;
+
 using DecodeKernel = void (*)(uint64_t, uint64_t, uint8_t*);
 
 template <int... I>
 static constexpr std::array<DecodeKernel, sizeof...(I)> packed_decode_kernels(std::integer_sequence<int, I...>) {
-    return {{decode_packed_kernel<16 + I>...}};
+    return {{decode_packed_kernel<kPackedMin + I>...}};
 }
 
 template <int... I>
 static constexpr std::array<uint32_t, sizeof...(I)> packed_tile_words(std::integer_sequence<int, I...>) {
-    return {{PackedDecode<16 + I>::TILE...}};
+    return {{PackedDecode<kPackedMin + I>::TILE...}};
 }
 
 hipError_t launch_decode(uint64_t first, uint64_t count, int depth, uint8_t* out, hipStream_t s) {
     if (count == 0) return hipSuccess;
-    static constexpr std::array<DecodeKernel, 17> kPacked = packed_decode_kernels(std::make_integer_sequence<int, 17>{});
-    static constexpr std::array<uint32_t, 17> kTile = packed_tile_words(std::make_integer_sequence<int, 17>{});
-    const bool pack = depth >= 16 && depth <= 32 && ((uintptr_t)out & 15u) == 0;
-    const void* fn = pack ? reinterpret_cast<const void*>(kPacked[depth - 16])
+    using Depths = std::make_integer_sequence<int, kPackedDepths>;
+    static constexpr std::array<DecodeKernel, kPackedDepths> kPacked = packed_decode_kernels(Depths{});
+    static constexpr std::array<uint32_t, kPackedDepths> kTile = packed_tile_words(Depths{});
+    const bool pack = depth >= kPackedMin && ((uintptr_t)out & 15u) == 0;
+    const void* fn = pack ? reinterpret_cast<const void*>(kPacked[depth - kPackedMin])
                           : reinterpret_cast<const void*>(decode_bytes_kernel);
-    const uint64_t tile_words = pack ? kTile[depth - 16] : 256;
+    const uint64_t tile_words = pack ? kTile[depth - kPackedMin] : 256;
     const uint64_t tiles = (count + tile_words - 1) / tile_words;
     // as many workgroups as fit on a CU at once, so that none waits for a
     // second round (the same on every gfx950 device; asked once per kernel)
-    static std::atomic<int> fits[18];
-    const int slot = pack ? depth - 16 : 17;
+    static std::atomic<int> fits[kPackedDepths + 1];
+    const int slot = pack ? depth - kPackedMin : kPackedDepths;
     int resident = fits[slot].load(std::memory_order_relaxed);
     if (resident == 0) {
         int n = 0;

@@ -105,6 +105,33 @@ def test_decode_packed_path_every_word_of_ranges(depth):
     assert (host[:3] == 255).all() and (host[3 + count * depth:] == 255).all()
 
 
+@pytest.mark.parametrize("depth", [*range(4, 16), *range(33, 41)])
+def test_decode_packed_path_shallow_and_deepest_depths(depth):
+    """Depths 4..15 and 33..40 take the packed stream too: with no group of
+    six above the low part (4..9), with one (10..15), and with words longer
+    than 64 bits, formed in two fields (33..40; the low part of depth 40 has
+    nine digits).  Ranges around wraps of the low part and of the group above
+    it, across tiles of 2048 (even depths) and 4096 words, and to the last
+    word, against the oracle's unranking; and the whole range's bytes against
+    the byte path's (a misaligned destination)."""
+    n = kl.num_words(depth)
+    p = (depth - 1) % 6
+    radix = 3 ** (p if p >= 3 and depth < 40 else p + 6)
+    starts = [0, radix - 13, 2 * radix - 1, radix * 729 - 7, 3 * radix * 729 - 5, n // 3 + 7, n - 4111, n - 1]
+    counts = [4111, 33, 300, 40, 2049, 4097, 4111, 1]
+    for first, count in zip(starts, counts):
+        first = max(0, min(first, n - 1))
+        count = min(count, n - first)
+        got = kl.decode(first, count, depth).cpu().numpy()
+        np.testing.assert_array_equal(got, np.stack([O.unrank(first + j, depth) for j in range(count)]))
+    first = n // 5
+    count = min(70_001, n - first)
+    buf = torch.full((count * depth + 16,), 255, dtype=torch.uint8, device="cuda")
+    view = buf[1:1 + count * depth]
+    kl._check(kl.lib().kl_decode_ex(first, count, depth, view.data_ptr(), kl._stream(None)))
+    assert torch.equal(kl.decode(first, count, depth).ravel(), view)
+
+
 @pytest.mark.parametrize("depth,count", [(18, 12_000_000), (17, 12_000_000), (32, 9_000_000), (40, 3_000_000)])
 def test_decode_many_tiles_per_workgroup(depth, count):
     """Ranges long enough that every workgroup takes many tiles: rows at both
