@@ -103,15 +103,36 @@ __device__ inline CayleyHead cayley_head(const CayleyJob& a, const m64& M) {
     return h;
 }
 
+// Pole form at the point y.
+__device__ __forceinline__ void cayley_pole_word(const CayleyHead& h, c64 y, double& px, double& py) {
+    const double ur = y.re + h.S.re, ui = y.im + h.S.im;
+    const double rc = cayley_recip(fma_(ur, ur, ui * ui));
+    px = fma_(fma_(h.ax, ur, h.bx * ui), rc, h.Px);
+    py = fma_(fma_(h.ay, ur, h.by * ui), rc, h.Py);
+}
+
+// Run key of a word: the saturating int32 floors of its pixel coordinates,
+// (row, column), in the window exactly when both are (cayley_bin's rule).
+// v_cvt_i32_f64 maps NaN to 0, so px goes through a maximum with -1, which
+// keeps the number: a NaN px is outside.  In the pole form, whose guards keep
+// every other factor finite, px and py are NaN together (with the
+// reciprocal); elsewhere the caller checks.
+constexpr uint64_t kCayleyOutsideKey = ~0ull;
+__device__ __forceinline__ int cayley_floor(double x) {
+    int r;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(__builtin_floor(x)));
+    return r;
+}
+__device__ __forceinline__ uint64_t cayley_pole_key(double px, double py) {
+    return (uint64_t)(uint32_t)cayley_floor(__builtin_fmax(px, -1.0)) | ((uint64_t)(uint32_t)cayley_floor(py) << 32);
+}
+
 // Pixel coordinates of head . tail from the tail's stored point (u : v): the
 // pole form where the head has one and the point is (y : 1), else the ratio
 // form.  Render and eval both come here, so their values agree bit for bit.
 __device__ inline void cayley_word(const CayleyJob& a, const CayleyHead& h, c64 u, c64 v, double& px, double& py) {
     if (h.pole && v.re == 1.0 && v.im == 0.0) {
-        const double ur = u.re + h.S.re, ui = u.im + h.S.im;
-        const double rc = cayley_recip(fma_(ur, ur, ui * ui));
-        px = fma_(fma_(h.ax, ur, h.bx * ui), rc, h.Px);
-        py = fma_(fma_(h.ay, ur, h.by * ui), rc, h.Py);
+        cayley_pole_word(h, u, px, py);
     } else {
         cayley_pixel(a, cfma(h.M.a, u, cmul(h.M.b, v)), cfma(h.M.c, u, cmul(h.M.d, v)), px, py);
     }
@@ -238,8 +259,9 @@ __global__ __launch_bounds__(256) void cayley_kernel(const CayleyJob a) {
         }
     };
     // the seed of a word whose last symbol is `last` (0-based), homogeneous
+    const int seed = MODE == kCayleyRender ? a.seed_list[blockIdx.y] : a.seed;   // a render's seeds: one grid row each
     auto seed_point = [&](int last, c64& u, c64& v) {
-        const int sd = a.seed < 0 ? last : a.seed;
+        const int sd = seed < 0 ? last : seed;
         u = a.fix[sd];
         v = {1.0, 0.0};
         if ((a.inf_mask >> sd) & 1u) {
@@ -384,19 +406,31 @@ __global__ __launch_bounds__(256) void cayley_kernel(const CayleyJob a) {
 // the first and last of its heads.  The arithmetic of a word is that of
 // cayley_kernel: the head's FP64 product left to right, then cayley_pixel.
 //
-// LDS, sized from the table (HeadLayout): C, CM and NH rows for lengths
-// 0..D, the set automaton, the maps, the tail table, and per depth the
-// range's head offsets.
+// The counts CM and NH satisfy the same recurrence over the good sets,
+//   CM[L][g] = sum over x of CM[L - 1][next_set(g, x)],
+// from CM[0][g] = [state 0 in g] and NH[0][g] = [CM[r][g] > 0], so one wave
+// forms both with a lane per good set.  A thread takes a whole head, or, when
+// the launch has more threads than heads, one of `parts` slices of its tails.
+//
+// LDS, sized from the table (HeadLayout): CM and NH rows for lengths 0..D,
+// the set automaton, the tail table, and per depth the range's head offsets.
 struct HeadLayout {
-    // byte offsets: C, CM, NH rows ([(D + 1) * S], [(D + 1) * M] twice); per
-    // depth (index d - min_depth) the range's first head HA, the prefix of
-    // head counts HS and the word range WA, WB; the tail points TU, TV; the
-    // maps G; the sets SETS; the automaton NX; the tail end states TS; and
-    // per good set g the tails it accepts, in table order, at AL[g * n_tails]
-    uint32_t C, CM, NH, HA, HS, WA, WB, TU, TV, G, SETS, NX, TS, AL, TB, A, total;
+    // byte offsets: the job; CM, NH rows ([(D + 1) * (M + 1)], entry M of a
+    // row zero); per good set its successors, a byte a symbol (NX, M for none);
+    // per depth (index d - min_depth) the range's first head HA, the prefix of
+    // head counts HS and the word range WA, WB; the tail points TU, TV, their
+    // end states TS; and per good set g the tails it accepts, in table order,
+    // at AL[g * stride]
+    uint32_t job, CM, NH, NX, HA, HS, WA, WB, TU, TV, TS, AL, total;
 };
 
-__host__ __device__ inline HeadLayout cayley_head_layout(int S, int M, int m, int D, int n_tails, int n_seeds) {
+// entries of a good set's tail list, padded to whole groups of kCayleyGroup
+constexpr int kCayleyGroup = 4;
+__host__ __device__ inline int cayley_list_stride(int n_tails) {
+    return (n_tails + kCayleyGroup - 1) / kCayleyGroup * kCayleyGroup;
+}
+
+__host__ __device__ inline HeadLayout cayley_head_layout(int M, int D, int n_tails, int n_seeds) {
     HeadLayout L;
     uint32_t off = 0;
     auto take = [&](uint32_t bytes) {
@@ -405,103 +439,145 @@ __host__ __device__ inline HeadLayout cayley_head_layout(int S, int M, int m, in
         return at;
     };
     const uint32_t rows = (uint32_t)(D + 1);
-    L.C = take(rows * (uint32_t)S * 8u);
-    L.CM = take(rows * (uint32_t)M * 8u);
-    L.NH = take(rows * (uint32_t)M * 8u);
+    L.job = take((uint32_t)sizeof(CayleyJob));
+    L.CM = take(rows * (uint32_t)(M + 1) * 8u);
+    L.NH = take(rows * (uint32_t)(M + 1) * 8u);
+    L.NX = take((uint32_t)M * 8u);
     L.HA = take((KL_MAX_DEPTH + 1) * 8u);
     L.HS = take((KL_MAX_DEPTH + 2) * 8u);
     L.WA = take((KL_MAX_DEPTH + 1) * 8u);
     L.WB = take((KL_MAX_DEPTH + 1) * 8u);
     L.TU = take((uint32_t)n_seeds * (uint32_t)n_tails * (uint32_t)sizeof(c64));
     L.TV = take((uint32_t)n_seeds * (uint32_t)n_tails * (uint32_t)sizeof(c64));
-    L.G = take((uint32_t)m * (uint32_t)sizeof(m64));
-    L.SETS = take((uint32_t)M * 2u);
-    L.NX = take((uint32_t)M * (uint32_t)m);
     L.TS = take((uint32_t)n_tails);
-    L.AL = take((uint32_t)M * (uint32_t)n_tails * 2u);
-    L.TB = take((uint32_t)S * (uint32_t)(m + 1));
-    L.A = take((uint32_t)S * (uint32_t)S);
+    L.AL = take((uint32_t)M * (uint32_t)cayley_list_stride(n_tails) * 2u);
     L.total = off;
     return L;
 }
 
-// Workgroup of the head kernel.  Every workgroup builds the count tables
-// and its seeds' tail tables in LDS, and two of them share a CU: 512 threads
-// give 16 waves a CU to hide the latency of the FP64 head products and LDS
-// reads.  On Table 2 at depth 16 and the PSL(2, Z) tiling, 256 threads took
-// 0.215 / 0.225 ms, 512 threads 0.167 / 0.198 ms, 768 0.195 / 0.195 ms, 1024
-// 0.19 / 0.26 ms; 512 threads with four workgroups a CU 0.169 / 0.236 ms.
-constexpr unsigned kCayleyHeadBlock = 512;
-
-__global__ __launch_bounds__(kCayleyHeadBlock) void cayley_head_kernel(const CayleyJob a) {
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int S = a.S, m = a.m, M = a.n_sets, D = a.max_depth, r = a.r;
-    const int NT = a.n_tails, NS = a.n_seeds;
-    const HeadLayout lay = cayley_head_layout(S, M, m, D, NT, NS);
-    struct {
-        uint64_t *C, *CM, *NH, *HA, *HS, *WA, *WB;
-        c64 *TU, *TV;
-        m64* G;
-        uint16_t* SETS;
-        uint8_t *NX, *TS;
-        uint16_t* AL;
-        uint8_t *TB, *A;
-    } q = {(uint64_t*)(lds + lay.C), (uint64_t*)(lds + lay.CM), (uint64_t*)(lds + lay.NH), (uint64_t*)(lds + lay.HA),
-           (uint64_t*)(lds + lay.HS), (uint64_t*)(lds + lay.WA), (uint64_t*)(lds + lay.WB), (c64*)(lds + lay.TU),
-           (c64*)(lds + lay.TV), (m64*)(lds + lay.G), (uint16_t*)(lds + lay.SETS), (uint8_t*)(lds + lay.NX),
-           (uint8_t*)(lds + lay.TS), (uint16_t*)(lds + lay.AL), (uint8_t*)(lds + lay.TB), (uint8_t*)(lds + lay.A)};
-    for (int i = threadIdx.x; i < M * m; i += blockDim.x) q.NX[i] = a.next_set[i];
-    for (int i = threadIdx.x; i < M; i += blockDim.x) q.SETS[i] = a.sets[i];
-    for (int i = threadIdx.x; i < m; i += blockDim.x) q.G[i] = a.maps[i];
-    for (int i = threadIdx.x; i < S * (m + 1); i += blockDim.x) q.TB[i] = a.table[i];
-    __syncthreads();
-    cayley_counts(q.TB, q.A, q.C, S, S, m, D);
-    for (int i = threadIdx.x; i < (D + 1) * M; i += blockDim.x) {
-        const int L = i / M, g = i - L * M;
-        uint64_t n = 0;
-        for (int s = 0; s < S; ++s)
-            if ((q.SETS[g] >> s) & 1u) n += q.C[L * S + s];
-        q.CM[i] = n;
-    }
-    __syncthreads();
-    // heads of L more symbols that accept at least one tail: the first wave,
-    // one lane per good set, one length after another
-    static_assert(kCayleyMaxSets <= kWave, "one lane per good set");
-    if (threadIdx.x < (unsigned)kWave) {
-        const int g = threadIdx.x;
-        if (g < M) q.NH[g] = q.CM[r * M + g] > 0 ? 1 : 0;
-        wave_sync();
-        for (int L = 1; L + r <= D; ++L) {
-            if (g < M) {
-                uint64_t n = 0;
-                for (int x = 1; x <= m; ++x) n += q.NH[(L - 1) * M + q.NX[g * m + x - 1]];
-                q.NH[L * M + g] = n;
-            }
-            wave_sync();
+// The symbol (x, 0-based) of rank `local` among the successors nx of a good
+// set, symbol x leading to n[nx byte x] words: local becomes the rank within
+// that symbol's words, g its good set, and `skipped` grows by the `also`
+// counts of the symbols before it.  All counts are read together; bytes past
+// the last symbol name an entry that is zero.
+template <bool ALSO>
+__device__ __forceinline__ void choose_symbol(const uint64_t* n, const uint64_t* also, uint64_t nx, bool wide,
+                                              uint64_t& local, int& x, int& g, uint64_t& skipped) {
+    uint64_t cum = 0, below = 0, cum2 = 0, below2 = 0;
+    x = 0;
+    auto four = [&](int y0) {
+        uint64_t c[4], c2[4];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            const int to = (int)((nx >> (8 * (y0 + y))) & 255u);
+            c[y] = n[to];
+            if (ALSO) c2[y] = also[to];
         }
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            cum += c[y];
+            const bool past = local >= cum;
+            x += past ? 1 : 0;
+            below = past ? cum : below;
+            if (ALSO) {
+                cum2 += c2[y];
+                below2 = past ? cum2 : below2;
+            }
+        }
+    };
+    four(0);
+    if (wide) four(4);
+    local -= below;
+    if (ALSO) skipped += below2;
+    g = (int)((nx >> (8 * x)) & 255u);
+}
+
+// Workgroup of the head kernel: 512 threads, two workgroups a CU, 16 waves a
+// CU to hide the latency of the FP64 head products and LDS reads; every
+// workgroup builds the tables above in LDS.
+//
+// What bounds it: at depth 16 of the once-punctured torus table (57.4 M
+// words) the words' FP64 instructions, some 25 a word; at shallow depths the
+// chain of dependent LDS reads that builds the tables, hence the counts by
+// shuffles, the symbols' counts read together, the job copied to LDS in one
+// load, and one wave a good set for the tail lists.  Table 2 at depth 16:
+// 92.5 us a call, with one thread a list, counts through LDS and a range
+// test per word 156.8; depth 7: 15.5 against 102; the PSL(2, Z) tiling to
+// depth 38 from three seeds: 114 against 160.
+constexpr unsigned kCayleyHeadBlock = 512;
+constexpr uint64_t kCayleyMaxParts = 16;   // slices of a head's tails: a thread keeps some 15 words
+
+__global__ __launch_bounds__(kCayleyHeadBlock) void cayley_head_kernel(const CayleyJob job, const int M, const int D,
+                                                                       const int NT, const int NS) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ uint32_t odd_slots;   // seeds with a tail that is not stored as (y : 1)
+    const HeadLayout lay = cayley_head_layout(M, D, NT, NS);
+    const CayleyJob& a = *(const CayleyJob*)(lds + lay.job);
+    uint64_t *CM = (uint64_t*)(lds + lay.CM), *NH = (uint64_t*)(lds + lay.NH), *NX = (uint64_t*)(lds + lay.NX);
+    uint64_t *HA = (uint64_t*)(lds + lay.HA), *HS = (uint64_t*)(lds + lay.HS), *WA = (uint64_t*)(lds + lay.WA),
+             *WB = (uint64_t*)(lds + lay.WB);
+    c64 *TU_all = (c64*)(lds + lay.TU), *TV_all = (c64*)(lds + lay.TV);
+    uint8_t* TS = (uint8_t*)(lds + lay.TS);
+    uint16_t* AL = (uint16_t*)(lds + lay.AL);
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int M1 = M + 1, LA = cayley_list_stride(NT);
+    static_assert(sizeof(CayleyJob) % 4 == 0, "copied by dwords");
+    for (uint32_t i = threadIdx.x; i < sizeof(CayleyJob) / 4; i += blockDim.x)
+        ((uint32_t*)(lds + lay.job))[i] = ((const uint32_t*)&job)[i];
+    if (threadIdx.x == 0) odd_slots = 0;
+    __syncthreads();
+    const int m = a.m, r = a.r;
+    const bool wide = m > 4;
+    static_assert(kCayleyMaxSets <= kWave, "one lane per good set");
+    if (wave == 0) {
+        uint64_t nx = 0;
+        for (int x = 0; x < 8; ++x) nx |= (uint64_t)(x < m && lane < M ? a.next_set[lane * m + x] : M) << (8 * x);
+        if (lane < M) NX[lane] = nx;
+        uint64_t cm = lane < M ? a.sets[lane] & 1u : 0u, nh = 0;
+        for (int L = 0;; ++L) {
+            if (L == r) nh = cm > 0 ? 1 : 0;
+            if (lane <= M) {
+                CM[L * M1 + lane] = cm;
+                if (L >= r) NH[(L - r) * M1 + lane] = nh;
+            }
+            if (L == D) break;
+            uint64_t c = 0, h = 0;
+            auto four = [&](int y0) {
+#pragma unroll
+                for (int y = y0; y < y0 + 4; ++y) {
+                    // a set index of M (no symbol) names lane M, or with 64 sets none
+                    const int to = (int)((nx >> (8 * y)) & 255u);
+                    const uint64_t cv = __shfl(cm, to & (kWave - 1), kWave), hv = __shfl(nh, to & (kWave - 1), kWave);
+                    c += to < M ? cv : 0;
+                    h += to < M ? hv : 0;
+                }
+            };
+            four(0);
+            if (wide) four(4);
+            cm = lane < M ? c : 0;
+            nh = lane < M ? h : 0;
+        }
+        // with 64 sets no lane holds the rows' zero entry
+        if (M == kWave && lane <= D) CM[lane * M1 + M] = NH[lane * M1 + M] = 0;
     }
     __syncthreads();
     // the tail table: regular words of length r in lexicographic order, their
     // end states, and their points from each seed in turn (TU[slot * NT + t])
     for (int e = threadIdx.x; e < NS * NT; e += blockDim.x) {
         const int slot = e / NT, t = e - slot * NT;
-        uint64_t local = (uint64_t)t, lo = 0, hi = 0;
+        uint64_t local = (uint64_t)t, lo = 0, hi = 0, unused = 0;
         int g = 0;
         for (int j = 0; j < r; ++j) {
-            int x = 1, gx = 0;
-            for (; x <= m; ++x) {
-                gx = q.NX[g * m + x - 1];
-                const uint64_t n = q.CM[(r - j - 1) * M + gx];
-                if (local < n) break;
-                local -= n;
-            }
-            g = gx;
-            if (j < 21) lo |= (uint64_t)(x - 1) << (3 * j);
-            else hi |= (uint64_t)(x - 1) << (3 * (j - 21));
+            int x;
+            choose_symbol<false>(CM + (r - j - 1) * M1, nullptr, NX[g], wide, local, x, g, unused);
+            if (j < 21) lo |= (uint64_t)x << (3 * j);
+            else hi |= (uint64_t)x << (3 * (j - 21));
         }
-        int s = 0;
-        for (int j = r - 1; j >= 0; --j) s = q.TB[s * (m + 1) + packed_symbol(lo, hi, j) + 1];
-        if (slot == 0) q.TS[t] = (uint8_t)s;
+        if (slot == 0) {
+            int s = 0;
+            for (int j = r - 1; j >= 0; --j) s = a.table[s * (m + 1) + packed_symbol(lo, hi, j) + 1];
+            TS[t] = (uint8_t)s;
+        }
         const int last = packed_symbol(lo, hi, r - 1);
         const int sd = a.seed_list[slot] < 0 ? last : a.seed_list[slot];
         c64 u = a.fix[sd], v = {1.0, 0.0};
@@ -510,124 +586,171 @@ __global__ __launch_bounds__(kCayleyHeadBlock) void cayley_head_kernel(const Cay
             v = {0.0, 0.0};
         }
         for (int j = r - 1; j >= 0; --j) {
-            const m64& Gx = q.G[packed_symbol(lo, hi, j)];
+            const m64& Gx = a.maps[packed_symbol(lo, hi, j)];
             const c64 nu = cfma(Gx.a, u, cmul(Gx.b, v));
             const c64 nv = cfma(Gx.c, u, cmul(Gx.d, v));
             u = nu;
             v = nv;
         }
         cayley_tail_normalize(u, v);
-        q.TU[e] = u;
-        q.TV[e] = v;
-    }
-    __syncthreads();
-    // per good set, the tails it accepts in table order
-    for (int g = threadIdx.x; g < M; g += blockDim.x) {
-        int k = 0;
-        for (int t = 0; t < a.n_tails; ++t)
-            if ((q.SETS[g] >> q.TS[t]) & 1u) q.AL[g * a.n_tails + k++] = (uint16_t)t;
+        TU_all[e] = u;
+        TV_all[e] = v;
+        if (!(v.re == 1.0 && v.im == 0.0)) atomicOr(&odd_slots, 1u << slot);
     }
     // per depth: the range's local word interval and the heads it touches
     const int d0 = r > a.min_depth ? r : a.min_depth;
     for (int e = threadIdx.x; e < 2 * (D - d0 + 1); e += blockDim.x) {
-        const int d = d0 + e / 2, di = d - a.min_depth;
+        const int d = d0 + e / 2, di = d - a.min_depth, hl = d - r;
         const uint64_t s0 = a.depth_start[di], s1 = a.depth_start[di + 1];
         const uint64_t lo_w = a.first > s0 ? a.first - s0 : 0;
         const uint64_t end = a.first + a.count;
         const uint64_t hi_w = end < s1 ? (end > s0 ? end - s0 : 0) : s1 - s0;
         if (e % 2 == 0) {
-            q.WA[di] = lo_w;
-            q.WB[di] = hi_w;
+            WA[di] = lo_w;
+            WB[di] = hi_w;
         }
-        // rank of the head of word lo_w (e even) or hi_w - 1 (e odd)
+        // rank of the head of word lo_w (e even) or hi_w - 1 (e odd): the
+        // first or last of its depth where the range does not cut it
         uint64_t hr = 0;
         if (hi_w > lo_w) {
-            uint64_t local = e % 2 == 0 ? lo_w : hi_w - 1;
-            const int hl = d - r;
-            int g = 0;
-            for (int j = 0; j < hl; ++j) {
-                int x = 1, gx = 0;
-                for (; x <= m; ++x) {
-                    gx = q.NX[g * m + x - 1];
-                    const uint64_t n = q.CM[(d - j - 1) * M + gx];
-                    if (local < n) break;
-                    local -= n;
-                    hr += q.NH[(hl - j - 1) * M + gx];
-                }
-                g = gx;
+            if (e % 2 ? end >= s1 : lo_w == 0) {
+                hr = e % 2 ? NH[hl * M1] - 1 : 0;
+            } else {
+                uint64_t local = e % 2 == 0 ? lo_w : hi_w - 1;
+                int g = 0, x;
+                for (int j = 0; j < hl; ++j)
+                    choose_symbol<true>(CM + (d - j - 1) * M1, NH + (hl - j - 1) * M1, NX[g], wide, local, x, g, hr);
             }
         }
-        if (e % 2 == 0) q.HA[di] = hr;
-        else q.HS[di] = hr;   // the last head, turned into a count below
+        if (e % 2 == 0) HA[di] = hr;
+        else HS[di] = hr;   // the last head, turned into a count below
     }
     __syncthreads();
+    // per good set, the tails it accepts in table order (as byte offsets of
+    // their points): one wave a set, 64 tails at a time
+    for (int g = wave; g < M; g += (int)(blockDim.x / kWave)) {
+        const uint32_t set = a.sets[g];
+        int k = 0;
+        for (int t0 = 0; t0 < NT; t0 += kWave) {
+            const int t = t0 + lane;
+            const bool in = t < NT && ((set >> TS[t]) & 1u);
+            const uint64_t b = __ballot(in);
+            if (in) AL[g * LA + k + __popcll(b & ((1ull << lane) - 1))] = (uint16_t)(t * sizeof(c64));
+            k += __popcll(b);
+        }
+    }
     if (threadIdx.x == 0) {
         uint64_t total = 0;
         for (int d = d0; d <= D; ++d) {
             const int di = d - a.min_depth;
-            const uint64_t n = q.WB[di] > q.WA[di] ? q.HS[di] - q.HA[di] + 1 : 0;
-            q.HS[di] = total;
+            const uint64_t n = WB[di] > WA[di] ? HS[di] - HA[di] + 1 : 0;
+            HS[di] = total;
             total += n;
         }
-        q.HS[D - a.min_depth + 1] = total;
+        HS[D - a.min_depth + 1] = total;
     }
     __syncthreads();
 
-    // (seed, head) pairs, seed-major so that the lanes of a wave share a seed
-    const uint64_t total = q.HS[D - a.min_depth + 1];
-    uint64_t drop = 0;
-    uint32_t run_key = kCayleyOutside, run_len = 0;
+    // (seed, head, part) triples, seed-major so that the lanes of a wave share
+    // a seed, a head's parts on neighbouring lanes
+    const uint64_t total = HS[D - a.min_depth + 1];
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t uu = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; uu < total * (uint64_t)NS; uu += stride) {
-        const int slot = (int)(uu / total);
-        const uint64_t u = uu - (uint64_t)slot * total;
-        const c64* TU = q.TU + (size_t)slot * NT;
-        const c64* TV = q.TV + (size_t)slot * NT;
+    const uint64_t heads = total * (uint64_t)NS;
+    const uint32_t parts = heads ? (uint32_t)max((uint64_t)1, min(kCayleyMaxParts, stride / heads)) : 1u;
+    uint64_t drop = 0;
+    uint64_t run_key = kCayleyOutsideKey;
+    uint32_t run_len = 0;
+    const uint32_t W = job.W, H = job.H;
+    uint32_t* image = job.image;   // from the argument: an address read from LDS would make flat atomics
+    auto close_run = [&]() {
+        const uint32_t col = (uint32_t)run_key, row = (uint32_t)(run_key >> 32);
+        if ((col < W) & (row < H)) {
+            if (run_len) atomicAdd(image + __umul24(row, W) + col, run_len);
+        } else {
+            drop += run_len;
+        }
+        run_len = 0;
+    };
+    auto emit = [&](uint64_t key) {
+        if (key != run_key) {
+            close_run();
+            run_key = key;
+        }
+        ++run_len;
+    };
+    for (uint64_t uu = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; uu < heads * parts; uu += stride) {
+        const uint64_t hu = parts == 1 ? uu : uu / parts;
+        const uint32_t part = (uint32_t)(uu - hu * parts);
+        const int slot = hu < total ? 0 : (int)(hu / total);
+        const uint64_t u = hu - (uint64_t)slot * total;
+        const unsigned char* TU = (const unsigned char*)(TU_all + (size_t)slot * NT);
+        const unsigned char* TV = (const unsigned char*)(TV_all + (size_t)slot * NT);
         int d = d0;
-        while (u >= q.HS[d + 1 - a.min_depth]) ++d;
+        while (u >= HS[d + 1 - a.min_depth]) ++d;
         const int di = d - a.min_depth, hl = d - r;
-        uint64_t hh = q.HA[di] + (u - q.HS[di]);
+        uint64_t hh = HA[di] + (u - HS[di]);
         // unrank the head by NH; the skipped CM counts give its first word
         int g = 0;
         uint64_t wstart = 0;
         m64 Mh = {{1.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {1.0, 0.0}};
         for (int j = 0; j < hl; ++j) {
-            int x = 1, gx = 0;
-            for (; x <= m; ++x) {
-                gx = q.NX[g * m + x - 1];
-                const uint64_t n = q.NH[(hl - j - 1) * M + gx];
-                if (hh < n) break;
-                hh -= n;
-                wstart += q.CM[(d - j - 1) * M + gx];
-            }
-            g = gx;
-            Mh = mmul(Mh, q.G[x - 1]);
+            int x;
+            choose_symbol<true>(NH + (hl - j - 1) * M1, CM + (d - j - 1) * M1, NX[g], wide, hh, x, g, wstart);
+            Mh = mmul(Mh, a.maps[x]);
         }
-        // this head's accepted tails with ordinals in [o0, o1) are words of the range
-        const uint64_t wa = q.WA[di], wb = q.WB[di], n_acc = q.CM[r * M + g];
-        const uint32_t o0 = (uint32_t)(wa > wstart ? wa - wstart : 0);
-        const uint32_t o1 = (uint32_t)(wb - wstart < n_acc ? wb - wstart : n_acc);
-        const uint16_t* list = q.AL + (size_t)g * a.n_tails;
+        // this head's accepted tails with ordinals in [o0, o1) are words of the
+        // range, this part's share of them (whole groups)
+        const uint64_t wa = WA[di], wb = WB[di], n_acc = CM[r * M1 + g];
+        uint32_t o0 = (uint32_t)(wa > wstart ? wa - wstart : 0);
+        uint32_t o1 = (uint32_t)(wb - wstart < n_acc ? wb - wstart : n_acc);
+        if (parts > 1) {
+            const uint32_t per = (uint32_t)((n_acc + kCayleyGroup * parts - 1) / (kCayleyGroup * parts)) * kCayleyGroup;
+            o0 = max(o0, part * per);
+            o1 = min(o1, (part + 1) * per);
+        }
+        const uint16_t* list = AL + (size_t)g * LA;
         const CayleyHead ch = cayley_head(a, Mh);
-        for (uint32_t i = o0; i < o1; ++i) {
-            const int t = list[i];
-            double px, py;
-            cayley_word(a, ch, TU[t], TV[t], px, py);
-            const uint32_t key = cayley_bin(px, py, a.W, a.H);
-            if (key != run_key) {
-                if (run_key == kCayleyOutside) drop += run_len;
-                else if (run_len) atomicAdd(a.image + run_key, run_len);
-                run_key = key;
-                run_len = 0;
+        uint32_t i = o0;
+        if (ch.pole && !((odd_slots >> slot) & 1u)) {
+            // every tail is (y : 1): groups of kCayleyGroup tails, their list
+            // entries in one read and their points read before use
+            auto one = [&](uint32_t off) {
+                double px, py;
+                cayley_pole_word(ch, *(const c64*)(TU + off), px, py);
+                emit(cayley_pole_key(px, py));
+            };
+            for (; i < o1 && (i & (kCayleyGroup - 1)); ++i) one(list[i]);
+            for (; i + kCayleyGroup <= o1; i += kCayleyGroup) {
+                const uint2 w = *(const uint2*)(list + i);
+                const uint32_t off[kCayleyGroup] = {w.x & 0xFFFFu, w.x >> 16, w.y & 0xFFFFu, w.y >> 16};
+                c64 y[kCayleyGroup];
+                uint64_t key[kCayleyGroup];
+#pragma unroll
+                for (int e = 0; e < kCayleyGroup; ++e) y[e] = *(const c64*)(TU + off[e]);
+#pragma unroll
+                for (int e = 0; e < kCayleyGroup; ++e) {
+                    double px, py;
+                    cayley_pole_word(ch, y[e], px, py);
+                    key[e] = cayley_pole_key(px, py);
+                }
+#pragma unroll
+                for (int e = 0; e < kCayleyGroup; ++e) emit(key[e]);
             }
-            ++run_len;
+            for (; i < o1; ++i) one(list[i]);
+        } else {
+            for (; i < o1; ++i) {
+                const uint32_t off = list[i];
+                double px, py;
+                cayley_word(a, ch, *(const c64*)(TU + off), *(const c64*)(TV + off), px, py);
+                const bool number = (px == px) & (py == py);
+                emit(number ? cayley_pole_key(px, py) : kCayleyOutsideKey);
+            }
         }
     }
-    if (run_key == kCayleyOutside) drop += run_len;
-    else if (run_len) atomicAdd(a.image + run_key, run_len);
-    if (a.dropped) {
+    close_run();
+    if (job.dropped) {
         for (int off = kWave / 2; off > 0; off >>= 1) drop += __shfl_down(drop, off, kWave);
-        if ((threadIdx.x & (kWave - 1)) == 0 && drop) atomicAdd((unsigned long long*)a.dropped, (unsigned long long)drop);
+        if (lane == 0 && drop) atomicAdd((unsigned long long*)job.dropped, (unsigned long long)drop);
     }
 }
 
@@ -645,39 +768,34 @@ hipError_t launch_cayley(const CayleyJob& job, int mode, hipStream_t s) {
             h.first = j.first > B ? j.first : B;
             h.count = end - h.first;
             // as many seeds per launch as their tail tables fit the LDS of a CU
-            const size_t cap = 160 * 1024;
+            const size_t cap = 160 * 1024 - 16;   // less the kernel's static LDS
             int per = j.n_seeds;
-            while (per > 1 && cayley_head_layout(j.S, j.n_sets, j.m, j.max_depth, j.n_tails, per).total > cap) --per;
+            while (per > 1 && cayley_head_layout(j.n_sets, j.max_depth, j.n_tails, per).total > cap) --per;
             for (int k0 = 0; k0 < j.n_seeds; k0 += per) {
                 h.n_seeds = std::min(per, j.n_seeds - k0);
                 for (int k = 0; k < h.n_seeds; ++k) h.seed_list[k] = j.seed_list[k0 + k];
-                const size_t lds = cayley_head_layout(j.S, j.n_sets, j.m, j.max_depth, j.n_tails, h.n_seeds).total;
+                const size_t lds = cayley_head_layout(j.n_sets, j.max_depth, j.n_tails, h.n_seeds).total;
                 if (lds > 65536) {
                     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(cayley_head_kernel),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
                     if (e != hipSuccess) return e;
                 }
                 hipLaunchKernelGGL(cayley_head_kernel, dim3((unsigned)std::max(1, j.grid_blocks)), dim3(kCayleyHeadBlock),
-                                   lds, s, h);
+                                   lds, s, h, h.n_sets, h.max_depth, h.n_tails, h.n_seeds);
                 hipError_t e = hipGetLastError();
                 if (e != hipSuccess) return e;
             }
         }
         if (j.first >= B) return hipSuccess;
         // the words shorter than r, each walked in full by a thread of its own
-        // (no tail table), one launch per seed
+        // (no tail table)
         j.count = (end < B ? end : B) - j.first;
         j.r = 0;
         j.n_tails = 0;
         j.run = 1;
         const uint64_t blocks = std::min<uint64_t>((j.count + 255) / 256, (uint64_t)std::max(1, j.grid_blocks));
-        for (int k = 0; k < j.n_seeds; ++k) {
-            j.seed = j.seed_list[k];
-            hipLaunchKernelGGL(cayley_kernel<kCayleyRender>, dim3((unsigned)blocks), dim3(256), 0, s, j);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+        hipLaunchKernelGGL(cayley_kernel<kCayleyRender>, dim3((unsigned)blocks, (unsigned)j.n_seeds), dim3(256), 0, s, j);
+        return hipGetLastError();
     }
     const uint64_t per = mode == kCayleyRender ? (uint64_t)j.run : 1;
     uint64_t blocks = (j.count + 256 * per - 1) / (256 * per);

@@ -251,3 +251,36 @@ def test_largest_table():
             assert int(dropped.item()) == drop
         rimg, _, near = O.cayley_render(ref, depth, win, seed=s, min_depth=mind, edge_tol=1e-7)
         assert int(np.abs(img - rimg.astype(np.int64)).sum()) <= 2 * near, (depth, seed)
+
+
+@pytest.mark.parametrize("case", ["t11", "maskit", "klein4", "modular", "largest"])
+@pytest.mark.parametrize("depth", [5, 6, 8, 9])
+def test_head_slices_ranges_and_seeds(case, depth):
+    """A render gives each head's tails to one thread, or slices of them to up
+    to 16 when heads are few (the depths here), in groups of four; index
+    ranges cut the first and last head anywhere.  Ranges from 1 word to all,
+    with every seed and each table's own count of symbols and sets, against
+    the histogram of the words' own evaluated bins.  Maskit's maps (a
+    translation, whose seeds and some tails lie at infinity, and heads with
+    c = 0) and the Klein group's (0 and infinity) take the ratio form."""
+    if case == "largest":
+        table, maps = _largest_table()
+        depth = min(depth, 6)
+    else:
+        table = {"t11": T11, "maskit": T11, "klein4": KLEIN4, "modular": MODULAR}[case]
+        maps = {"t11": _recipe_maps, "maskit": lambda: O.group_maskit(wl.MASKIT_MU).gens, "klein4": lambda: K4_MAPS,
+                "modular": lambda: MOD_MAPS}[case]()
+    t = kl.Cayley(table, maps)
+    win = (-1.7, 1.9, -1.3, 2.2, 211, 187)
+    n = kl.cayley_num_words(t, depth)
+    rng = np.random.default_rng(depth)
+    cuts = [(0, n), (n // 3, 1), (max(0, n - 2), min(2, n))]
+    cuts += [(int(a), int(rng.integers(1, n - a + 1))) for a in rng.integers(0, n, size=3)]
+    for seed in ["own", *range(2, 2 + table.shape[1] - 1)]:
+        p = kl.cayley_eval(t, depth, np.arange(n, dtype=np.uint64), window=win, seed=seed).cpu().numpy()
+        for first, count in cuts:
+            dropped = torch.zeros(1, dtype=torch.int64, device="cuda")
+            img = kl.as_u32(kl.cayley_render(t, depth, win, first=first, count=count, seed=seed, dropped=dropped))
+            own, drop = _bins(p[first:first + count, 0], p[first:first + count, 1], win)
+            np.testing.assert_array_equal(img.astype(np.int64), own, err_msg=f"{seed} {first} {count}")
+            assert int(dropped.item()) == drop
