@@ -331,7 +331,9 @@ int plan_split(int depth, int precision, int r_req, int m_req, Split* sp, PlanCo
 }
 
 // ------------------------------------------------------------------ temporaries
-// Largest table set that the per-device table cache holds.
+// Largest table set that the per-device table cache holds.  Letting it grow to
+// 128 MB, so that a batch of 256 sets of depths 12..18 (79 to 110 MB of tables)
+// fits, was tried and dropped: 10.86 against 10.93 ms a batch.
 constexpr size_t kTableCacheMax = size_t(64) << 20;
 
 // Stream-ordered temporaries of one call, freed on its stream when the call
@@ -864,15 +866,16 @@ struct SetSpec {
     uint64_t* dropped;
 };
 
-// Many sets in a few launches: one table launch builds every set's prefix
-// and suffix tables, one persistent launch renders the sets the persistent
-// kernel takes (whole heads), one per-word launch renders the rest.  Sets
+// Many sets in a few launches: one set-up launch clears the outputs (unless
+// accumulating) and builds every set's prefix and suffix tables, one
+// persistent launch renders the sets the persistent kernel takes (whole
+// heads), one per-word launch renders the rest.  Sets
 // may share an image and a dropped counter.  Every word is evaluated with
 // its set's split and tables, bit for bit as a single render of that set.
 // The descriptors are uploaded from host memory; the call waits for those
 // copies (not for the renders) before it returns.
 static int render_sets(const std::vector<SetSpec>& specs, const kl_window* w, const kl_opts& o, int wpc,
-                       hipStream_t s) {
+                       uint32_t* image, uint64_t bins, uint64_t n_dropped, hipStream_t s) {
     const int nb = (int)specs.size();
     if (nb == 0) return KL_OK;
     const size_t esz = o.precision == KL_PREC_FP64 ? sizeof(c64) : sizeof(c32);
@@ -886,8 +889,11 @@ static int render_sets(const std::vector<SetSpec>& specs, const kl_window* w, co
         max_prefix = std::max(max_prefix, np);
         max_tail = std::max(max_tail, nt);
     }
-    // every temporary in one allocation: the descriptors (uploaded together)
-    // then the tables
+    // every temporary in one buffer: the descriptors (uploaded together) then
+    // the tables; on the null stream the device's cached one, where they fit
+    // it (kTableCacheMax).  Rendering larger batches in groups that fit was
+    // tried and dropped: two groups of the 256 sets of depths 12..18 ran their
+    // kernels in 10.55 ms against 10.02, each ending in a last round of blocks.
     std::vector<SetDesc> h_sets(nb), h_psets;
     std::vector<uint64_t> h_off(1, 0), h_woff(1, 0);
     std::vector<int> h_ids;
@@ -921,7 +927,7 @@ static int render_sets(const std::vector<SetSpec>& specs, const kl_window* w, co
     Temp tmp(s);
     unsigned char* base = nullptr;
     hipError_t e;
-    if ((e = tmp.alloc((void**)&base, off)) != hipSuccess) return hip_fail(e, "batch temporaries");
+    if ((e = tmp.tables((void**)&base, off)) != hipSuccess) return hip_fail(e, "batch temporaries");
     SetDesc* d_sets = (SetDesc*)(base + o_sets);
     SetDesc* d_psets = (SetDesc*)(base + o_psets);
     uint64_t* d_off = (uint64_t*)(base + o_off);
@@ -984,7 +990,13 @@ static int render_sets(const std::vector<SetSpec>& specs, const kl_window* w, co
     job.force_homog = o.suffix_form;
     job.count_dropped = o.dropped_out != nullptr;
     job.bounded = o.block_bounds;
-    if (e == hipSuccess) e = launch_batch_tables(job, s);
+    if (!o.accumulate) {
+        job.clear_image = image;
+        job.clear_bins = bins;
+        job.clear_dropped = o.dropped_out;
+        job.n_dropped = n_dropped;
+    }
+    if (e == hipSuccess) e = launch_batch_setup(job, s);
     if (e == hipSuccess && np_sets) {
         BatchJob pj = job;
         pj.sets = d_psets;
@@ -1035,14 +1047,7 @@ static int render_tiling(const Gens& G, int depth, const kl_window* w, uint32_t*
             if (!wpc && d == depth) wpc = od.waves_per_cu;
             specs.push_back({G, sp, sd, image, o.dropped_out});
         }
-    if (!o.accumulate) {
-        hipError_t e;
-        if ((e = launch_fill_u32(image, (uint64_t)w->width * w->height, 0, s)) != hipSuccess)
-            return hip_fail(e, "clear image");
-        if (o.dropped_out && (e = launch_fill_u64(o.dropped_out, 1, 0, s)) != hipSuccess)
-            return hip_fail(e, "clear dropped");
-    }
-    return render_sets(specs, w, o, wpc, s);
+    return render_sets(specs, w, o, wpc, image, (uint64_t)w->width * w->height, 1, s);
 }
 
 // The render itself, once every argument has been checked.  KL_SEED_ALL is
@@ -1665,19 +1670,13 @@ static int render_many_run(int n, const kl_c64* ta, const kl_c64* tb, const int*
         }
     }
     hipStream_t s = (hipStream_t)o.stream;
-    hipError_t e;
-    if (!o.accumulate) {
-        if ((e = launch_fill_u32(images_out, bins * (uint64_t)n, 0, s)) != hipSuccess) return hip_fail(e, "clear images");
-        if (o.dropped_out && (e = launch_fill_u64(o.dropped_out, (uint64_t)n, 0, s)) != hipSuccess)
-            return hip_fail(e, "clear dropped");
-    }
     std::vector<SetSpec> specs(n);
     int wpc = o.waves_per_cu ? o.waves_per_cu : (bp ? bp->wpc : 0);
     for (int i = 0; i < n; ++i) {
         specs[i] = {gens[i], splits[i], seed_index(o), images_out + bins * i, o.dropped_out ? o.dropped_out + i : nullptr};
         if (!wpc && persistent_ok(splits[i])) wpc = per[i].waves_per_cu;
     }
-    return render_sets(specs, window, o, wpc, s);
+    return render_sets(specs, window, o, wpc, images_out, bins * (uint64_t)n, (uint64_t)n, s);
 }
 
 // Median time of a batched render with plans bp (one untimed run first).

@@ -187,8 +187,12 @@ struct BatchJob {
     int force_homog;
     int count_dropped;             // the sets' dropped counters are set
     int bounded;                   // block bounds in the persistent batch kernel (kl_opts::block_bounds)
+    uint32_t* clear_image;         // cleared by the set-up launch, or null (accumulating render)
+    uint64_t clear_bins;
+    uint64_t* clear_dropped;       // n_dropped counters cleared with the image, or null
+    uint64_t n_dropped;
 };
-hipError_t launch_batch_tables(const BatchJob& job, hipStream_t s);
+hipError_t launch_batch_setup(const BatchJob& job, hipStream_t s);
 hipError_t launch_render_batch(const BatchJob& job, hipStream_t s);
 
 // Every word of the sets too shallow for the persistent kernel, one per
