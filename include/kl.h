@@ -46,10 +46,12 @@
  *           others are host pointers.  The caller owns every buffer; the
  *           library never frees caller memory.  The library allocates its
  *           own temporaries with hipMallocAsync on the call's stream; calls
- *           on the null stream keep their prefix and suffix tables in one
- *           buffer per device instead (1 MiB growing to at most 64 MiB,
- *           held until the process ends), which calls on other streams,
- *           or on another host thread while one holds it, do not touch.
+ *           on the null stream keep their tables and staged points in one
+ *           buffer per device instead (1 MiB growing to at most 192 MiB; up
+ *           to 64 MiB held until the process ends, more than that given back
+ *           after 32 calls in a row that did not need it), which calls on
+ *           other streams, or on another host thread while one holds it, do
+ *           not touch.
  * streams   the plain entry points run on the null stream and return after
  *           the device has finished; the *_ex entry points enqueue on
  *           opts->stream (a hipStream_t, NULL = null stream) and return at
@@ -364,7 +366,8 @@ int kl_walk_eval_ex(const kl_c64 *ab, const kl_walk *walk, const kl_window *wind
  *   KL_HIST_RUNS  one global atomic add per point in the window;
  *   KL_HIST_LDS   each workgroup's points of 8 steps sorted by image tile
  *                 (2^15 bins) in LDS and staged in device temporaries
- *                 (2 bytes a point, allocated on the stream), then counted
+ *                 (2 bytes a point, in the library's buffer on the null
+ *                 stream, else allocated on the stream), then counted
  *                 tile by tile in LDS; images of at most 256 tiles
  *                 (8,388,608 bins), at most 524,288 drawn points a walker;
  *   KL_HIST_AUTO  KL_HIST_LDS from 2^18 points up where it applies, else

@@ -217,6 +217,7 @@ static Fold make_fold(const kl_window* w, int head_form) {
 struct TableCache {
     void* base = nullptr;
     size_t bytes = 0;
+    int idle = 0;        // calls in a row that a buffer of kTableCacheKeep bytes would have served
     bool busy = false;   // leased to a call that is still enqueuing its kernels
 };
 
@@ -331,10 +332,14 @@ int plan_split(int depth, int precision, int r_req, int m_req, Split* sp, PlanCo
 }
 
 // ------------------------------------------------------------------ temporaries
-// Largest table set that the per-device table cache holds.  Letting it grow to
-// 128 MB, so that a batch of 256 sets of depths 12..18 (79 to 110 MB of tables)
-// fits, was tried and dropped: 10.86 against 10.93 ms a batch.
-constexpr size_t kTableCacheMax = size_t(64) << 20;
+// Largest buffer that the per-device table cache holds, and the size above
+// which it is given back after kTableCacheIdle calls in a row that a buffer of
+// that size would have served.  A walk render of 2^26 points takes 152 MB, a
+// batch of 256 sets of depths 12..18 some 110: mapped and unmapped on each call,
+// as the stream-ordered allocator does around a synchronisation, they cost 420
+// and 400 us beside 200 us and 9.9 ms of kernels.
+constexpr size_t kTableCacheMax = size_t(192) << 20, kTableCacheKeep = size_t(64) << 20;
+constexpr int kTableCacheIdle = 32;
 
 // Stream-ordered temporaries of one call, freed on its stream when the call
 // returns.  tables() lends the call its device's cached table buffer instead
@@ -366,7 +371,8 @@ struct Temp {
             std::lock_guard<std::mutex> lk(g_dev_mutex);
             TableCache& c = g_devs[dev].tables;
             if (!c.busy) {
-                if (c.bytes < bytes) {
+                c.idle = bytes > kTableCacheKeep ? 0 : std::min(c.idle + 1, kTableCacheIdle);
+                if (c.bytes < bytes || (c.bytes > kTableCacheKeep && c.idle == kTableCacheIdle)) {
                     if (c.base) (void)hipFreeAsync(c.base, s);
                     c.base = nullptr;
                     c.bytes = 0;
@@ -1328,11 +1334,17 @@ int kl_walk_render_ex(const kl_c64* ab, const kl_walk* walk, const kl_window* wi
     j.W = window->width;
     j.H = window->height;
     j.dropped = o.dropped_out;
-    e = o.hist_mode == KL_HIST_LDS || (o.hist_mode == KL_HIST_AUTO && np >= (1ull << 18) &&
+    if (o.hist_mode == KL_HIST_LDS || (o.hist_mode == KL_HIST_AUTO && np >= (1ull << 18) &&
                                        walk_tiles(j.W, j.H) <= kMaxWalkTiles &&
-                                       walk_region_points(walk->n_steps) <= kWalkBinnedPoints)
-            ? launch_walk_binned(j, s)
-            : launch_walk(j, s);
+                                       walk_region_points(walk->n_steps) <= kWalkBinnedPoints)) {
+        Temp tmp(s);
+        const WalkBinned L = walk_binned_layout(j);
+        void* buf = nullptr;
+        if (L.blocks && (e = tmp.tables(&buf, L.bytes)) != hipSuccess) return hip_fail(e, "walk temporaries");
+        e = launch_walk_binned(j, L, buf, s);
+    } else {
+        e = launch_walk(j, s);
+    }
     return e == hipSuccess ? KL_OK : hip_fail(e, "walk kernel");
 }
 

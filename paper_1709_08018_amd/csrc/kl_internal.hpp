@@ -278,7 +278,12 @@ constexpr uint32_t kMaxWalkTiles = 256;
 constexpr uint64_t kWalkBinnedPoints = 1ull << 27;
 uint32_t walk_tiles(uint32_t W, uint32_t H);
 uint64_t walk_region_points(uint32_t n_steps);
-hipError_t launch_walk_binned(const WalkJob& j, hipStream_t s);
+struct WalkBinned {
+    uint64_t blocks;           // workgroups of walkers a launch; 0: nothing to draw
+    size_t off_starts, bytes;
+};
+WalkBinned walk_binned_layout(const WalkJob& j);
+hipError_t launch_walk_binned(const WalkJob& j, const WalkBinned& L, void* buf, hipStream_t s);
 
 int device_cu_count();
 

@@ -28,11 +28,14 @@
 // infinity outside).  The points of a walk jump across the limit set, so
 // there are no runs to merge, and a global atomic per point (walk_kernel)
 // costs a cache line per lane.  The binned path (walk_bin_kernel,
-// walk_tile_hist_kernel) instead sorts each workgroup's points of 8 steps
-// by image tile of 2^15 bins in LDS and writes them out as 16-bit offsets
-// within their tiles; a second kernel counts each tile's offsets in an LDS
-// histogram and adds its non-zero bins to the image.
+// walk_tile_hist_kernel) instead sorts each workgroup's points of one Philox
+// block (8 steps) by image tile of 2^15 bins in LDS and writes them out as
+// 16-bit offsets within their tiles; a second kernel counts each tile's
+// offsets in an LDS histogram and adds its non-zero bins to the image.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "kl_internal.hpp"
 
@@ -86,9 +89,17 @@ __device__ __forceinline__ void philox4x64_10(uint64_t c0, uint64_t c1, uint64_t
 // bin of pixel coordinates, the renderer's rule; kWalkOutside when outside
 constexpr uint32_t kWalkOutside = 0xFFFFFFFFu;
 
+// FP32: on the floors, saturating int32 (v_cvt_flr_i32_f32; NaN to 0, so NaNs
+// are told apart by an ordered comparison), as the renderer bins
+__device__ __forceinline__ int walk_floor(float x) {
+    int r;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
 __device__ __forceinline__ uint32_t walk_bin(float px, float py, uint32_t W, uint32_t H) {
-    const bool ok = (px >= 0.0f) & (px < (float)W) & (py >= 0.0f) & (py < (float)H);
-    return ok ? (uint32_t)__builtin_floorf(py) * W + (uint32_t)__builtin_floorf(px) : kWalkOutside;
+    const uint32_t col = (uint32_t)walk_floor(px), row = (uint32_t)walk_floor(py);
+    const bool ok = (col < W) & (row < H) & !__builtin_isunordered(px, py);
+    return ok ? __umul24(row, W) + col : kWalkOutside;
 }
 
 __device__ __forceinline__ uint32_t walk_bin(double px, double py, uint32_t W, uint32_t H) {
@@ -149,176 +160,232 @@ __device__ __forceinline__ void load_walk_maps(const WalkJob& j, WalkMaps<T>& m)
     }
 }
 
-// The walk of one walker: letters c_0 .. c_{n_total - 1} (letter(k, c)),
-// and after each step k > burn_in its drawn point in the window's pixel
-// coordinates (point(d, px, py), d = k - burn_in - 1).  All walkers of a
-// launch take the same steps, so calls happen at the same k in every lane
-// (`active` lanes without a walker step along on walker 0's stream and
-// report nothing).
-template <typename T, typename Letter, typename Point>
-__device__ __forceinline__ void walk_walker(const WalkJob& j, const WalkMaps<T>& m, uint64_t walker, bool active,
-                                            Letter letter, Point point) {
-    const uint32_t n_total = 1 + j.burn_in + j.n_steps;
-    const T s = (T)j.fold.s, ox = (T)j.fold.o.re, oy = (T)j.fold.o.im, an = (T)j.fold.aniso;
-    cpx<T> u = {T(0), T(0)}, v = {T(1), T(0)};
-    int prev = 0;
-    uint32_t k = 0;
-    for (uint64_t blk = 0; k < n_total; ++blk) {
-        uint64_t r[4];
-        philox4x64_10(blk, walker, 0, 0, j.seed, 0, r);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (k < n_total) {
-                const uint32_t x = (uint32_t)(r[i >> 1] >> (32 * (i & 1)));
-                int c;
-                if (k == 0) {
-                    c = (int)(x >> 30);
-                    u = m.SU[c];
-                    v = m.SV[c];
-                } else {
-                    const int t = (int)__umulhi(x, 3u);
-                    c = t + (t >= (prev ^ 2));
-                    const mat<T> g = m.G[c];
-                    const cpx<T> nu = cfma(g.a, u, cmul(g.b, v));
-                    const cpx<T> nv = cfma(g.c, u, cmul(g.d, v));
-                    u = nu;
-                    v = nv;
-                }
-                if (active) letter(k, c);
-                if (k > j.burn_in) {
-                    // z = u / v, then the window's affine map s z + o (x anisotropy on the real part)
-                    const T n2 = fma_(v.re, v.re, v.im * v.im);
-                    const T rc = walk_recip(n2);
-                    const T zr = fma_(u.re, v.re, u.im * v.im) * rc;
-                    const T zi = fma_(u.im, v.re, -(u.re * v.im)) * rc;
-                    const T px = fma_(s, zr, ox) * an, py = fma_(s, zi, oy);
-                    point(k - j.burn_in - 1, px, py, active);
-                }
-                prev = c;
-                ++k;
-            }
-        }
-        walk_rescale(u, v);
-    }
+// One walker's state, and its step k (x: value k of its stream), k > burn_in
+// giving the drawn point in the window's pixel coordinates.
+template <typename T>
+struct Walker {
+    cpx<T> u, v;
+    int prev;
+};
+
+template <typename T>
+struct WalkFold {
+    T s, ox, oy, an;
+};
+
+template <typename T>
+__device__ __forceinline__ int walk_letter(const Walker<T>& w, uint32_t k, uint32_t x) {
+    if (k == 0) return (int)(x >> 30);
+    const int t = (int)__umulhi(x, 3u);
+    return t + (t >= (w.prev ^ 2));
 }
 
-// Letters, points or a render with one global atomic per point.
 template <typename T>
+__device__ __forceinline__ void walk_step(Walker<T>& w, const WalkMaps<T>& m, uint32_t k, int c) {
+    if (k == 0) {
+        w.u = m.SU[c];
+        w.v = m.SV[c];
+    } else {
+        const mat<T> g = m.G[c];
+        const cpx<T> nu = cfma(g.a, w.u, cmul(g.b, w.v));
+        const cpx<T> nv = cfma(g.c, w.u, cmul(g.d, w.v));
+        w.u = nu;
+        w.v = nv;
+    }
+    w.prev = c;
+}
+
+// z = u / v, then the window's affine map s z + o (x anisotropy on the real part)
+template <typename T>
+__device__ __forceinline__ void walk_pixel(const Walker<T>& w, const WalkFold<T>& f, T& px, T& py) {
+    const T n2 = fma_(w.v.re, w.v.re, w.v.im * w.v.im);
+    const T rc = walk_recip(n2);
+    const T zr = fma_(w.u.re, w.v.re, w.u.im * w.v.im) * rc;
+    const T zi = fma_(w.u.im, w.v.re, -(w.u.re * w.v.im)) * rc;
+    px = fma_(f.s, zr, f.ox) * f.an;
+    py = fma_(f.s, zi, f.oy);
+}
+
+template <typename T>
+__device__ __forceinline__ WalkFold<T> walk_fold(const WalkJob& j) {
+    return {(T)j.fold.s, (T)j.fold.o.re, (T)j.fold.o.im, (T)j.fold.aniso};
+}
+
+// Letters, points or a render with one global atomic per point.  A small walk
+// is bound by its serial chain (letter, matrix from LDS, product), so a block
+// of eight steps that are all drawn goes without conditions between them,
+// which lets the letters and matrices of later steps be fetched during
+// earlier products.  1,754 walkers of 118 steps: 36.2 us in FP64 and 31.1
+// in FP32, with a condition per step 45.1 and 41.5.
+template <typename T, int MODE>
 __global__ __launch_bounds__(256) void walk_kernel(const WalkJob j) {
     __shared__ WalkMaps<T> m;
     load_walk_maps(j, m);
     __syncthreads();
     const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    uint64_t drop = 0;
+    uint32_t drop = 0;   // at most n_steps
     if (tid < j.n_walkers) {
         const uint32_t n_total = 1 + j.burn_in + j.n_steps;
-        walk_walker<T>(j, m, j.first_walker + tid, true,
-                       [&](uint32_t k, int c) {
-                           if (j.mode == kWalkLetters) j.letters[tid * n_total + k] = (uint8_t)c;
-                       },
-                       [&](uint32_t d, T px, T py, bool) {
-                           const uint64_t p = tid * j.n_steps + d;
-                           if (j.mode == kWalkEval) {
-                               j.z_out[p] = {(double)px, (double)py};
-                           } else if (j.mode == kWalkRender) {
-                               const uint32_t b = walk_bin(px, py, j.W, j.H);
-                               if (b != kWalkOutside) atomicAdd(j.image + b, 1u);
-                               else ++drop;
-                           }
-                       });
+        const WalkFold<T> f = walk_fold<T>(j);
+        Walker<T> w = {{T(0), T(0)}, {T(1), T(0)}, 0};
+        for (uint64_t blk = 0; blk * 8 < n_total; ++blk) {   // 64 bits: n_total may be 2^32 - 1
+            const uint32_t k0 = (uint32_t)(blk * 8);
+            uint64_t r[4];
+            philox4x64_10(blk, j.first_walker + tid, 0, 0, j.seed, 0, r);
+            // inner: every step of the block is drawn (and none is the first)
+            auto steps = [&](auto inner) {
+#pragma unroll
+                for (uint32_t i = 0; i < 8; ++i) {
+                    const uint32_t k = inner.value ? 1u : k0 + i;
+                    if (!inner.value && i >= n_total - k0) continue;
+                    const int c = walk_letter(w, k, (uint32_t)(r[i >> 1] >> (32 * (i & 1))));
+                    if (MODE == kWalkLetters) {
+                        w.prev = c;
+                        j.letters[tid * n_total + k0 + i] = (uint8_t)c;
+                        continue;
+                    }
+                    walk_step(w, m, k, c);
+                    if (!inner.value && k <= j.burn_in) continue;
+                    T px, py;
+                    walk_pixel(w, f, px, py);
+                    if (MODE == kWalkEval) {
+                        j.z_out[tid * j.n_steps + (k0 + i - j.burn_in - 1)] = {(double)px, (double)py};
+                    } else {
+                        const uint32_t b = walk_bin(px, py, j.W, j.H);
+                        if (b != kWalkOutside) atomicAdd(j.image + b, 1u);
+                        else ++drop;
+                    }
+                }
+            };
+            if (k0 > j.burn_in && n_total - k0 >= 8) steps(std::true_type{});
+            else steps(std::false_type{});
+            if (MODE != kWalkLetters) walk_rescale(w.u, w.v);
+        }
     }
-    if (j.mode == kWalkRender && j.dropped) {
-        for (int off = 32; off > 0; off >>= 1) drop += __shfl_down(drop, off, 64);
-        if ((threadIdx.x & 63) == 0 && drop) atomicAdd((unsigned long long*)j.dropped, (unsigned long long)drop);
+    if (MODE == kWalkRender && j.dropped) {
+        uint64_t sum = drop;
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+        if ((threadIdx.x & 63) == 0 && sum) atomicAdd((unsigned long long*)j.dropped, (unsigned long long)sum);
     }
 }
 
 // ---- binned render
 constexpr uint32_t kWalkTileBits = 15;                    // a tile: 2^15 bins
 constexpr uint32_t kWalkTileBins = 1u << kWalkTileBits;
-// Drawn steps per region.  Eight keep a workgroup's LDS near 14 KB, so that
-// eight workgroups (32 waves) fit a CU and hide the sort's barriers and
-// LDS atomics behind each other's arithmetic; sixteen steps (26 KB, six
-// workgroups) took 15% longer on 2^30 points, thirty-two 72% longer, and
-// four no shorter.
+// A region holds a workgroup's drawn points of one Philox block, eight steps
+// at most, so that a step's place in its region is known at compile time and
+// its bin and rank stay in registers.  (Sixteen steps a region took 15%
+// longer on 2^30 points, thirty-two 72% longer, and four no shorter.)
 constexpr uint32_t kWalkChunk = 8;
-constexpr uint32_t kWalkRegion = 256 * kWalkChunk;        // points of a region at most
-constexpr uint32_t kNoKey = 0xFFFFFFFFu;
+constexpr uint32_t kWalkBlock = 512;                      // walkers of a workgroup
+constexpr uint32_t kWalkRegion = kWalkBlock * kWalkChunk; // points of a region at most
 
-// One region per (workgroup, chunk of kWalkChunk drawn steps): its points
-// in the window as offsets within their tiles, tile by tile (ids, kWalkRegion
-// slots a region), and where each tile's offsets start (starts, T + 1
-// entries a region: starts[T] is the region's count).
+// regions of a workgroup: the Philox blocks with a drawn step burn_in + 1 .. burn_in + n_steps
+__host__ __device__ inline uint32_t walk_chunks(uint32_t burn_in, uint32_t n_steps) {
+    return (burn_in + n_steps) / kWalkChunk - (burn_in + 1) / kWalkChunk + 1;
+}
+
+// One region per (workgroup, Philox block): its points in the window as
+// offsets within their tiles, tile by tile (ids, kWalkRegion slots a region),
+// and where each tile's offsets start (starts, T + 1 entries a region:
+// starts[T] is the region's count).
+//
+// A point takes one LDS atomic, whose old value is its rank among its tile's
+// points; after a scan of the tiles' counts, first point plus rank is its
+// place.  Three barriers a region: the counters alternate, so one set is
+// cleared while the other is read.  What bounds it: VALU issue (some 90
+// instructions a point, 28 of them the Philox rounds, whose 64-bit products
+// issue at a quarter of the rate; sums with carries in place of their chained
+// addends took 7% longer).  2^26 points in FP32: 153 us; with the bins
+// staged in LDS eight words apart (8-way bank conflicts), a second atomic and
+// five barriers 189.  Workgroups of 256 walkers take 7% less, but their regions
+// are half as long and the histogram kernel pays for it (64 us against 51).
 template <typename T>
-__global__ __launch_bounds__(256) void walk_bin_kernel(const WalkJob j, uint16_t* __restrict__ ids,
+constexpr int kWalkWaves = std::is_same<T, float>::value ? 6 : 5;   // per SIMD, without spills
+
+template <typename T>
+__global__ __launch_bounds__(kWalkBlock) __attribute__((amdgpu_waves_per_eu(kWalkWaves<T>))) void walk_bin_kernel(const WalkJob j, uint16_t* __restrict__ ids,
                                                        uint32_t* __restrict__ starts, uint32_t T_tiles,
                                                        uint32_t n_chunks) {
     __shared__ WalkMaps<T> m;
-    __shared__ uint32_t keys[kWalkRegion];
-    __shared__ uint16_t sorted[kWalkRegion];
-    __shared__ uint32_t cnt[kMaxWalkTiles + 1], cur[kMaxWalkTiles];
+    __shared__ __align__(4) uint16_t sorted[kWalkRegion];
+    __shared__ uint32_t cnt[2][kMaxWalkTiles], base[kMaxWalkTiles + 1];
     load_walk_maps(j, m);
-    for (uint32_t t = threadIdx.x; t <= kMaxWalkTiles; t += blockDim.x) cnt[t] = 0;
+    for (uint32_t t = threadIdx.x; t < kMaxWalkTiles; t += blockDim.x) cnt[0][t] = 0;
     __syncthreads();
     const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool active = tid < j.n_walkers;
-    const uint32_t lane_slot = threadIdx.x * kWalkChunk;
-    uint64_t drop = 0;
-    walk_walker<T>(j, m, j.first_walker + (active ? tid : 0), active, [](uint32_t, int) {},
-                   [&](uint32_t d, T px, T py, bool act) {
-                       const uint32_t slot = d % kWalkChunk;
-                       const uint32_t b = walk_bin(px, py, j.W, j.H);
-                       uint32_t key = kNoKey;
-                       if (act) {
-                           if (b != kWalkOutside) key = b;
-                           else ++drop;
-                       }
-                       keys[lane_slot + slot] = key;
-                       if (key != kNoKey) atomicAdd(&cnt[key >> kWalkTileBits], 1u);
-                       // the chunk is full, or the walk ends: sort it into its region
-                       if (slot == kWalkChunk - 1 || d == j.n_steps - 1) {
-                           const uint32_t nk = slot + 1;
-                           __syncthreads();
-                           if (threadIdx.x < 64) {
-                               // exclusive scan of cnt[0 .. T) by one wave, into cnt, with cnt[T] the total
-                               uint32_t carry = 0;
-                               for (uint32_t base = 0; base < T_tiles; base += 64) {
-                                   const uint32_t t = base + threadIdx.x;
-                                   const uint32_t c = t < T_tiles ? cnt[t] : 0u;
-                                   uint32_t x = c;
-                                   for (int off = 1; off < 64; off <<= 1) {
-                                       const uint32_t y = __shfl_up(x, off, 64);
-                                       if ((int)threadIdx.x >= off) x += y;
-                                   }
-                                   if (t < T_tiles) {
-                                       cnt[t] = carry + x - c;
-                                       cur[t] = carry + x - c;
-                                   }
-                                   carry += __shfl(x, 63, 64);
-                               }
-                               if (threadIdx.x == 0) cnt[T_tiles] = carry;
-                           }
-                           __syncthreads();
-                           for (uint32_t q = 0; q < nk; ++q) {
-                               const uint32_t kq = keys[lane_slot + q];
-                               if (kq != kNoKey)
-                                   sorted[atomicAdd(&cur[kq >> kWalkTileBits], 1u)] = (uint16_t)(kq & (kWalkTileBins - 1));
-                           }
-                           __syncthreads();
-                           const uint64_t region = (uint64_t)blockIdx.x * n_chunks + d / kWalkChunk;
-                           const uint32_t n_in = cnt[T_tiles];
-                           uint16_t* out = ids + region * kWalkRegion;
-                           for (uint32_t i = threadIdx.x; i < n_in; i += blockDim.x) out[i] = sorted[i];
-                           uint32_t* st = starts + region * (T_tiles + 1);
-                           for (uint32_t t = threadIdx.x; t <= T_tiles; t += blockDim.x) st[t] = cnt[t];
-                           __syncthreads();
-                           for (uint32_t t = threadIdx.x; t <= T_tiles; t += blockDim.x) cnt[t] = 0;
-                           __syncthreads();
-                       }
-                   });
+    const bool active = tid < j.n_walkers;   // the others step along on the first walker's stream
+    const uint64_t walker = j.first_walker + (active ? tid : 0);
+    const uint32_t n_total = 1 + j.burn_in + j.n_steps;
+    const WalkFold<T> f = walk_fold<T>(j);
+    Walker<T> w = {{T(0), T(0)}, {T(1), T(0)}, 0};
+    const uint32_t W = active ? j.W : 0u;    // ... and every point of theirs is outside
+    uint32_t drop = 0;   // at most n_steps
+    uint64_t region = (uint64_t)blockIdx.x * n_chunks;
+    uint32_t par = 0;
+    for (uint64_t blk = 0; blk * kWalkChunk < n_total; ++blk) {   // 64 bits: n_total may be 2^32 - 1
+        const uint32_t k0 = (uint32_t)(blk * kWalkChunk);
+        uint64_t r[4];
+        philox4x64_10(blk, walker, 0, 0, j.seed, 0, r);
+        uint32_t bin[kWalkChunk], rank[kWalkChunk];
+        // inner: every step of the block is drawn (and none is the first)
+        auto steps = [&](auto inner) {
+#pragma unroll
+            for (uint32_t i = 0; i < kWalkChunk; ++i) {
+                const uint32_t k = inner.value ? 1u : k0 + i;   // uniform: every walker takes the same steps
+                bin[i] = kWalkOutside;
+                rank[i] = 0;
+                if (!inner.value && i >= n_total - k0) continue;
+                walk_step(w, m, k, walk_letter(w, k, (uint32_t)(r[i >> 1] >> (32 * (i & 1)))));
+                if (!inner.value && k <= j.burn_in) continue;
+                T px, py;
+                walk_pixel(w, f, px, py);
+                bin[i] = walk_bin(px, py, W, j.H);
+                if (bin[i] != kWalkOutside) rank[i] = atomicAdd(&cnt[par][bin[i] >> kWalkTileBits], 1u);
+                else ++drop;
+            }
+        };
+        if (k0 > j.burn_in && n_total - k0 >= kWalkChunk) steps(std::true_type{});
+        else steps(std::false_type{});
+        walk_rescale(w.u, w.v);
+        if ((blk + 1) * kWalkChunk <= (uint64_t)j.burn_in + 1) continue;   // no drawn step yet
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            // exclusive scan of the counts by one wave, base[T] the total
+            uint32_t carry = 0;
+            for (uint32_t t0 = 0; t0 < T_tiles; t0 += 64) {
+                const uint32_t t = t0 + threadIdx.x;
+                const uint32_t c = t < T_tiles ? cnt[par][t] : 0u;
+                uint32_t x = c;
+                for (int off = 1; off < 64; off <<= 1) {
+                    const uint32_t y = __shfl_up(x, off, 64);
+                    if ((int)threadIdx.x >= off) x += y;
+                }
+                if (t < T_tiles) base[t] = carry + x - c;
+                carry += __shfl(x, 63, 64);
+            }
+            if (threadIdx.x == 0) base[T_tiles] = carry;
+        } else {
+            for (uint32_t t = threadIdx.x - 64; t < T_tiles; t += blockDim.x - 64) cnt[par ^ 1][t] = 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t i = 0; i < kWalkChunk; ++i)
+            if (bin[i] != kWalkOutside)
+                sorted[base[bin[i] >> kWalkTileBits] + rank[i]] = (uint16_t)(bin[i] & (kWalkTileBins - 1));
+        __syncthreads();
+        const uint32_t n2 = (base[T_tiles] + 1) / 2;   // whole dwords: a region's slots are its own
+        uint32_t* out = (uint32_t*)(ids + region * kWalkRegion);
+        for (uint32_t i = threadIdx.x; i < n2; i += blockDim.x) out[i] = ((const uint32_t*)sorted)[i];
+        uint32_t* st = starts + region * (T_tiles + 1);
+        for (uint32_t t = threadIdx.x; t <= T_tiles; t += blockDim.x) st[t] = base[t];
+        ++region;
+        par ^= 1;
+    }
     if (j.dropped) {
-        for (int off = 32; off > 0; off >>= 1) drop += __shfl_down(drop, off, 64);
-        if ((threadIdx.x & 63) == 0 && drop) atomicAdd((unsigned long long*)j.dropped, (unsigned long long)drop);
+        uint64_t sum = active ? drop : 0u;
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+        if ((threadIdx.x & 63) == 0 && sum) atomicAdd((unsigned long long*)j.dropped, (unsigned long long)sum);
     }
 }
 
@@ -342,17 +409,71 @@ __device__ __forceinline__ void hist_chunk(uint32_t* hist, uint4 v, uint32_t c, 
     }
 }
 
-// Tile blockIdx.x / split over its share of the regions: every offset
-// counted in an LDS histogram, then each non-zero bin added to the image.
+// Which tile a workgroup counts, and which of the tile's `of` equal shares of
+// the regions.  Walks crowd into some tiles (the fullest of Fig. 3's window
+// holds 3.4 times the mean, four of 32 are empty), so the workgroups are dealt
+// to the tiles by the rounds that up to kHistSamples regions, spread over all,
+// take: every tile gets one workgroup, the other gridDim.x - T in proportion
+// (rounded down; workgroups left over return at once).
+constexpr uint32_t kHistSamples = 64;
+struct HistShare {
+    uint32_t tile, part, of;   // of = 0: no share
+};
+
+__device__ __forceinline__ HistShare hist_share(const uint32_t* __restrict__ starts, uint64_t n_regions, uint32_t T) {
+    __shared__ uint32_t weight[kMaxWalkTiles];
+    __shared__ HistShare share;
+    for (uint32_t t = threadIdx.x; t < T; t += blockDim.x) weight[t] = 0;
+    __syncthreads();
+    const uint32_t samples = n_regions < kHistSamples ? (uint32_t)n_regions : kHistSamples;
+    for (uint32_t i = threadIdx.x; i < samples * T; i += blockDim.x) {
+        const uint32_t q = i / T, t = i - q * T;
+        const uint32_t* st = starts + (n_regions * q / samples) * (T + 1) + t;
+        // a region costs one round of its lanes' chunks (64 offsets) at least
+        const uint32_t c = st[1] - st[0], rounds = (c + 63) / 64;
+        atomicAdd(&weight[t], rounds ? rounds : 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const uint32_t lane = threadIdx.x;
+        uint32_t sum = 0;
+        for (uint32_t t = lane; t < T; t += 64) sum += weight[t];
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        if (lane == 0) share = {0, 0, 0};
+        uint32_t carry = 0;
+        for (uint32_t t0 = 0; t0 < T; t0 += 64) {
+            const uint32_t t = t0 + lane;
+            const uint32_t n = t < T ? 1u + (uint32_t)((uint64_t)weight[t] * (gridDim.x - T) / (sum ? sum : 1u)) : 0u;
+            uint32_t x = n;
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t y = __shfl_up(x, off, 64);
+                if ((int)lane >= off) x += y;
+            }
+            const uint32_t lo = carry + x - n;
+            if (blockIdx.x >= lo && blockIdx.x - lo < n) share = {t, blockIdx.x - lo, n};
+            carry += __shfl(x, 63, 64);
+        }
+    }
+    __syncthreads();
+    return share;
+}
+
+// One tile over a share of the regions: every offset counted in an LDS
+// histogram, then each non-zero bin added to the image.  What bounds it: the
+// latency of the offsets' loads and the LDS atomics, sixteen waves a CU (the
+// histogram takes 128 KB).  2^26 points: 51 us; with an equal number of
+// workgroups for every tile, and regions of 256 walkers, 63.
 __global__ __launch_bounds__(1024) void walk_tile_hist_kernel(const uint16_t* __restrict__ ids,
                                                               const uint32_t* __restrict__ starts,
-                                                              uint64_t n_regions, uint32_t T_tiles, uint32_t split,
+                                                              uint64_t n_regions, uint32_t T_tiles,
                                                               uint32_t* __restrict__ image) {
-    __shared__ uint32_t hist[kWalkTileBins];
-    const uint32_t tile = blockIdx.x / split, part = blockIdx.x % split;
-    for (uint32_t i = threadIdx.x; i < kWalkTileBins; i += blockDim.x) hist[i] = 0;
+    __shared__ __align__(16) uint32_t hist[kWalkTileBins];
+    const HistShare share = hist_share(starts, n_regions, T_tiles);
+    if (share.of == 0) return;
+    const uint32_t tile = share.tile;
+    for (uint32_t i = threadIdx.x; i < kWalkTileBins / 4; i += blockDim.x) ((uint4*)hist)[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    const uint64_t r0 = n_regions * part / split, r1 = n_regions * (part + 1) / split;
+    const uint64_t r0 = n_regions * share.part / share.of, r1 = n_regions * (share.part + 1) / share.of;
     const uint32_t wave = threadIdx.x / 64, lane = threadIdx.x % 64, waves = blockDim.x / 64;
     const uint32_t grp = lane / kHistLanes, sub = lane % kHistLanes;
     // a wave takes a contiguous slice of the regions, 64 at a time; lane l
@@ -420,10 +541,11 @@ hipError_t launch_walk(const WalkJob& j, hipStream_t s) {
         if (c.letters) c.letters += off * n_total;
         if (c.z_out) c.z_out += off * j.n_steps;
         const unsigned blocks = (unsigned)((c.n_walkers + 255) / 256);
-        if (j.precision == KL_PREC_FP64)
-            hipLaunchKernelGGL(walk_kernel<double>, dim3(blocks), dim3(256), 0, s, c);
-        else
-            hipLaunchKernelGGL(walk_kernel<float>, dim3(blocks), dim3(256), 0, s, c);
+        const bool fp64 = j.precision == KL_PREC_FP64;
+        void (*kern)(WalkJob) = j.mode == kWalkLetters ? walk_kernel<float, kWalkLetters>
+                                : j.mode == kWalkEval  ? (fp64 ? walk_kernel<double, kWalkEval> : walk_kernel<float, kWalkEval>)
+                                                       : (fp64 ? walk_kernel<double, kWalkRender> : walk_kernel<float, kWalkRender>);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, c);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -439,53 +561,48 @@ uint64_t walk_region_points(uint32_t n_steps) {
     return 256ull * kWalkChunk * ((n_steps + kWalkChunk - 1) / kWalkChunk);
 }
 
+// The temporaries of a binned render: `blocks` workgroups of walkers a launch,
+// their regions' ids and starts.
+WalkBinned walk_binned_layout(const WalkJob& j) {
+    WalkBinned L{};
+    if (j.n_walkers == 0 || j.n_steps == 0) return L;
+    const uint64_t chunks = walk_chunks(j.burn_in, j.n_steps), total = (j.n_walkers + kWalkBlock - 1) / kWalkBlock;
+    L.blocks = std::min(total, std::max<uint64_t>(1, kWalkBinnedPoints / (kWalkRegion * chunks)));
+    L.off_starts = L.blocks * chunks * kWalkRegion * sizeof(uint16_t);
+    L.bytes = L.off_starts + L.blocks * chunks * (walk_tiles(j.W, j.H) + 1) * sizeof(uint32_t);
+    return L;
+}
+
 // The binned render: walkers in launches whose regions hold at most
 // kWalkBinnedPoints points, each launch binning its walkers' points
 // (walk_bin_kernel) and then counting them tile by tile
-// (walk_tile_hist_kernel), in temporaries allocated on the stream.
-hipError_t launch_walk_binned(const WalkJob& j, hipStream_t s) {
-    if (j.n_walkers == 0 || j.n_steps == 0) return hipSuccess;
-    const uint32_t T_tiles = walk_tiles(j.W, j.H);
-    const uint32_t n_chunks = (j.n_steps + kWalkChunk - 1) / kWalkChunk;
-    const uint64_t block_points = walk_region_points(j.n_steps);   // one block of 256 walkers
-    uint64_t blocks_per = kWalkBinnedPoints / block_points;
-    if (blocks_per == 0) return hipErrorInvalidValue;
-    const uint64_t total_blocks = (j.n_walkers + 255) / 256;
-    if (blocks_per > total_blocks) blocks_per = total_blocks;
-    uint16_t* ids = nullptr;
-    uint32_t* starts = nullptr;
-    const uint64_t regions_per = blocks_per * n_chunks;
-    hipError_t e = hipMallocAsync((void**)&ids, regions_per * kWalkRegion * sizeof(uint16_t), s);
-    if (e != hipSuccess) return e;
-    e = hipMallocAsync((void**)&starts, regions_per * (T_tiles + 1) * sizeof(uint32_t), s);
-    if (e != hipSuccess) {
-        (void)hipFreeAsync(ids, s);
-        return e;
-    }
-    int cus = device_cu_count();
-    for (uint64_t b0 = 0; b0 < total_blocks && e == hipSuccess; b0 += blocks_per) {
-        const uint64_t nb = total_blocks - b0 < blocks_per ? total_blocks - b0 : blocks_per;
+// (walk_tile_hist_kernel), in `buf` (L.bytes bytes).
+hipError_t launch_walk_binned(const WalkJob& j, const WalkBinned& L, void* buf, hipStream_t s) {
+    if (L.blocks == 0) return hipSuccess;
+    const uint32_t T_tiles = walk_tiles(j.W, j.H), n_chunks = walk_chunks(j.burn_in, j.n_steps);
+    const uint64_t total_blocks = (j.n_walkers + kWalkBlock - 1) / kWalkBlock;
+    uint16_t* ids = (uint16_t*)buf;
+    uint32_t* starts = (uint32_t*)((unsigned char*)buf + L.off_starts);
+    // two workgroups for each CU, or for each tile if that is more
+    const unsigned hist_blocks = std::max(2u * (unsigned)device_cu_count(), 2u * T_tiles);
+    for (uint64_t b0 = 0; b0 < total_blocks; b0 += L.blocks) {
+        const uint64_t nb = std::min(total_blocks - b0, L.blocks);
         WalkJob c = j;
-        c.first_walker = j.first_walker + b0 * 256;
-        c.n_walkers = j.n_walkers - b0 * 256 < nb * 256 ? j.n_walkers - b0 * 256 : nb * 256;
+        c.first_walker = j.first_walker + b0 * kWalkBlock;
+        c.n_walkers = std::min(j.n_walkers - b0 * kWalkBlock, nb * kWalkBlock);
         if (j.precision == KL_PREC_FP64)
-            hipLaunchKernelGGL(walk_bin_kernel<double>, dim3((unsigned)nb), dim3(256), 0, s, c, ids, starts, T_tiles,
-                               n_chunks);
+            hipLaunchKernelGGL(walk_bin_kernel<double>, dim3((unsigned)nb), dim3(kWalkBlock), 0, s, c, ids, starts,
+                               T_tiles, n_chunks);
         else
-            hipLaunchKernelGGL(walk_bin_kernel<float>, dim3((unsigned)nb), dim3(256), 0, s, c, ids, starts, T_tiles,
-                               n_chunks);
-        if ((e = hipGetLastError()) != hipSuccess) break;
-        const uint64_t n_regions = nb * n_chunks;
-        // enough workgroups to fill the GPU twice over, each tile split evenly
-        uint64_t split = (2ull * (uint64_t)cus + T_tiles - 1) / T_tiles;
-        if (split > n_regions) split = n_regions;
-        if (split < 1) split = 1;
-        hipLaunchKernelGGL(walk_tile_hist_kernel, dim3((unsigned)(T_tiles * split)), dim3(1024), 0, s, ids, starts,
-                           n_regions, T_tiles, (uint32_t)split, j.image);
-        e = hipGetLastError();
+            hipLaunchKernelGGL(walk_bin_kernel<float>, dim3((unsigned)nb), dim3(kWalkBlock), 0, s, c, ids, starts,
+                               T_tiles, n_chunks);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(walk_tile_hist_kernel, dim3(hist_blocks), dim3(1024), 0, s, ids, starts, nb * n_chunks, T_tiles,
+                           j.image);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const hipError_t f1 = hipFreeAsync(ids, s), f2 = hipFreeAsync(starts, s);
-    return e != hipSuccess ? e : f1 != hipSuccess ? f1 : f2;
+    return hipSuccess;
 }
 
 }  // namespace kl

@@ -247,3 +247,38 @@ def test_binned_render_limits():
     # no points: an empty image either way
     assert int(kl.walk_render(ab, 1, 0, 0, 0, 4, WIN_M, hist_mode="lds").abs().sum()) == 0
     assert int(kl.walk_render(ab, 1, 0, 10, 3, 0, WIN_M, hist_mode="lds").abs().sum()) == 0
+
+
+@pytest.mark.parametrize("n,burn,steps,win", [
+    (511, 6, 1, WIN_M), (512, 7, 1, WIN_M), (513, 7, 8, WIN_M), (1025, 8, 7, WIN_M), (3000, 0, 7, WIN_M),
+    (3000, 6, 9, WIN_M), (700, 15, 24, WIN_M), (40000, 1, 31, (-1.05, 1.05, -0.1, 2.0, 2896, 2896)),
+    (70000, 3, 20, (-1.05, 1.05, -0.1, 2.0, 1500, 1500)), (30000, 0, 64, (50.0, 51.0, 50.0, 51.0, 400, 400)),
+])
+def test_binned_regions_follow_the_random_blocks(n, burn, steps, win):
+    """A region holds the drawn steps of one block of eight random values:
+    walks that start or end anywhere in a block, workgroups of 512 walkers
+    with a remainder, 1 to 256 tiles (the shares of the counting kernel are
+    dealt by sampled regions), and no point in the window at all.  The same
+    image and dropped count as one atomic per point."""
+    ab = kl.maskit_generators(wl.MASKIT_MU)
+    out = []
+    for mode in ("lds", "runs"):
+        dropped = torch.zeros(1, dtype=torch.int64, device="cuda")
+        img = kl.walk_render(ab, 11, 3, n, burn, steps, win, hist_mode=mode, dropped=dropped)
+        assert int(kl.as_u32(img).astype(np.int64).sum()) + int(dropped.item()) == n * steps
+        out.append((img, int(dropped.item())))
+    assert torch.equal(out[0][0], out[1][0]) and out[0][1] == out[1][1]
+
+
+def test_large_walk_then_small_renders_share_the_buffer():
+    """On the null stream a large walk render grows the device's buffer, and
+    small renders after it give that back (after 32 of them) and go on in a
+    small one: every image equals its first."""
+    ab = kl.maskit_generators(wl.MASKIT_MU)
+    win = (-1.5, 1.5, -1.5, 1.5, 300, 200)
+    ref_small = kl.render(wl.C2_TA, wl.C2_TB, 10, win).clone()
+    ref_walk = kl.walk_render(ab, 4, 0, 1 << 20, 0, 40, WIN_M).clone()
+    for _ in range(2):
+        for _ in range(40):
+            assert torch.equal(kl.render(wl.C2_TA, wl.C2_TB, 10, win), ref_small)
+        assert torch.equal(kl.walk_render(ab, 4, 0, 1 << 20, 0, 40, WIN_M), ref_walk)
