@@ -136,16 +136,9 @@ static hipError_t gemm(int M, int N, int K, const float* A, int64_t lam, int64_t
     return hipGetLastError();
 }
 
-__global__ void adam_kernel(float* p, const float* g, float* m, float* v, int64_t n, float lr, float bc1, float bc2) {
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const float ge = g[e];
-        const float me = b1 * m[e] + (1.f - b1) * ge;
-        const float ve = b2 * v[e] + (1.f - b2) * ge * ge;
-        m[e] = me;
-        v[e] = ve;
-        p[e] -= lr * (me / bc1) / (sqrtf(ve / bc2) + eps);
-    }
+__global__ void adam_kernel(const Adam a, const float* g, int64_t n) {
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
+        a.update(e, g[e]);
 }
 
 __global__ void occupancy_kernel(const uint32_t* c, uint64_t n, uint8_t* o) {
@@ -353,18 +346,18 @@ __global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
     for (int kx = 0; kx < 4; ++kx)
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) w1[kx][ct] = loadw(a.packed + kT1f + ((4 * wave + kx) * 64 + 16 * ct + lr) * 16 + 4 * lq);
+        for (int ct = 0; ct < 4; ++ct) w1[kx][ct] = frag4(a.packed + kT1f, (4 * wave + kx) * 4 + ct, lane);
     bf16x8 w2[2][8];    // convT 2: both column phases, (tap, channel half); output channels 16 half ..
     bf16x8 w3[2][4];    // convT 3: both column phases, tap; columns 2 (16 half + lr) + px
 #pragma unroll
     for (int px = 0; px < 2; ++px) {
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks)
-            w2[px][ks] = loadw8(a.packed + kT2f + (((2 * py + px) * 4 + (ks >> 1)) * 32 + 16 * half + lr) * 64 + (ks & 1) * 32 + 8 * lq);
+            w2[px][ks] = frag8(a.packed + kI2, ((2 * py + px) * 8 + ks) * 2 + half, lane);
 #pragma unroll
-        for (int tap = 0; tap < 4; ++tap) w3[px][tap] = loadw8(a.packed + kT3f + (((2 * py + px) * 4 + tap) * 16 + lr) * 32 + 8 * lq);
+        for (int tap = 0; tap < 4; ++tap) w3[px][tap] = frag8(a.packed + kI3, (2 * py + px) * 4 + tap, lane);
     }
-    const bf16x4 w4 = loadw(a.packed + kT4f + lr * 16 + 4 * lq);
+    const bf16x4 w4 = frag4(a.packed + kT4f, 0, lane);
     f32x4 bias1[4];
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) bias1[ct] = load4(a.P + a.L.c1 + 16 * ct + 4 * lq);
@@ -555,23 +548,32 @@ int kl_sur_forward(const float* params, const kl_c64* ta, const kl_c64* tb, int 
     return e == hipSuccess ? KL_OK : sur_fail(KL_EDEVICE, hipGetErrorString(e));
 }
 
-int kl_sur_loss_grad(const float* params, const kl_c64* ta, const kl_c64* tb, const uint8_t* targets, int batch,
-                     float* grad_out, float* loss_out, void* workspace, size_t workspace_bytes, void* stream) {
+static Adam adam_args(float* params, float* m, float* v, int step, float lr) {
+    return {params, m, v, lr, 1.f - powf(0.9f, (float)step), 1.f - powf(0.999f, (float)step)};
+}
+
+static int sur_loss_grad(const float* params, const kl_c64* ta, const kl_c64* tb, const uint8_t* targets, int batch,
+                         float* grad_out, float* loss_out, const Adam& adam, void* workspace, size_t workspace_bytes,
+                         void* stream) {
     if (batch > 512) return sur_fail(KL_EINVAL, "batch above 512");
     if (batch <= 0 || !params || !ta || !tb || !targets || !grad_out || !loss_out || !workspace)
         return sur_fail(KL_EINVAL, "bad surrogate gradient arguments");
     if (workspace_bytes < kl_sur_workspace_bytes(batch)) return sur_fail(KL_EINVAL, "workspace too small");
     const WS w = carve(workspace, batch);
-    hipError_t e = loss_grad(params, ta, tb, targets, batch, grad_out, loss_out, w, (hipStream_t)stream);
+    hipError_t e = loss_grad(params, ta, tb, targets, batch, grad_out, loss_out, adam, w, (hipStream_t)stream);
     return e == hipSuccess ? KL_OK : sur_fail(KL_EDEVICE, hipGetErrorString(e));
+}
+
+int kl_sur_loss_grad(const float* params, const kl_c64* ta, const kl_c64* tb, const uint8_t* targets, int batch,
+                     float* grad_out, float* loss_out, void* workspace, size_t workspace_bytes, void* stream) {
+    return sur_loss_grad(params, ta, tb, targets, batch, grad_out, loss_out, Adam{}, workspace, workspace_bytes, stream);
 }
 
 int kl_sur_adam(float* params, const float* grad, float* m, float* v, int step, float lr, void* stream) {
     if (!params || !grad || !m || !v || step < 1) return sur_fail(KL_EINVAL, "bad Adam arguments");
     const int64_t n = (int64_t)layout().total;
-    const float bc1 = 1.f - powf(0.9f, (float)step), bc2 = 1.f - powf(0.999f, (float)step);
-    hipLaunchKernelGGL(adam_kernel, dim3(grid_for(n)), dim3(256), 0, (hipStream_t)stream, params, grad, m, v, n, lr,
-                       bc1, bc2);
+    hipLaunchKernelGGL(adam_kernel, dim3(grid_for(n)), dim3(256), 0, (hipStream_t)stream,
+                       adam_args(params, m, v, step, lr), grad, n);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? KL_OK : sur_fail(KL_EDEVICE, hipGetErrorString(e));
 }
@@ -580,9 +582,10 @@ int kl_sur_train_step(float* params, float* m, float* v, float* grad_scratch, in
                       const kl_c64* tb, const uint8_t* targets, int batch, float* loss_out, void* workspace,
                       size_t workspace_bytes, void* stream) {
     if (!grad_scratch) return sur_fail(KL_EINVAL, "grad_scratch is NULL");
-    int rc = kl_sur_loss_grad(params, ta, tb, targets, batch, grad_scratch, loss_out, workspace, workspace_bytes, stream);
-    if (rc) return rc;
-    return kl_sur_adam(params, grad_scratch, m, v, step, lr, stream);
+    const bool ok = m && v && step >= 1;   // otherwise the gradient is still formed, then the update refused
+    int rc = sur_loss_grad(params, ta, tb, targets, batch, grad_scratch, loss_out,
+                           ok ? adam_args(params, m, v, step, lr) : Adam{}, workspace, workspace_bytes, stream);
+    return rc || ok ? rc : kl_sur_adam(params, grad_scratch, m, v, step, lr, stream);
 }
 
 int kl_occupancy(const uint32_t* counts, uint64_t n, uint8_t* occ_out, void* stream) {

@@ -68,45 +68,64 @@ __device__ __forceinline__ f32x4 mma32(bf16x8 a, bf16x8 b, f32x4 c) {
 __device__ __forceinline__ int tap_dy(int p, int a) { return p ? (a ? 0 : 1) : (a ? -1 : 0); }
 __device__ __forceinline__ int tap_k(int p, int a) { return p ? (a ? 2 : 0) : (a ? 3 : 1); }
 
-// Packed bfloat16 weights (offsets in elements), rounded once a pass in the
-// order the products read them: the forward products' left operands, then,
-// for a training step, the backward ones', which are the parameters' own
-// order.
-constexpr int kT1f = 0;                       // [tap][o 64][c 16]
-constexpr int kT2f = kT1f + 16 * 64 * 16;     // [phase][tap][o 32][c 64]
-constexpr int kT3f = kT2f + 16 * 32 * 64;     // [phase][tap][o 16][c 32]
-constexpr int kT4f = kT3f + 16 * 16 * 32;     // [tap][c 16]
-constexpr int kForwardPacked = kT4f + 16 * 16;
-constexpr int kT1b = kForwardPacked;          // K1 [c 16][o 64][tap]
-constexpr int kT2b = kT1b + 16 * 64 * 16;     // K2 [c 64][o 32][tap]
-constexpr int kT3b = kT2b + 64 * 32 * 16;     // K3 [c 32][o 16][tap]
-constexpr int kT4b = kT3b + 32 * 16 * 16;     // K4 [c 16][tap]
-constexpr int kT2w = kT4b + 16 * 16;          // W2 [i][j], 256 x 256
+// Packed bfloat16 weights (offsets in elements), rounded once a pass into
+// operand order: a fragment is the 64 lanes' values one after another (lane
+// l's row l % 16 and its 4, or for mma32 8, consecutive k from l / 16), so that
+// a wave reads it as one contiguous piece.  Read from the parameters' own
+// order a fragment is 64 separate requests, some 60 cycles of a CU's address
+// unit each: the weights of the second layer's backward alone took 7 us.
+constexpr int kT1f = 0;                       // K1 forward: [tap][o / 16], k = c
+constexpr int kT4f = kT1f + 16 * 64 * 16;     // K4 forward: rows taps, k = c
+constexpr int kI2 = kT4f + 16 * 16;           // K2 forward, mma32: [phase][tap][c / 32][o / 16], k = c % 32
+constexpr int kI3 = kI2 + 16 * 32 * 64;       // K3 forward, mma32: [phase][tap], k = c
+constexpr int kForwardPacked = kI3 + 16 * 16 * 32;
+constexpr int kT2f = kForwardPacked;          // K2 forward: [phase][tap][o / 16][c / 16]
+constexpr int kT3f = kT2f + 16 * 32 * 64;     // K3 forward: [phase][tap][c / 16]
+constexpr int kT1b = kT3f + 16 * 16 * 32;     // K1 backward: [o], rows c, k = taps
+constexpr int kT2b = kT1b + 16 * 64 * 16;     // K2 backward: [c / 16][o], k = taps
+constexpr int kT3b = kT2b + 64 * 32 * 16;     // K3 backward: [c / 16][o]
+constexpr int kT4b = kT3b + 32 * 16 * 16;     // K4 backward: rows c, k = taps
+constexpr int kT2w = kT4b + 16 * 16;          // W2 backward: [i / 16][j / 16], rows i, k = j
 constexpr int kTrainPacked = kT2w + 256 * 256;
 
 // Packed element e of the parameters P.
 __device__ __forceinline__ float packed_weight(const float* P, const Layout& L, int e) {
-    if (e < kT2f) {
-        const int c = e % 16, o = (e / 16) % 64, tap = e / 1024;
-        return P[L.K1 + (c * 64 + o) * 16 + tap];
+    auto taps = [](int ph, int tap) { return tap_k(ph >> 1, tap >> 1) * 4 + tap_k(ph & 1, tap & 1); };
+    if (e >= kI2 && e < kForwardPacked) {   // mma32 fragments
+        const int i = (e - kI2) % 512, f = (e - kI2) / 512, row = i / 8 % 16, k = 8 * (i / 128) + i % 8;
+        if (e < kI3) {
+            const int o = 16 * (f % 2) + row, c = 32 * (f / 2 % 2) + k, tap = f / 4 % 4, ph = f / 16;
+            return P[L.K2 + (c * 32 + o) * 16 + taps(ph, tap)];
+        }
+        const int g = (e - kI3) / 512;
+        return P[L.K3 + (k * 16 + row) * 16 + taps(g / 4, g % 4)];
     }
-    if (e < kT3f) {
-        const int i = e - kT2f, c = i % 64, o = (i / 64) % 32, tap = (i / 2048) % 4, ph = i / 8192;
-        return P[L.K2 + ((c * 32 + o) * 4 + tap_k(ph >> 1, tap >> 1)) * 4 + tap_k(ph & 1, tap & 1)];
-    }
+    const int row = e / 4 % 16, k = 4 * (e / 64 % 4) + e % 4;   // every offset is a multiple of a fragment's 256
     if (e < kT4f) {
-        const int i = e - kT3f, c = i % 32, o = (i / 32) % 16, tap = (i / 512) % 4, ph = i / 2048;
-        return P[L.K3 + ((c * 16 + o) * 4 + tap_k(ph >> 1, tap >> 1)) * 4 + tap_k(ph & 1, tap & 1)];
+        const int f = e / 256;
+        return P[L.K1 + (k * 64 + 16 * (f % 4) + row) * 16 + f / 4];
+    }
+    if (e < kI2) return P[L.K4 + k * 16 + row];
+    if (e < kT3f) {
+        const int f = (e - kT2f) / 256, c = 16 * (f % 4) + k, o = 16 * (f / 4 % 2) + row;
+        return P[L.K2 + (c * 32 + o) * 16 + taps(f / 32, f / 8 % 4)];
     }
     if (e < kT1b) {
-        const int i = e - kT4f;
-        return P[L.K4 + (i % 16) * 16 + i / 16];
+        const int f = (e - kT3f) / 256, c = 16 * (f % 2) + k;
+        return P[L.K3 + (c * 16 + row) * 16 + taps(f / 8, f / 2 % 4)];
     }
-    if (e < kT2b) return P[L.K1 + (e - kT1b)];
-    if (e < kT3b) return P[L.K2 + (e - kT2b)];
-    if (e < kT4b) return P[L.K3 + (e - kT3b)];
-    if (e < kT2w) return P[L.K4 + (e - kT4b)];
-    return P[L.W2 + (e - kT2w)];
+    if (e < kT2b) return P[L.K1 + (row * 64 + (e - kT1b) / 256) * 16 + k];
+    if (e < kT3b) {
+        const int f = (e - kT2b) / 256;
+        return P[L.K2 + ((16 * (f / 32) + row) * 32 + f % 32) * 16 + k];
+    }
+    if (e < kT4b) {
+        const int f = (e - kT3b) / 256;
+        return P[L.K3 + ((16 * (f / 16) + row) * 16 + f % 16) * 16 + k];
+    }
+    if (e < kT2w) return P[L.K4 + row * 16 + k];
+    const int f = (e - kT2w) / 256;
+    return P[L.W2 + (16 * (f / 16) + row) * 256 + 16 * (f % 16) + k];
 }
 
 // Vectors of global memory, 4-byte aligned: callers may pass any float array
@@ -117,7 +136,9 @@ typedef short bf16x8g __attribute__((ext_vector_type(8), aligned(4)));
 __device__ __forceinline__ f32x4 load4(const float* p) { return *(const f32x4g*)p; }
 __device__ __forceinline__ void store4(float* p, f32x4 v) { *(f32x4g*)p = v; }
 __device__ __forceinline__ bf16x4 loadw(const bf16_t* p) { return *(const bf16x4g*)p; }
-__device__ __forceinline__ bf16x8 loadw8(const bf16_t* p) { return *(const bf16x8g*)p; }
+// fragment f of packed weights, this lane's part
+__device__ __forceinline__ bf16x4 frag4(const bf16_t* w, int f, int lane) { return *(const bf16x4g*)(w + (f * 64 + lane) * 4); }
+__device__ __forceinline__ bf16x8 frag8(const bf16_t* w, int f, int lane) { return *(const bf16x8g*)(w + (f * 64 + lane) * 8); }
 __device__ __forceinline__ bf16x4 lds4(const bf16_t* p) { return *(const bf16x4*)p; }   // 8-byte aligned LDS
 __device__ __forceinline__ bf16x8 lds8(const bf16_t* p) { return *(const bf16x8*)p; }   // 16-byte aligned LDS
 
@@ -140,9 +161,24 @@ __device__ __forceinline__ f32x4 relu4(f32x4 a) {
     return f32x4{fmaxf(a[0], 0.f), fmaxf(a[1], 0.f), fmaxf(a[2], 0.f), fmaxf(a[3], 0.f)};
 }
 
+// One Adam update (bc: the step's bias corrections), by its own kernel or at
+// the end of a training step.  p == nullptr: none.
+struct Adam {
+    float *p, *m, *v;
+    float lr, bc1, bc2;
+    __device__ __forceinline__ void update(int64_t e, float g) const {
+        const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+        const float me = b1 * m[e] + (1.f - b1) * g;
+        const float ve = b2 * v[e] + (1.f - b2) * g * g;
+        m[e] = me;
+        v[e] = ve;
+        p[e] -= lr * (me / bc1) / (sqrtf(ve / bc2) + eps);
+    }
+};
+
 // Workgroups of the training kernels that keep a weight gradient in their
 // registers over several sets, each leaving one partial sum.
-constexpr int kParts3 = 512, kParts2 = 64, kParts1 = 64;
+constexpr int kParts3 = 512, kParts2 = 64, kParts1 = 128;
 // floats of one workgroup's partial sums: the last two layers' (loss, bias 4,
 // bias 3 at 2 .. 17, K4 at 32 .. 287), and K3 with bias 2
 constexpr int kPart34 = 288, kPart3 = 32 * 256 + 32, kPart2 = 64 * 512, kPart1 = 16 * 1024;
@@ -159,7 +195,7 @@ struct WS {
 WS carve(void* base, int B);
 
 hipError_t loss_grad(const float* P, const kl_c64* ta, const kl_c64* tb, const uint8_t* targets, int B, float* G,
-                     float* loss, const WS& w, hipStream_t s);
+                     float* loss, const Adam& adam, const WS& w, hipStream_t s);
 
 }  // namespace sur
 }  // namespace kl

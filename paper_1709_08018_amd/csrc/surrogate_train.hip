@@ -11,9 +11,10 @@
 //
 // What bounds it: the FP32 tensors a step leaves in the workspace (1.1 MB a
 // set, written once and read once or twice, 143 MB written at 128 sets) and
-// the latency of ten dependent launches; the products are 14 GFLOP.  A step
-// of 128 sets takes 159 us; with column matrices in memory (a GEMM into
-// them or out of them per layer, 560 MB of columns) it took 1371 us.
+// the latency of eight dependent launches; the products are 14 GFLOP.  A step
+// of 128 sets takes 113-120 us, of 8 sets 59 us; with column matrices in memory
+// (a GEMM into them or out of them per layer, 560 MB of columns) 128 sets took
+// 1371 us, with weights read in the parameters' own order 159 us.
 //
 // Sums that feed another rounding keep one fixed order (below, per kernel):
 // each tap's product over the input channels on its own, 16 channels a
@@ -28,6 +29,11 @@ namespace kl {
 namespace sur {
 
 namespace {
+
+// Keeps a loaded value in its registers from here on: the compiler would
+// otherwise move the load down to its use, inside the chain of products, where
+// every group of four cost a microsecond of latency.
+__device__ __forceinline__ void hold(bf16x4& v) { asm volatile("" : "+v"(v)); }
 
 // two consecutive LDS dwords as four bfloat16 values
 __device__ __forceinline__ bf16x4 lds_taps(const uint32_t* p) {
@@ -48,11 +54,41 @@ __device__ __forceinline__ f32x4 mask4(f32x4 g, f32x4 y) {
     for (int v = 0; v < 4; ++v) r[v] = y[v] > 0.f ? g[v] : 0.f;
     return r;
 }
+// A product leaves lane l with four channels (4 (l / 16) ..) of pixel l % 16:
+// in memory order, lane l holds the l-th 16 bytes of the sixteen pixels'
+// channels.  A store in the first order is 64 requests, in the second sixteen,
+// for four shuffles.
+__device__ __forceinline__ f32x4 to_memory(f32x4 v, int lane) {
+    const int src = (lane & 3) * 16 + (lane >> 2);
+    return f32x4{__shfl(v[0], src, 64), __shfl(v[1], src, 64), __shfl(v[2], src, 64), __shfl(v[3], src, 64)};
+}
 // sum over the 16 lanes that share lane / 16
 __device__ __forceinline__ float sum16(float x) {
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) x += __shfl_xor(x, o, 64);
     return x;
+}
+
+// sum over the 16 lanes that share lane % 4 (memory order)
+__device__ __forceinline__ float sum_rows(float x) {
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
+
+// log(1 + e^-|z|) from x = e^-z, as 2 atanh(s) with s = e^-|z| / (2 + e^-|z|),
+// the atanh by its power series to s^15 (s <= 1/3: truncated below 2e-9 of
+// its value).  x = infinity, or below FP32's range, gives 0.
+__device__ __forceinline__ float softplus_abs(float z, float x) {
+    const float n = z >= 0.f ? x : 1.f, d = z >= 0.f ? 2.f + x : 1.f + 2.f * x, s = n / d, y = s * s;
+    float c = 1.f / 15.f;
+    c = fmaf(c, y, 1.f / 13.f);
+    c = fmaf(c, y, 1.f / 11.f);
+    c = fmaf(c, y, 1.f / 9.f);
+    c = fmaf(c, y, 1.f / 7.f);
+    c = fmaf(c, y, 1.f / 5.f);
+    c = fmaf(c, y, 1.f / 3.f);
+    return fmaf(2.f * s, c * y, 2.f * s);
 }
 
 struct TrainArgs {
@@ -75,7 +111,68 @@ int sum_chunk(int rows, int Co) {
     const int tiles = (rows + 63) / 64;
     if (tiles >= 512) return Co;
     const int split = std::min(Co / 8, std::max(1, 1024 / tiles));
-    return ((Co + split - 1) / split + 1) / 2 * 2;   // whole steps of 32 terms
+    return ((Co + split - 1) / split + 3) / 4 * 4;
+}
+
+// Planes of one gradient tensor in LDS: `rows` rows from y0 on of the W x W x C
+// tensor d (NHWC), channels c0 .. c0 + 4 CG - 1, one bfloat16 plane a channel
+// (RW dwords a row, RP a plane), entry X + 1 of a row, X = -1 .. W, zero
+// outside.  A task is a pixel pair by four channels; every load is issued
+// before the first is used.
+template <int THREADS, int W, int C, int CG, int ROWS, int RW, int RP>
+__device__ __forceinline__ void load_planes(const float* __restrict__ d, int y0, int c0, uint32_t* pl, int tid) {
+    constexpr int PAIRS = W / 2 + 1, TASKS = ROWS * PAIRS * CG, N = (TASKS + THREADS - 1) / THREADS;
+    constexpr int STEP = THREADS / CG;   // pairs from a thread's task to its next
+    static_assert(THREADS % CG == 0, "a thread keeps its channels");
+    const int cg = tid % CG, j0 = (tid / CG) % PAIRS, r0 = tid / (CG * PAIRS);
+    f32x4 v[N][2];
+    int j = j0, r = r0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const int y = y0 + r;
+        const float* p = d + (y * W + 2 * j) * C + c0 + 4 * cg;
+        const bool in = y >= 0 && y < W && (q < N - 1 || r < ROWS);
+        v[q][0] = in && j > 0 ? load4(p - C) : kZero4;
+        v[q][1] = in && j < W / 2 ? load4(p) : kZero4;
+        j += STEP % PAIRS;
+        r += STEP / PAIRS + (j >= PAIRS ? 1 : 0);
+        j -= j >= PAIRS ? PAIRS : 0;
+    }
+    j = j0;
+    r = r0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        if (q < N - 1 || r < ROWS) {
+            uint32_t* t = pl + 4 * cg * RP + r * RW + j;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[e * RP] = pack2(v[q][0][e], v[q][1][e]);
+        }
+        j += STEP % PAIRS;
+        r += STEP / PAIRS + (j >= PAIRS ? 1 : 0);
+        j -= j >= PAIRS ? PAIRS : 0;
+    }
+}
+
+// N pixels of an activation (C channels, NHWC, from x on) transposed into LDS as
+// bfloat16: channel c's pixels at t[c * (TW dwords)], two a dword.
+template <int THREADS, int N, int C, int TW>
+__device__ __forceinline__ void load_transposed(const float* __restrict__ x, uint32_t* t, int tid) {
+    constexpr int CG = C / 4, TASKS = N / 2 * CG, Q = TASKS / THREADS;
+    static_assert(TASKS % THREADS == 0, "whole rounds");
+    f32x4 v[Q][2];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int i = tid + THREADS * q, cg = i % CG, j = i / CG;
+        const float* p = x + (2 * j) * C + 4 * cg;
+        v[q][0] = load4(p);
+        v[q][1] = load4(p + C);
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int i = tid + THREADS * q, cg = i % CG, j = i / CG;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[(4 * cg + e) * TW + j] = pack2(v[q][0][e], v[q][1][e]);
+    }
 }
 
 // ------------------------------------------------------------------ linear layers and weight packing
@@ -88,8 +185,11 @@ __global__ __launch_bounds__(256) void prologue_kernel(const TrainArgs a, int ml
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if ((int)blockIdx.x >= mlp_blocks) {
         const int stride = (int)(gridDim.x - mlp_blocks) * 256;
-        for (int e = ((int)blockIdx.x - mlp_blocks) * 256 + tid; e < kTrainPacked; e += stride)
+        constexpr int kSkip = kForwardPacked - kI2;   // the inference path's fragments
+        for (int i = ((int)blockIdx.x - mlp_blocks) * 256 + tid; i < kTrainPacked - kSkip; i += stride) {
+            const int e = i < kI2 ? i : i + kSkip;
             a.w.packed[e] = to_bf16(packed_weight(a.P, a.L, e));
+        }
         return;
     }
     const int b0 = ((int)blockIdx.x / 4) * 16, nb = (int)blockIdx.x % 4;
@@ -124,7 +224,7 @@ __global__ __launch_bounds__(256) void prologue_kernel(const TrainArgs a, int ml
     __syncthreads();
     const int n = (4 * nb + wave) * 16 + lr;   // h2 feature c * 16 + q -> x0 pixel q, channel c
     f32x4 d = kZero4;
-#pragma unroll
+#pragma unroll 4
     for (int k0 = 0; k0 < 256; k0 += 16) {
         f32x4 wv;
 #pragma unroll
@@ -156,25 +256,16 @@ __global__ __launch_bounds__(256) void conv12_kernel(const TrainArgs a) {
     const int b = (int)blockIdx.x >> 2, s = (int)blockIdx.x & 3;
     const bf16_t* T = a.w.packed;
     for (int i = tid; i < 6 * 18 * kY1P / 8; i += 256) ((uint4*)y1s)[i] = make_uint4(0, 0, 0, 0);
-    const bf16x4 x = round4(load4(a.w.x0 + ((size_t)b * 16 + lr) * 16 + 4 * lq));
-    __syncthreads();
-    {
-        const int i = lr >> 2, j = lr & 3, ky = wave;   // input pixel (i, j); output row 4 i + ky
-        const int row = 4 * i + ky - (4 * s - 1);
-        const bool in = row >= 0 && row < 6, own = i == s;
+    // every weight and bias is asked for before the first is used
+    bf16x4 w1[4][4];
+    f32x4 bias1[4];
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-            const f32x4 bias = load4(a.P + a.L.c1 + 16 * ct + 4 * lq);
+    for (int ct = 0; ct < 4; ++ct) {
+        bias1[ct] = load4(a.P + a.L.c1 + 16 * ct + 4 * lq);
 #pragma unroll
-            for (int kx = 0; kx < 4; ++kx) {
-                const f32x4 d = mma16(loadw(T + kT1f + ((4 * ky + kx) * 64 + 16 * ct + lr) * 16 + 4 * lq), x, kZero4);
-                const f32x4 y = relu4(add4(d, bias));
-                if (in) *(bf16x4*)(y1s + (row * 18 + 4 * j + kx + 1) * kY1P + 16 * ct + 4 * lq) = round4(y);
-                if (own) store4(a.w.y1 + (((size_t)b * 16 + 4 * i + ky) * 16 + 4 * j + kx) * 64 + 16 * ct + 4 * lq, y);
-            }
-        }
+        for (int kx = 0; kx < 4; ++kx) w1[ct][kx] = frag4(T + kT1f, (4 * wave + kx) * 4 + ct, lane);
     }
-    __syncthreads();
+    const bf16x4 x = round4(load4(a.w.x0 + ((size_t)b * 16 + lr) * 16 + 4 * lq));
     const int py = wave >> 1, px = wave & 1;
     bf16x4 w[2][4][4];
 #pragma unroll
@@ -183,9 +274,33 @@ __global__ __launch_bounds__(256) void conv12_kernel(const TrainArgs a) {
         for (int tap = 0; tap < 4; ++tap)
 #pragma unroll
             for (int kc = 0; kc < 4; ++kc)
-                w[ct][tap][kc] = loadw(T + kT2f + ((wave * 4 + tap) * 32 + 16 * ct + lr) * 64 + 16 * kc + 4 * lq);
-    const f32x4 bias0 = load4(a.P + a.L.c2 + 4 * lq), bias1 = load4(a.P + a.L.c2 + 16 + 4 * lq);
+                w[ct][tap][kc] = frag4(T + kT2f, ((wave * 4 + tap) * 2 + ct) * 4 + kc, lane);
+    const f32x4 bias20 = load4(a.P + a.L.c2 + 4 * lq), bias21 = load4(a.P + a.L.c2 + 16 + 4 * lq);
 #pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        hold(w1[i / 4][i % 4]);
+        hold(w[0][i / 4][i % 4]);
+        hold(w[1][i / 4][i % 4]);
+    }
+    __syncthreads();
+    {
+        const int i = lr >> 2, j = lr & 3, ky = wave;   // input pixel (i, j); output row 4 i + ky
+        const int row = 4 * i + ky - (4 * s - 1);
+        const bool in = row >= 0 && row < 6, own = i == s;
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) {
+            const f32x4 bias = bias1[ct];
+#pragma unroll
+            for (int kx = 0; kx < 4; ++kx) {
+                const f32x4 d = mma16(w1[ct][kx], x, kZero4);
+                const f32x4 y = relu4(add4(d, bias));
+                if (in) *(bf16x4*)(y1s + (row * 18 + 4 * j + kx + 1) * kY1P + 16 * ct + 4 * lq) = round4(y);
+                if (own) store4(a.w.y1 + (((size_t)b * 16 + 4 * i + ky) * 16 + 4 * j + kx) * 64 + 16 * ct + 4 * lq, y);
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll 1
     for (int mi = 0; mi < 4; ++mi) {
         f32x4 s0 = kZero4, s1 = kZero4;
 #pragma unroll
@@ -201,9 +316,9 @@ __global__ __launch_bounds__(256) void conv12_kernel(const TrainArgs a) {
             s0 = add4(s0, d0);
             s1 = add4(s1, d1);
         }
-        float* y = a.w.y2 + (((size_t)b * 32 + 2 * (4 * s + mi) + py) * 32 + 2 * lr + px) * 32 + 4 * lq;
-        store4(y, relu4(add4(s0, bias0)));
-        store4(y + 16, relu4(add4(s1, bias1)));
+        float* y = a.w.y2 + (((size_t)b * 32 + 2 * (4 * s + mi) + py) * 32 + 2 * (lane >> 2) + px) * 32 + 4 * (lane & 3);
+        store4(y, to_memory(relu4(add4(s0, bias20)), lane));
+        store4(y + 16, to_memory(relu4(add4(s1, bias21)), lane));
     }
 }
 
@@ -235,11 +350,12 @@ __global__ __launch_bounds__(512) void conv34_kernel(const TrainArgs a) {
     const bf16_t* T = a.w.packed;
 
     // y2 rows 4 s - 1 .. 4 s + 4, zero outside
-    for (int i = tid; i < 6 * 32 * 8; i += 512) {
-        const int g = i & 7, x = (i >> 3) & 31, r = i >> 8, y = 4 * s - 1 + r;
-        f32x4 v = kZero4;
-        if (y >= 0 && y < 32) v = load4(a.w.y2 + (((size_t)b * 32 + y) * 32 + x) * 32 + 4 * g);
-        *(bf16x4*)(y2s + (r * 34 + x + 1) * kY2P + 4 * g) = round4(v);
+    f32x4 y2v[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int i = tid + 512 * q, g = i & 7, x = (i >> 3) & 31, y = 4 * s - 1 + (i >> 8);
+        y2v[q] = kZero4;
+        if (y >= 0 && y < 32) y2v[q] = load4(a.w.y2 + (((size_t)b * 32 + y) * 32 + x) * 32 + 4 * g);
     }
     if (tid < 6 * 2 * 8) {
         const int g = tid & 7, e = (tid >> 3) & 1, r = tid >> 4;
@@ -247,15 +363,31 @@ __global__ __launch_bounds__(512) void conv34_kernel(const TrainArgs a) {
     }
     if (tid < 320) col[(tid >> 1) * kColW + ((tid & 1) ? kColW - 1 : 0)] = 0.f;
     const int px = wave & 1, h = (wave >> 1) & 1, py = wave >> 2, x = 2 * (16 * h + lr) + px;
+    const int xm = 2 * (16 * h + (lane >> 2)) + px;   // in memory order
     bf16x4 w3[4][2];
 #pragma unroll
     for (int tap = 0; tap < 4; ++tap)
 #pragma unroll
         for (int kc = 0; kc < 2; ++kc)
-            w3[tap][kc] = loadw(T + kT3f + (((py * 2 + px) * 4 + tap) * 16 + lr) * 32 + 16 * kc + 4 * lq);
-    const bf16x4 w4f = loadw(T + kT4f + lr * 16 + 4 * lq), w4b = loadw(T + kT4b + lr * 16 + 4 * lq);
+            w3[tap][kc] = frag4(T + kT3f, ((py * 2 + px) * 4 + tap) * 2 + kc, lane);
+    const bf16x4 w4f = frag4(T + kT4f, 0, lane), w4b = frag4(T + kT4b, 0, lane);
     const f32x4 bias3 = load4(a.P + a.L.c3 + 4 * lq);
     const float bias4 = a.P[a.L.c4];
+    uint8_t tgt[3][2] = {};   // the targets of this thread's pixels (the logits' loop below)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int i = tid + 512 * q, Z = 16 * s - 1 + (i >> 6);
+        if (i < 18 * 64 && Z >= 0 && Z < kImg) {
+            const uint8_t* t = a.targets + ((size_t)b * kImg + Z) * kImg + 2 * (i & 63);
+            tgt[q][0] = t[0];
+            tgt[q][1] = t[1];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int i = tid + 512 * q, g = i & 7, x = (i >> 3) & 31, r = i >> 8;
+        *(bf16x4*)(y2s + (r * 34 + x + 1) * kY2P + 4 * g) = round4(y2v[q]);
+    }
     __syncthreads();
 
     // y3 rows of this wave's parity: local rows li = 2 t + 1 - py (row 8 s - 1 + li)
@@ -275,14 +407,17 @@ __global__ __launch_bounds__(512) void conv34_kernel(const TrainArgs a) {
         const f32x4 c = mma16(w4f, round4(y3[t]), kZero4);   // taps 4 lq .. + 3 of pixel x
 #pragma unroll
         for (int v = 0; v < 4; ++v) col[(li * 16 + 4 * lq + v) * kColW + x + 1] = in ? c[v] : 0.f;
-        if (li >= 1 && li <= 8) store4(a.w.y3 + (((size_t)b * 64 + Y) * 64 + x) * 16 + 4 * lq, y3[t]);
+        if (li >= 1 && li <= 8) store4(a.w.y3 + (((size_t)b * 64 + Y) * 64 + xm) * 16 + 4 * (lane & 3), to_memory(y3[t], lane));
     }
     __syncthreads();
 
-    // logits and their loss gradient: row 16 s - 1 + zr, columns 2 u and 2 u + 1
+    // logits, their loss and its gradient: row 16 s - 1 + zr, columns 2 u and 2 u + 1
     const float inv = 1.0f / (float)((int64_t)a.B * kImg * kImg);
     float loss = 0.f, dsum = 0.f;
-    for (int i = tid; i < 18 * 64; i += 512) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int i = tid + 512 * q;
+        if (i >= 18 * 64) break;
         const int zr = i >> 6, u = i & 63, Z = 16 * s - 1 + zr;
         float d0 = 0.f, d1 = 0.f;
         if (Z >= 0 && Z < kImg) {
@@ -299,12 +434,13 @@ __global__ __launch_bounds__(512) void conv34_kernel(const TrainArgs a) {
             e0 += bias4;
             e1 += bias4;
             const size_t at = ((size_t)b * kImg + Z) * kImg + 2 * u;
-            const float t0 = a.targets[at] ? 1.f : 0.f, t1 = a.targets[at + 1] ? 1.f : 0.f;
-            d0 = (1.f / (1.f + expf(-e0)) - t0) * inv;
-            d1 = (1.f / (1.f + expf(-e1)) - t1) * inv;
+            const float t0 = tgt[q][0] ? 1.f : 0.f, t1 = tgt[q][1] ? 1.f : 0.f;
+            const float x0 = expf(-e0), x1 = expf(-e1);
+            d0 = (1.f / (1.f + x0) - t0) * inv;
+            d1 = (1.f / (1.f + x1) - t1) * inv;
             if (zr >= 1 && zr <= 16) {
-                loss += fmaxf(e0, 0.f) - e0 * t0 + log1pf(expf(-fabsf(e0)));
-                loss += fmaxf(e1, 0.f) - e1 * t1 + log1pf(expf(-fabsf(e1)));
+                loss += fmaxf(e0, 0.f) - e0 * t0 + softplus_abs(e0, x0);
+                loss += fmaxf(e1, 0.f) - e1 * t1 + softplus_abs(e1, x1);
                 dsum += d0;
                 dsum += d1;
                 *(float2*)(a.w.logits + at) = make_float2(e0, e1);
@@ -329,7 +465,7 @@ __global__ __launch_bounds__(512) void conv34_kernel(const TrainArgs a) {
         if (li < 1 || li > 8) continue;
         const int r = li - 1;   // row in the strip; dlogits rows 2 r + ky
         const f32x4 d = mask4(mma16(w4b, lds_taps(dlw + (2 * r + lq) * (kDlW / 2) + x), kZero4), y3[t]);
-        store4(a.w.dy3 + (((size_t)b * 64 + 8 * s + r) * 64 + x) * 16 + 4 * lq, d);
+        store4(a.w.dy3 + (((size_t)b * 64 + 8 * s + r) * 64 + xm) * 16 + 4 * (lane & 3), to_memory(d, lane));
         bsum = add4(bsum, d);
 #pragma unroll
         for (int v = 0; v < 4; ++v) y3t[(4 * lq + v) * kY3T + r * 64 + x] = to_bf16(y3[t][v]);
@@ -378,46 +514,51 @@ __global__ __launch_bounds__(512) void conv34_kernel(const TrainArgs a) {
 // ------------------------------------------------------------------ backward of the third layer
 // Units of (set, 8 rows of y2), dealt round robin: dy3 rows 16 s' - 1 .. + 17
 // as one bfloat16 plane per channel, and y2 transposed, both in LDS.  dy2
-// (masked) takes the 16 taps of one channel per matrix instruction; the K3
-// gradient stays in registers over a workgroup's units.
+// (masked) takes the 16 taps of one channel per matrix instruction, weights
+// read four channels ahead; the K3 gradient stays in registers over a
+// workgroup's units.  Bound by memory (70 MB at 128 sets) and its latency,
+// hence two workgroups a CU: 24.8 us, 28.3 us with one (188 registers), 39 us
+// with all weights held in registers, which spill.
 constexpr int kD3W = 34;                      // dwords of a dy3 plane row: entry X + 1, X = -1 .. 66
 constexpr int kD3P = 18 * kD3W;               // dwords of a plane
 constexpr int kY2T = 256 + 8;
 
-__global__ __launch_bounds__(512) void back3_kernel(const TrainArgs a) {
+__global__ __launch_bounds__(512, 4) void back3_kernel(const TrainArgs a) {
     __shared__ __align__(16) uint32_t pl[16 * kD3P];
     __shared__ __align__(16) bf16_t y2t[32 * kY2T];
     __shared__ float red[8 * 32];
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bf16_t* T = a.w.packed + kT3b;
-    const int ky = lr >> 2, kx = lr & 3;
-    const uint32_t sel = (kx & 1) ? 0x07060302u : 0x05040100u;
     f32x4 g[2][2] = {{kZero4, kZero4}, {kZero4, kZero4}};   // [channel o - 2 wave][input channel tile]
     f32x4 bsum[2] = {kZero4, kZero4};
     for (int unit = blockIdx.x; unit < 4 * a.B; unit += gridDim.x) {
         const int b = unit >> 2, s = unit & 3;
-        for (int i = tid; i < 18 * 33 * 4; i += 512) {
-            const int cg = i & 3, j = (i >> 2) % 33, r = i / 132, y = 16 * s - 1 + r;
-            const float* row = a.w.dy3 + (((size_t)b * 64 + y) * 64 + 2 * j) * 16 + 4 * cg;
-            const bool in = y >= 0 && y < 64;
-            const f32x4 v0 = in && j > 0 ? load4(row - 16) : kZero4, v1 = in && j < 32 ? load4(row) : kZero4;
+        int u0 = threadIdx.x;   // opaque, so that no address is kept over the units: 128 registers, two workgroups a CU
+        asm volatile("" : "+v"(u0));
+        const int tid = u0, lane = tid & 63, lr = lane & 15, lq = lane >> 4, ky = lr >> 2, kx = lr & 3;
+        const uint32_t sel = (kx & 1) ? 0x07060302u : 0x05040100u;
+        load_planes<512, 64, 16, 4, 18, kD3W, kD3P>(a.w.dy3 + (size_t)b * 4096 * 16, 16 * s - 1, 0, pl, tid);
+        __builtin_amdgcn_sched_barrier(0);
+        load_transposed<512, 256, 32, kY2T / 2>(a.w.y2 + ((size_t)b * 1024 + 256 * s) * 32, (uint32_t*)y2t, tid);
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x4 w[4][2];   // four channels ahead
 #pragma unroll
-            for (int e = 0; e < 4; ++e) pl[(4 * cg + e) * kD3P + r * kD3W + j] = pack2(v0[e], v1[e]);
-        }
-        for (int i = tid; i < 128 * 8; i += 512) {
-            const int cg = i & 7, j = i >> 3;
-            const float* row = a.w.y2 + ((size_t)b * 1024 + 256 * s + 2 * j) * 32 + 4 * cg;
-            const f32x4 v0 = load4(row), v1 = load4(row + 32);
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) ((uint32_t*)y2t)[(4 * cg + e) * (kY2T / 2) + j] = pack2(v0[e], v1[e]);
-        }
+            for (int ct = 0; ct < 2; ++ct) w[u][ct] = frag4(T, ct * 16 + u, lane);
         __syncthreads();
+        f32x4 y2v[2][2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct)
+                y2v[t][ct] = load4(a.w.y2 + (((size_t)b * 32 + 8 * s + wave) * 32 + 16 * t + (lane >> 2)) * 32 + 16 * ct + 4 * (lane & 3));
         // dy2 row 8 s + wave: two tiles of 16 pixels by two of 16 channels
         f32x4 d[2][2] = {{kZero4, kZero4}, {kZero4, kZero4}}, done[2][2] = {{kZero4, kZero4}, {kZero4, kZero4}};
-#pragma unroll
-        for (int o = 0; o < 16; ++o) {
-            if (o == a.chunk3) {   // 8 or 16: at most two chains
+#pragma unroll 1
+        for (int o0 = 0; o0 < 16; o0 += 4) {
+            if (o0 == a.chunk3) {   // eight, or all sixteen
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -426,26 +567,30 @@ __global__ __launch_bounds__(512) void back3_kernel(const TrainArgs a) {
                         d[t][ct] = kZero4;
                     }
             }
-            const uint32_t* p = pl + o * kD3P + (2 * wave + lq) * kD3W + lr;
-            const bf16x4 v0 = lds_taps(p), v1 = lds_taps(p + 16);
+            const uint32_t* p = pl + o0 * kD3P + (2 * wave + lq) * kD3W + lr;
+            const int next = o0 < 12 ? o0 + 4 : 0;
 #pragma unroll
-            for (int ct = 0; ct < 2; ++ct) {
-                const bf16x4 w = loadw(T + ((16 * ct + lr) * 16 + o) * 16 + 4 * lq);
-                d[0][ct] = mma16(w, v0, d[0][ct]);
-                d[1][ct] = mma16(w, v1, d[1][ct]);
+            for (int u = 0; u < 4; ++u) {
+                const bf16x4 v0 = lds_taps(p + u * kD3P), v1 = lds_taps(p + u * kD3P + 16);
+#pragma unroll
+                for (int ct = 0; ct < 2; ++ct) {
+                    d[0][ct] = mma16(w[u][ct], v0, d[0][ct]);
+                    d[1][ct] = mma16(w[u][ct], v1, d[1][ct]);
+                    w[u][ct] = frag4(T, ct * 16 + next + u, lane);
+                }
             }
         }
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int ct = 0; ct < 2; ++ct) {
-                const size_t at = (((size_t)b * 32 + 8 * s + wave) * 32 + 16 * t + lr) * 32 + 16 * ct + 4 * lq;
-                const f32x4 m = mask4(add4(done[t][ct], d[t][ct]), load4(a.w.y2 + at));
+                const size_t at = (((size_t)b * 32 + 8 * s + wave) * 32 + 16 * t + (lane >> 2)) * 32 + 16 * ct + 4 * (lane & 3);
+                const f32x4 m = mask4(to_memory(add4(done[t][ct], d[t][ct]), lane), y2v[t][ct]);
                 store4(a.w.dy2 + at, m);
                 bsum[ct] = add4(bsum[ct], m);
             }
         // K3 gradient of the channels 2 wave and 2 wave + 1: columns taps, k = 16 pixels of a row
-#pragma unroll 4
+#pragma unroll 2
         for (int c = 0; c < 16; ++c) {
             const bf16x4 x0 = lds4(y2t + lr * kY2T + 16 * c + 4 * lq), x1 = lds4(y2t + (16 + lr) * kY2T + 16 * c + 4 * lq);
             const uint32_t* p = pl + 2 * wave * kD3P + (2 * (c >> 1) + ky) * kD3W + 16 * (c & 1) + 4 * lq + (kx >> 1);
@@ -470,8 +615,8 @@ __global__ __launch_bounds__(512) void back3_kernel(const TrainArgs a) {
     for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const float sv = sum16(bsum[ct][v]);
-            if (lr == 0) red[wave * 32 + 16 * ct + 4 * lq + v] = sv;
+            const float sv = sum_rows(bsum[ct][v]);
+            if (lane < 4) red[wave * 32 + 16 * ct + 4 * lane + v] = sv;
         }
     __syncthreads();
     if (tid < 32) {
@@ -484,88 +629,74 @@ __global__ __launch_bounds__(512) void back3_kernel(const TrainArgs a) {
 // ------------------------------------------------------------------ backward of the second layer
 // dy1 of one (set, 8 rows of y1) a workgroup: dy2 rows 16 s - 1 .. 16 s + 16
 // as one bfloat16 plane per channel; a wave takes 16 of the 64 channels and
-// four rows of 16 pixels, its weights in registers.
+// four rows of 16 pixels, its weights read four channels ahead (with all 32
+// held, 141 registers and one workgroup a CU: 52 us at 512 sets, 39 us so).
 constexpr int kD2W = 18;                      // dwords of a dy2 plane row: entry X + 1, X = -1 .. 34
 
-__global__ __launch_bounds__(512) void back2_kernel(const TrainArgs a) {
-    __shared__ __align__(16) uint32_t pl[32 * 18 * kD2W];
-    __shared__ float red[2 * 64];
+__device__ __forceinline__ void dy1_strip(const TrainArgs& a, uint32_t* pl, float* red, int blk) {
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int b = (int)blockIdx.x >> 1, s = (int)blockIdx.x & 1;
+    const int b = blk >> 1, s = blk & 1;
     const int ct = wave & 3, r0 = 4 * (wave >> 2);
-    bf16x4 w[32];
+    bf16x4 w[4];   // four channels ahead
 #pragma unroll
-    for (int o = 0; o < 32; ++o) w[o] = loadw(a.w.packed + kT2b + ((16 * ct + lr) * 32 + o) * 16 + 4 * lq);
-    for (int i = tid; i < 18 * 17 * 8; i += 512) {
-        const int cg = i & 7, j = (i >> 3) % 17, r = i / 136, y = 16 * s - 1 + r;
-        const float* row = a.w.dy2 + (((size_t)b * 32 + y) * 32 + 2 * j) * 32 + 4 * cg;
-        const bool in = y >= 0 && y < 32;
-        const f32x4 v0 = in && j > 0 ? load4(row - 32) : kZero4, v1 = in && j < 16 ? load4(row) : kZero4;
+    for (int u = 0; u < 4; ++u) w[u] = frag4(a.w.packed + kT2b, ct * 32 + u, lane);
+    f32x4 y1v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) pl[((4 * cg + e) * 18 + r) * kD2W + j] = pack2(v0[e], v1[e]);
-    }
+    for (int r = 0; r < 4; ++r) y1v[r] = load4(a.w.y1 + (((size_t)b * 16 + 8 * s + r0 + r) * 16 + (lane >> 2)) * 64 + 16 * ct + 4 * (lane & 3));
+    load_planes<512, 32, 32, 8, 18, kD2W, 18 * kD2W>(a.w.dy2 + (size_t)b * 1024 * 32, 16 * s - 1, 0, pl, tid);
     __syncthreads();
     f32x4 d[4] = {kZero4, kZero4, kZero4, kZero4}, done[4] = {kZero4, kZero4, kZero4, kZero4};
-    int next = a.chunk2;
-#pragma unroll
-    for (int o = 0; o < 32; ++o) {
-        if (o == next) {
-            next += a.chunk2;
+    int chain = a.chunk2;   // a multiple of four
+#pragma unroll 1
+    for (int o0 = 0; o0 < 32; o0 += 4) {
+        if (o0 == chain) {
+            chain += a.chunk2;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 done[r] = add4(done[r], d[r]);
                 d[r] = kZero4;
             }
         }
+        const uint32_t* p = pl + (o0 * 18 + 2 * r0 + lq) * kD2W + lr;
+        const int next = ct * 32 + (o0 < 28 ? o0 + 4 : 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) d[r] = mma16(w[o], lds_taps(pl + (o * 18 + 2 * (r0 + r) + lq) * kD2W + lr), d[r]);
+        for (int u = 0; u < 4; ++u) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) d[r] = mma16(w[u], lds_taps(p + (u * 18 + 2 * r) * kD2W), d[r]);
+            w[u] = frag4(a.w.packed + kT2b, next + u, lane);
+        }
     }
     f32x4 bsum = kZero4;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const size_t at = (((size_t)b * 16 + 8 * s + r0 + r) * 16 + lr) * 64 + 16 * ct + 4 * lq;
-        const f32x4 m = mask4(add4(done[r], d[r]), load4(a.w.y1 + at));
+        const size_t at = (((size_t)b * 16 + 8 * s + r0 + r) * 16 + (lane >> 2)) * 64 + 16 * ct + 4 * (lane & 3);
+        const f32x4 m = mask4(to_memory(add4(done[r], d[r]), lane), y1v[r]);
         store4(a.w.dy1 + at, m);
         bsum = add4(bsum, m);
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        const float sv = sum16(bsum[v]);
-        if (lr == 0) red[(wave >> 2) * 64 + 16 * ct + 4 * lq + v] = sv;
+        const float sv = sum_rows(bsum[v]);
+        if (lane < 4) red[(wave >> 2) * 64 + 16 * ct + 4 * lane + v] = sv;
     }
     __syncthreads();
-    if (tid < 64) a.w.pc1[(size_t)blockIdx.x * 64 + tid] = red[tid] + red[64 + tid];
+    if (tid < 64) a.w.pc1[(size_t)blk * 64 + tid] = red[tid] + red[64 + tid];
 }
 
-// K2 gradient: a workgroup takes 8 of the 32 output channels (blockIdx.y)
-// over every gridDim.x-th set, one channel a wave, all 64 input channels.
+// K2 gradient: a workgroup takes 8 of the 32 output channels (from o0 on)
+// over every `parts`-th set, one channel a wave, all 64 input channels.
 constexpr int kY1T = 256 + 8;
 
-__global__ __launch_bounds__(512) void grad2_kernel(const TrainArgs a) {
-    __shared__ __align__(16) uint32_t pl[8 * 34 * kD2W];
-    __shared__ __align__(16) bf16_t y1t[64 * kY1T];
+__device__ __forceinline__ void k2_gradient(const TrainArgs& a, uint32_t* pl, bf16_t* y1t, int part0, int parts, int o0) {
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int o0 = 8 * (int)blockIdx.y, ky = lr >> 2, kx = lr & 3;
+    const int ky = lr >> 2, kx = lr & 3;
     const uint32_t sel = (kx & 1) ? 0x07060302u : 0x05040100u;
     f32x4 g[4] = {kZero4, kZero4, kZero4, kZero4};
-    for (int b = blockIdx.x; b < a.B; b += gridDim.x) {
-        for (int i = tid; i < 34 * 17 * 2; i += 512) {
-            const int cg = i & 1, j = (i >> 1) % 17, r = i / 34, y = r - 1;
-            const float* row = a.w.dy2 + (((size_t)b * 32 + y) * 32 + 2 * j) * 32 + o0 + 4 * cg;
-            const bool in = y >= 0 && y < 32;
-            const f32x4 v0 = in && j > 0 ? load4(row - 32) : kZero4, v1 = in && j < 16 ? load4(row) : kZero4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) pl[((4 * cg + e) * 34 + r) * kD2W + j] = pack2(v0[e], v1[e]);
-        }
-        for (int i = tid; i < 128 * 16; i += 512) {
-            const int cg = i & 15, j = i >> 4;
-            const float* row = a.w.y1 + ((size_t)b * 256 + 2 * j) * 64 + 4 * cg;
-            const f32x4 v0 = load4(row), v1 = load4(row + 64);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) ((uint32_t*)y1t)[(4 * cg + e) * (kY1T / 2) + j] = pack2(v0[e], v1[e]);
-        }
+    for (int b = part0; b < a.B; b += parts) {
+        load_planes<512, 32, 32, 2, 34, kD2W, 34 * kD2W>(a.w.dy2 + (size_t)b * 1024 * 32, -1, o0, pl, tid);
+        load_transposed<512, 256, 64, kY1T / 2>(a.w.y1 + (size_t)b * 256 * 64, (uint32_t*)y1t, tid);
         __syncthreads();
 #pragma unroll 4
         for (int c = 0; c < 16; ++c) {   // row c of y1
@@ -575,11 +706,24 @@ __global__ __launch_bounds__(512) void grad2_kernel(const TrainArgs a) {
         }
         __syncthreads();
     }
-    float* part = a.w.p2 + (size_t)blockIdx.x * kPart2;
+    float* part = a.w.p2 + (size_t)part0 * kPart2;
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
         for (int v = 0; v < 4; ++v) part[(16 * ct + 4 * lq + v) * 512 + (o0 + wave) * 16 + lr] = g[ct][v];
+}
+
+// Both need dy2 alone, so one launch does them: 4 * parts workgroups the
+// gradient (the longer ones first), then 2 B dy1, two a CU, so that one's
+// loads run under the other's products: 21.0 us at 128 sets, 26.4 us as two
+// launches.
+__global__ __launch_bounds__(512) void back2_kernel(const TrainArgs a, int parts) {
+    __shared__ __align__(16) char lds[8 * 34 * kD2W * 4 + 64 * kY1T * 2];
+    static_assert(32 * 18 * kD2W * 4 + 2 * 64 * 4 <= sizeof(lds), "dy1's planes in the same space");
+    uint32_t* pl = (uint32_t*)lds;
+    const int q = blockIdx.x;
+    if (q < 4 * parts) k2_gradient(a, pl, (bf16_t*)(pl + 8 * 34 * kD2W), q % parts, parts, 8 * (q / parts));
+    else dy1_strip(a, pl, (float*)(pl + 32 * 18 * kD2W), q - 4 * parts);
 }
 
 // ------------------------------------------------------------------ backward of the first layer
@@ -595,18 +739,12 @@ __global__ __launch_bounds__(512) void back1_kernel(const TrainArgs a) {
     const bf16_t* plh = (const bf16_t*)pl;
     bf16x4 w[8];
 #pragma unroll
-    for (int o = 0; o < 8; ++o) w[o] = loadw(a.w.packed + kT1b + (lr * 64 + 8 * wave + o) * 16 + 4 * lq);
+    for (int o = 0; o < 8; ++o) w[o] = frag4(a.w.packed + kT1b, 8 * wave + o, lane);
     f32x4 g[8];
 #pragma unroll
     for (int o = 0; o < 8; ++o) g[o] = kZero4;
     for (int b = blockIdx.x; b < a.B; b += gridDim.x) {
-        for (int i = tid; i < 128 * 16; i += 512) {
-            const int cg = i & 15, j = i >> 4;
-            const float* row = a.w.dy1 + ((size_t)b * 256 + 2 * j) * 64 + 4 * cg;
-            const f32x4 v0 = load4(row), v1 = load4(row + 64);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) pl[(4 * cg + e) * (kY1T / 2) + j] = pack2(v0[e], v1[e]);
-        }
+        load_transposed<512, 256, 64, kY1T / 2>(a.w.dy1 + (size_t)b * 256 * 64, pl, tid);
         f32x4 xv;   // channel lr of input pixels 4 lq .. 4 lq + 3
 #pragma unroll
         for (int v = 0; v < 4; ++v) xv[v] = a.w.x0[((size_t)b * 16 + 4 * lq + v) * 16 + lr];
@@ -646,14 +784,25 @@ __global__ __launch_bounds__(256) void back_mlp_kernel(const TrainArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b0 = ((int)blockIdx.x / 4) * 16, n = (((int)blockIdx.x % 4) * 4 + wave) * 16 + lr;
-    const int br = min(b0 + lr, a.B - 1);
-    const float* dh2 = a.w.dh2 + (size_t)br * 256 + 4 * lq;
-    const bf16_t* W = a.w.packed + kT2w + n * 256 + 4 * lq;
+    bf16x4 w[16];
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) w[ks] = frag4(a.w.packed + kT2w, ((int)blockIdx.x % 4 * 4 + wave) * 16 + ks, lane);
+    __shared__ __align__(16) bf16_t ds[16 * 264];
+    f32x4 dv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {   // set 4 q + tid / 64, four features a thread
+        const int b = min(b0 + 4 * q + wave, a.B - 1);
+        dv[q] = load4(a.w.dh2 + (size_t)b * 256 + 4 * lane);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *(bf16x4*)(ds + (4 * q + wave) * 264 + 4 * lane) = round4(dv[q]);
+    __syncthreads();
+    const bf16_t* p = ds + lr * 264 + 4 * lq;
     f32x4 d0 = kZero4, d1 = kZero4;
 #pragma unroll
-    for (int k = 0; k < 128; k += 16) {
-        d0 = mma16(round4(load4(dh2 + k)), loadw(W + k), d0);
-        d1 = mma16(round4(load4(dh2 + k + 128)), loadw(W + k + 128), d1);
+    for (int ks = 0; ks < 8; ++ks) {
+        d0 = mma16(lds4(p + 16 * ks), w[ks], d0);
+        d1 = mma16(lds4(p + 16 * ks + 128), w[ks + 8], d1);
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -682,7 +831,7 @@ struct FinishArgs {
     int seg_blocks;
 };
 
-__global__ __launch_bounds__(256) void finish_kernel(const TrainArgs a, const FinishArgs f, float* G) {
+__global__ __launch_bounds__(256) void finish_kernel(const TrainArgs a, const FinishArgs f, float* G, const Adam adam) {
     __shared__ float red[256];
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -695,23 +844,28 @@ __global__ __launch_bounds__(256) void finish_kernel(const TrainArgs a, const Fi
         const float *x = first ? a.w.u : a.w.h1, *d = first ? a.w.dh1 : a.w.dh2;
         const int xw = first ? 4 : 256;
         f32x4 g = kZero4;
-        for (int b0 = 0; b0 < a.B; b0 += 16) {
-            f32x4 xv = kZero4, dv = kZero4;
+        for (int b0 = 0; b0 < a.B; b0 += 64) {   // four products' operands under way at once
+            f32x4 xv[4], dv[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int b = b0 + 4 * lq + v;
-                if (b < a.B) {
-                    if (i < xw) xv[v] = x[(size_t)b * xw + i];
-                    dv[v] = d[(size_t)b * 256 + j];
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int b = b0 + 16 * q + 4 * lq + v;
+                    xv[q][v] = b < a.B && i < xw ? x[(size_t)b * xw + i] : 0.f;
+                    dv[q][v] = b < a.B ? d[(size_t)b * 256 + j] : 0.f;
                 }
-            }
-            g = mma16(round4(xv), round4(dv), g);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (b0 + 16 * q < a.B) g = mma16(round4(xv[q]), round4(dv[q]), g);
         }
         float* dst = G + (first ? a.L.W1 : a.L.W2);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = first ? 4 * lq + v : (t / 16) * 16 + 4 * lq + v;
-            if (row < xw) dst[row * 256 + j] = g[v];
+            if (row < xw) {
+                dst[row * 256 + j] = g[v];
+                if (adam.p) adam.update(dst - G + row * 256 + j, g[v]);
+            }
         }
         return;
     }
@@ -739,7 +893,10 @@ __global__ __launch_bounds__(256) void finish_kernel(const TrainArgs a, const Fi
         if (tid < w) red[tid] += red[tid + w];
         __syncthreads();
     }
-    if (tid < s.cols && e < s.n) s.dst[e] = s.div != 0.f ? red[tid] / s.div : red[tid];
+    if (tid < s.cols && e < s.n) {
+        s.dst[e] = s.div != 0.f ? red[tid] / s.div : red[tid];
+        if (adam.p && s.div == 0.f) adam.update(s.dst - G + e, red[tid]);
+    }
 }
 
 }  // namespace
@@ -780,7 +937,7 @@ WS carve(void* base, int B) {
 }
 
 hipError_t loss_grad(const float* P, const kl_c64* ta, const kl_c64* tb, const uint8_t* targets, int B, float* G,
-                     float* loss, const WS& w, hipStream_t s) {
+                     float* loss, const Adam& adam, const WS& w, hipStream_t s) {
     const TrainArgs a{P, ta, tb, targets, w, layout(), B, sum_chunk(1024 * B, 16), sum_chunk(256 * B, 32)};
     const Layout& L = a.L;
     const int set16 = (B + 15) / 16, n3 = std::min(4 * B, kParts3), n2 = std::min(B, kParts2), n1 = std::min(B, kParts1);
@@ -788,8 +945,7 @@ hipError_t loss_grad(const float* P, const kl_c64* ta, const kl_c64* tb, const u
     hipLaunchKernelGGL(conv12_kernel, dim3(4 * B), dim3(256), 0, s, a);
     hipLaunchKernelGGL(conv34_kernel, dim3(8 * B), dim3(512), 0, s, a);
     hipLaunchKernelGGL(back3_kernel, dim3(n3), dim3(512), 0, s, a);
-    hipLaunchKernelGGL(back2_kernel, dim3(2 * B), dim3(512), 0, s, a);
-    hipLaunchKernelGGL(grad2_kernel, dim3(n2, 4), dim3(512), 0, s, a);
+    hipLaunchKernelGGL(back2_kernel, dim3(2 * B + 4 * n2), dim3(512), 0, s, a, n2);
     hipLaunchKernelGGL(back1_kernel, dim3(n1), dim3(512), 0, s, a);
     hipLaunchKernelGGL(back_mlp_kernel, dim3(4 * set16), dim3(256), 0, s, a);
     FinishArgs f{};
@@ -811,7 +967,7 @@ hipError_t loss_grad(const float* P, const kl_c64* ta, const kl_c64* tb, const u
     add(w.dh2, G + L.b2, 256, B, 256, 32);
     add(w.dh1, G + L.b1, 256, B, 256, 32);
     f.seg_blocks = blocks;
-    hipLaunchKernelGGL(finish_kernel, dim3(blocks + 64 + 4), dim3(256), 0, s, a, f, G);
+    hipLaunchKernelGGL(finish_kernel, dim3(blocks + 64 + 4), dim3(256), 0, s, a, f, G, adam);
     return hipGetLastError();
 }
 

@@ -366,7 +366,7 @@ def test_training_batches_with_several_sum_chains_and_passes(B):
     """Batches whose input gradients are summed in several chains (1: two for
     dy2 and four for dy1; 33: four for dy1; 70: three, of unequal length),
     and whose weight gradients stay in a workgroup's registers over more than
-    one pass (70: K2 and K1; 130: K3 too).  Input gradients of the first,
+    one pass (70: K2; 130: K1 and K3 too).  Input gradients of the first,
     middle and last set, and weight gradients of a few output channels over
     every set, against the reference on the GPU's own inputs, within
     gamma(n) of the terms' magnitudes (as the layer-by-layer test).  The sums
@@ -412,3 +412,44 @@ def test_uncertainty_over_the_logits_range():
     ref = np.log1p(e) + a * (e / (1 + e))
     assert (np.abs(u - ref) <= 64 * U32 * ref + 2.0 ** -126).all(), (u, ref)
     assert np.isnan(kl.sur_uncertainty(_dev(np.full((1, 128, 128), np.nan))).item())
+
+
+@pytest.mark.parametrize("B", [1, 18, 130])
+def test_train_step_is_the_gradient_and_its_update(B):
+    """A step's update at the end of the gradient's last kernel: parameters,
+    moments, gradient and loss are those of kl_sur_loss_grad and kl_sur_adam,
+    bit for bit, over every parameter tensor."""
+    ta, tb = _sets(B, 21)
+    targets = _dev((np.random.default_rng(6).random((B, 128, 128)) < 0.1).astype(np.uint8), torch.uint8)
+    ta_d, tb_d = kl.as_c64(ta), kl.as_c64(tb)
+    rng = np.random.default_rng(7)
+    start = [_params(5), rng.normal(size=N.N_PARAMS) * 0.01, np.abs(rng.normal(size=N.N_PARAMS)) * 1e-4]
+    p, m, v = (_dev(x) for x in start)
+    loss, grad = kl.sur_loss_grad(p, ta, tb, targets)
+    kl.sur_adam(p, grad, m, v, 3, 1e-3)
+    p2, m2, v2 = (_dev(x) for x in start)
+    grad2, loss2 = torch.full_like(grad, np.nan), torch.zeros(1, device="cuda")
+    kl.sur_train_step(p2, m2, v2, grad2, 3, 1e-3, ta_d, tb_d, targets, kl.sur_workspace(B), loss2)
+    for a, b in ((p, p2), (m, m2), (v, v2), (grad, grad2), (loss, loss2)):
+        assert torch.equal(a, b)
+    assert not torch.equal(p, _dev(start[0]))
+
+
+@pytest.mark.parametrize("x", [0.0, 1e-6, -0.5, 1.0, -3.0, 8.0, -16.0, 40.0, -80.0, 95.0, -95.0, 200.0, -200.0, 1e30, -1e30])
+def test_loss_over_the_logits_range(x):
+    """Every logit x (the last layer's bias, its kernel zero) from 0 to where
+    e^-|x| underflows and e^|x| overflows, targets of both kinds: the mean of
+    softplus(x) - x t within 64 FP32 roundings (some 25 in a term, and 38
+    additions of terms of one sign), and FP32's smallest normal number."""
+    flat = _params(2).astype(np.float32)
+    flat[-257:-1] = 0.0   # K4
+    flat[-1] = x          # c4
+    ta, tb = _sets(2, 15)
+    t = (np.random.default_rng(4).random((2, 128, 128)) < 0.3).astype(np.uint8)
+    loss, grad = kl.sur_loss_grad(_dev(flat), ta, tb, _dev(t, torch.uint8))
+    x = float(np.float32(x))
+    ref = (max(x, 0.0) - x * t.astype(np.float64) + np.log1p(np.exp(-abs(x)))).mean()
+    assert abs(loss.item() - ref) <= 64 * U32 * ref + 2.0 ** -126, (loss.item(), ref)
+    g = grad[-1].item()
+    d = 1.0 / (1.0 + np.exp(-x)) - t if x > -700 else -t.astype(np.float64)
+    assert abs(g - d.mean()) <= 64 * U32 * np.abs(d).mean() + 2.0 ** -126, (g, d.mean())
