@@ -275,47 +275,9 @@ __device__ __forceinline__ T conv(double x) { return (T)x; }
 template <typename T>
 __device__ __forceinline__ bool bounded(T x, double lim) { return x <= (T)lim && x >= -(T)lim; }
 
-// Head map of head index hidx: prefix-table product of its first k letters
-// times its m lane letters (FP64, left to right), in both forms.
+// Both forms of a head's product M (last letter e, head index hidx).
 template <typename T>
-__device__ inline Head<T> compute_head(uint64_t hidx, const Split& sp, const m64* __restrict__ prefix,
-                                       const uint8_t* __restrict__ plast, const m64* G, const Fold& f) {
-    m64 M;
-    int e;
-    if (sp.k + sp.m == 0) {
-        M = {{1.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {1.0, 0.0}};
-        e = -1;
-    } else {
-        uint64_t p;
-        uint64_t u;
-        if (sp.m == 0) {
-            p = hidx;
-            u = 0;
-        } else if (hidx >> 32) {
-            p = hidx / sp.pow3_m;
-            u = hidx - p * sp.pow3_m;
-        } else {
-            const uint32_t h32 = (uint32_t)hidx;
-            const uint32_t p32 = h32 / sp.pow3_m;
-            p = p32;
-            u = h32 - p32 * sp.pow3_m;
-        }
-        M = prefix[p];
-        e = plast[p];
-        // lane letters: base-3 digits of u, most significant first
-        uint64_t packed = 0;
-        for (int j = 0; j < sp.m; ++j) {
-            const uint64_t q = u / 3;
-            packed |= (u - 3 * q) << (2 * j);
-            u = q;
-        }
-        for (int j = sp.m - 1; j >= 0; --j) {
-            const int t = (int)((packed >> (2 * j)) & 3);
-            const int c = t + (t >= inv_letter(e));
-            M = mmul(M, G[c]);
-            e = c;
-        }
-    }
+__device__ inline Head<T> head_forms(const m64& M, int e, uint64_t hidx, const Fold& f) {
     Head<T> h;
     h.e = e;
     h.aniso = conv<T>(f.aniso);
@@ -358,6 +320,50 @@ __device__ inline Head<T> compute_head(uint64_t hidx, const Split& sp, const m64
     h.C = {conv<T>(C.re), conv<T>(C.im)};
     h.D = {conv<T>(D.re), conv<T>(D.im)};
     return h;
+}
+
+// Head map of head index hidx: prefix-table product of its first k letters
+// times its m lane letters (FP64, left to right), in both forms.
+template <typename T>
+__device__ inline Head<T> compute_head(uint64_t hidx, const Split& sp, const m64* __restrict__ prefix,
+                                       const uint8_t* __restrict__ plast, const m64* G, const Fold& f) {
+    m64 M;
+    int e;
+    if (sp.k + sp.m == 0) {
+        M = {{1.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {1.0, 0.0}};
+        e = -1;
+    } else {
+        uint64_t p;
+        uint64_t u;
+        if (sp.m == 0) {
+            p = hidx;
+            u = 0;
+        } else if (hidx >> 32) {
+            p = hidx / sp.pow3_m;
+            u = hidx - p * sp.pow3_m;
+        } else {
+            const uint32_t h32 = (uint32_t)hidx;
+            const uint32_t p32 = h32 / sp.pow3_m;
+            p = p32;
+            u = h32 - p32 * sp.pow3_m;
+        }
+        M = prefix[p];
+        e = plast[p];
+        // lane letters: base-3 digits of u, most significant first
+        uint64_t packed = 0;
+        for (int j = 0; j < sp.m; ++j) {
+            const uint64_t q = u / 3;
+            packed |= (u - 3 * q) << (2 * j);
+            u = q;
+        }
+        for (int j = sp.m - 1; j >= 0; --j) {
+            const int t = (int)((packed >> (2 * j)) & 3);
+            const int c = t + (t >= inv_letter(e));
+            M = mmul(M, G[c]);
+            e = c;
+        }
+    }
+    return head_forms<T>(M, e, hidx, f);
 }
 
 __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -1126,7 +1132,37 @@ struct PerWordArgs {
     const uint64_t* idx;
     c64* out;
     uint64_t n;
+    uint32_t inv_R, inv_pow3;   // div32_inverse of sp.R and sp.pow3_m
 };
+
+// n / d and n % d of 32-bit values by inv = min(2^32 / d, 2^32 - 1) rounded
+// down: the high half of n inv is the quotient or one less.
+__host__ __device__ constexpr uint32_t div32_inverse(uint64_t d) {
+    return (uint32_t)(d > 1 ? (1ull << 32) / d : 0xFFFFFFFFull);
+}
+__device__ __forceinline__ uint32_t div32(uint32_t n, uint32_t d, uint32_t inv, uint32_t& rem) {
+    uint32_t q = __umulhi(n, inv);
+    rem = n - q * d;
+    const bool up = rem >= d;
+    q += up ? 1u : 0u;
+    rem -= up ? d : 0u;
+    return q;
+}
+
+// Head h at suffix table entry `entry`.
+template <typename T>
+__device__ __forceinline__ void suffix_point(const Head<T>& h, uint64_t entry, const Tables& tab, const void* tail_homog,
+                                             bool affine, T& px, T& py) {
+    if (affine) {
+        const cpx<T> y = ((const cpx<T>*)tab.tail)[entry];
+        if (h.pole) eval_pole(h, y, px, py);
+        else eval_general(h, y, px, py);
+    } else {
+        const cpx<T>* hm = (const cpx<T>*)tail_homog;
+        if (h.pole) eval_pole_h(h, hm[2 * entry], hm[2 * entry + 1], px, py);
+        else eval_general_h(h, hm[2 * entry], hm[2 * entry + 1], px, py);
+    }
+}
 
 // Value of word i of depth sp.depth, with the renderer's arithmetic.
 template <typename T>
@@ -1146,15 +1182,7 @@ __device__ inline void word_point(uint64_t i, const Split& sp, const Tables& tab
         const int y1 = (int)j + ((int)j >= inv_letter(h.e));
         entry = (uint64_t)y1 * sp.R1 + tt;
     }
-    if (affine) {
-        const cpx<T> y = ((const cpx<T>*)tab.tail)[entry];
-        if (h.pole) eval_pole(h, y, px, py);
-        else eval_general(h, y, px, py);
-    } else {
-        const cpx<T>* hm = (const cpx<T>*)tail_homog;
-        if (h.pole) eval_pole_h(h, hm[2 * entry], hm[2 * entry + 1], px, py);
-        else eval_general_h(h, hm[2 * entry], hm[2 * entry + 1], px, py);
-    }
+    suffix_point<T>(h, entry, tab, tail_homog, affine, px, py);
 }
 
 template <typename T>
@@ -1249,21 +1277,69 @@ hipError_t launch_perword_batch(const PerWordBatchJob& job, hipStream_t s) {
     return hipGetLastError();
 }
 
+// One word a thread, its index asked for before the tables' form is known.
+// What bounds it: the instructions of a word's head (some 300, and 45 a lane
+// letter, two thirds of them FP64), then the gathers of its prefix product
+// and suffix.  Divisions therefore take precomputed inverses, and lane
+// letters are split off in 32 bits (u < 3^m <= 3^20).  2^20 words: 23.8 us
+// at depth 18, 39.5 at depth 30 (three and fifteen lane letters), 10^5 words
+// of depth 38 32.4, set-up included; with 64-bit divisions 24.3, 43.7 and
+// 41.5.  Four lanes reading one product together and turning it over in LDS
+// gained nothing (24.1, 41.9, 33.3).
 template <typename T>
 __global__ __launch_bounds__(256) void eval_kernel(const PerWordArgs a) {
     __shared__ m64 G[4];
+    const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t i = tid < a.n ? a.idx[tid] : a.n_words;
     if (threadIdx.x < 4) G[threadIdx.x] = a.gens.g[threadIdx.x];
     const bool affine = tail_affine_block(a.tab);  // also orders the G stores before their use
-    const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (tid >= a.n) return;
-    const uint64_t i = a.idx[tid];
-    if (i >= a.n_words) {
-        a.out[tid] = {__builtin_nan(""), __builtin_nan("")};
-        return;
-    }
+    const bool valid = i < a.n_words;
     T px, py;
-    word_point<T>(i, a, G, affine, px, py);
-    a.out[tid] = {(double)px, (double)py};
+    if (a.sp.k == 0) {
+        if (valid) word_point<T>(i, a, G, affine, px, py);
+    } else {
+        // word -> head (prefix p, lane letters u) and suffix t; word 0 for a lane without one
+        uint64_t hidx = 0;
+        uint32_t t = 0, p = 0, u = 0;
+        if (a.n_words >> 32) {
+            if (valid) {
+                hidx = i / a.sp.R;
+                t = (uint32_t)(i - hidx * a.sp.R);
+            }
+        } else if (valid) {
+            hidx = div32((uint32_t)i, (uint32_t)a.sp.R, a.inv_R, t);
+        }
+        if (a.sp.n_heads >> 32) {
+            const uint64_t q = hidx / a.sp.pow3_m;
+            p = (uint32_t)q;
+            u = (uint32_t)(hidx - q * a.sp.pow3_m);
+        } else {
+            p = div32((uint32_t)hidx, a.sp.pow3_m, a.inv_pow3, u);
+        }
+        m64 M = a.tab.prefix[p];
+        int e = a.tab.prefix_last[p];
+        uint64_t packed = 0;   // lane letters: base-3 digits of u, most significant first
+        for (int q = 0; q < a.sp.m; ++q) {
+            const uint32_t d = u / 3;
+            packed |= (uint64_t)(u - 3 * d) << (2 * q);
+            u = d;
+        }
+        for (int q = a.sp.m - 1; q >= 0; --q) {
+            const int d = (int)((packed >> (2 * q)) & 3);
+            const int c = d + (d >= inv_letter(e));
+            M = mmul(M, G[c]);
+            e = c;
+        }
+        const Head<T> h = head_forms<T>(M, e, hidx, a.fold);
+        const uint32_t first = (t >= a.sp.R1 ? 1u : 0u) + (t >= 2u * a.sp.R1 ? 1u : 0u);   // t < 3 R1
+        const uint32_t y1 = first + ((int)first >= inv_letter(e));
+        const uint64_t entry = (uint64_t)y1 * a.sp.R1 + (t - first * a.sp.R1);
+        suffix_point<T>(h, entry, a.tab, a.tail_homog, affine, px, py);
+    }
+    if (tid < a.n) {
+        if (valid) a.out[tid] = {(double)px, (double)py};
+        else a.out[tid] = {__builtin_nan(""), __builtin_nan("")};
+    }
 }
 
 }  // namespace kl
@@ -1351,6 +1427,8 @@ static hipError_t launch_eval_t(const EvalJob& job, hipStream_t s) {
     p.idx = job.idx;
     p.out = job.out;
     p.n = job.n;
+    p.inv_R = div32_inverse(job.sp.R);
+    p.inv_pow3 = div32_inverse(job.sp.pow3_m);
     const uint64_t blocks = (job.n + 255) / 256;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     hipLaunchKernelGGL((eval_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, s, p);

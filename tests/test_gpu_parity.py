@@ -770,3 +770,32 @@ def test_tiling_takes_its_deepest_depth_tail(precision):
         kl.render(*C2, depth, win, image=acc2, precision=precision, min_depth=mind, first=a, count=b - a,
                   accumulate=a > 0)
     assert torch.equal(full, acc2)
+
+
+@pytest.mark.parametrize("depth,tail_len,lane_len", [
+    (2, 1, 0), (9, 8, 0), (10, 8, 1), (19, 1, 6), (19, 6, 4),   # fewer than 2^32 words
+    (20, 8, 3), (20, 1, 9), (21, 1, 8),                        # 2^32 words and more, fewer heads; more heads
+    (40, 8, 20)])                                              # the most lane letters
+def test_eval_words_at_the_edges_of_their_index_split(depth, tail_len, lane_len):
+    """Word -> prefix, lane letters and suffix: words on both sides of every
+    suffix, prefix and 2^32 boundary, for splits whose word or head counts
+    need 32 bits and for those that need more, in both precisions.  FP64
+    values against the oracle (1e-10, as the values above); FP32 values bit
+    for bit those of the same words in other company."""
+    n = kl.num_words(depth)
+    R, P = 3 ** tail_len, 3 ** (tail_len + lane_len)
+    idx = {0, n - 1, n // 2}
+    for b in (R, P, 2 ** 32 - 1, 2 ** 32, 2 ** 32 * P // 3, R * 2 ** 32):
+        for q in (1, 2, n // b // 2, n // b):
+            idx |= {b * q - 1, b * q, b * q + 1}
+    idx = np.array(sorted(i for i in idx if 0 <= i < n), np.uint64)
+    kw = dict(tail_len=tail_len, lane_len=lane_len)
+    # FP64 suffix tables hold seven letters at most: the planner's split instead
+    z = _z(kl.eval_values(*C2, depth, idx, precision="fp64", **(kw if tail_len <= 7 else {})))
+    zr = O.eval_values(*C2, depth, idx)
+    assert (np.abs(z - zr) <= 1e-10 * np.maximum(1, np.abs(zr))).all()
+    full = np.concatenate([idx, idx[::-1], np.array([n], np.uint64)])
+    a = _z(kl.eval_values(*C2, depth, idx, precision="fp32", **kw))
+    b = _z(kl.eval_values(*C2, depth, full.view(np.int64), precision="fp32", **kw))
+    assert np.array_equal(a, b[:len(idx)]) and np.array_equal(a, b[len(idx):-1][::-1]) and np.isnan(b[-1])
+    assert (np.abs(a - zr) <= 1e-3 * np.maximum(1, np.abs(zr))).all()
