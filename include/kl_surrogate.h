@@ -22,11 +22,11 @@
  *
  * Arithmetic: the operands of every matrix product are rounded to bfloat16
  * (nearest even) and its products accumulated in FP32; everything else is
- * FP32.  kl_sur_forward runs the whole network of one set in one workgroup,
- * activations in LDS: the first linear layer (four inputs) on the vector
- * ALUs, every other product on the BF16 matrix cores.  Training runs every
- * product (the transposed convolutions in their column form, and all the
- * gradients) on the matrix cores.
+ * FP32.  kl_sur_forward keeps the activations of a strip of one set in LDS;
+ * training leaves every layer's in the workspace (kl_sur_workspace_tensor).
+ * Every product runs on the BF16 matrix cores, in training all the gradients
+ * too; inference alone takes the first linear layer (four inputs) on the
+ * vector ALUs.
  *
  * Parameters: one flat FP32 device vector of kl_sur_num_params() values in
  * the order W1 b1 W2 b2 K1 c1 K2 c2 K3 c3 K4 c4, each row-major as shaped

@@ -296,7 +296,7 @@ __host__ __device__ inline uint32_t walk_chunks(uint32_t burn_in, uint32_t n_ste
 // cleared while the other is read.  What bounds it: VALU issue (some 90
 // instructions a point, 28 of them the Philox rounds, whose 64-bit products
 // issue at a quarter of the rate; sums with carries in place of their chained
-// addends took 7% longer).  2^26 points in FP32: 153 us; with the bins
+// addends took 7% longer).  2^26 points in FP32: 153-161 us; with the bins
 // staged in LDS eight words apart (8-way bank conflicts), a second atomic and
 // five barriers 189.  Workgroups of 256 walkers take 7% less, but their regions
 // are half as long and the histogram kernel pays for it (64 us against 51).
