@@ -242,6 +242,14 @@ __device__ inline bool tail_affine_wave(const Tables& t) {
     return __ballot(bad != 0) == 0;
 }
 
+// A pointer read from device memory is generic to the compiler, and its
+// accesses flat: one under way then holds up every later LDS read, which
+// waits on the same counter.  This says that it points to global memory.
+template <typename P>
+__device__ __forceinline__ P* as_global(P* p) {
+    return (P*)(__attribute__((address_space(1))) P*)(uintptr_t)p;
+}
+
 // ------------------------------------------------------------------ shared arithmetic
 // Map of one head, rounded once to T, in two forms.
 //
@@ -569,6 +577,49 @@ struct GlobalSink {
         atomicAdd(image + bin, cnt);
     }
 };
+
+// MergeSink: a workgroup's runs are first added up by bin in an LDS hash
+// table, whose entries keep their bin until the workgroup flushes the table
+// (merge_flush); a run that finds both of its slots taken goes to the image.
+// Device-wide atomics all leave the XCD's L2, some 18 G a second, and a
+// unit's runs close a bin 2.9 times on average in Maskit's tiling to depth 14.
+constexpr int kMergeLog = 11, kMergeSlots = 1 << kMergeLog;
+constexpr uint32_t kFreeSlot = 0xFFFFFFFFu;   // no bin: images hold fewer than 2^32 - 1 bins
+
+struct MergeSink {
+    uint32_t* image;
+    uint32_t *bins, *counts;   // LDS, kMergeSlots each
+    KeyRange kr;
+    __device__ __forceinline__ void add(uint32_t row, uint32_t col, uint32_t cnt) const {
+        const uint32_t bin = row * kr.W + col;
+        const uint32_t slot = (bin * 0x9E3779B1u) >> (32 - kMergeLog);
+        uint32_t old = atomicCAS(bins + slot, kFreeSlot, bin);
+        uint32_t at = slot;
+        if (old != kFreeSlot && old != bin) {
+            at = slot ^ 1u;
+            old = atomicCAS(bins + at, kFreeSlot, bin);
+        }
+        if (old == kFreeSlot || old == bin) {
+            atomicAdd(counts + at, cnt);
+            asm volatile("");   // or the compiler joins both branches' adds in one flat atomic
+        } else {
+            atomicAdd(image + bin, cnt);
+        }
+    }
+};
+
+// The table's counts added to the image and its slots freed.  Every thread of
+// the workgroup takes part, between two barriers.
+__device__ __forceinline__ void merge_flush(uint32_t* image, uint32_t* bins, uint32_t* counts) {
+    for (int i = threadIdx.x; i < kMergeSlots; i += kBlock) {
+        const uint32_t bin = bins[i];
+        if (bin != kFreeSlot) {
+            atomicAdd(image + bin, counts[i]);
+            bins[i] = kFreeSlot;
+            counts[i] = 0;
+        }
+    }
+}
 
 constexpr int kTile = 32;
 
@@ -1252,17 +1303,22 @@ __global__ __launch_bounds__(256) void perword_batch_kernel(const PerWordBatchJo
                 else hi = mid - 1;
             }
             S = &a.sets[a.set_ids[lo]];
-            const bool affine = S->tab.tail_flags[0] == 0u;
+            Tables tab = S->tab;
+            tab.prefix = as_global(tab.prefix);
+            tab.prefix_last = as_global(tab.prefix_last);
+            tab.tail = as_global((const cpx<T>*)tab.tail);
+            const bool affine = as_global(tab.tail_flags)[0] == 0u;
             T px, py;
-            word_point<T>(w - a.word_offsets[lo], S->sp, S->tab, S->tail_homog, a.fold, S->gens.g, affine, px, py);
+            word_point<T>(w - a.word_offsets[lo], S->sp, tab, as_global((const cpx<T>*)S->tail_homog), a.fold, S->gens.g,
+                          affine, px, py);
             key = bin_key(px, py, a.width, a.height);
             tag = (uint32_t)lo;
         }
         // one atomic per run of equal bins of one set
         const uint32_t len = lane_run_length(key, tag);
         if (len && key != kDead) {
-            if (key != kOutside) atomicAdd(S->image + key, len);
-            else if (S->dropped) atomicAdd((unsigned long long*)S->dropped, (unsigned long long)len);
+            if (key != kOutside) atomicAdd(as_global(S->image) + key, len);
+            else if (S->dropped) atomicAdd((unsigned long long*)as_global(S->dropped), (unsigned long long)len);
         }
     }
 }
@@ -1290,7 +1346,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void eval_kernel(const PerWordArgs a) {
     __shared__ m64 G[4];
     const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t i = tid < a.n ? a.idx[tid] : a.n_words;
+    const uint64_t at = a.idx[min(tid, a.n - 1)], i = tid < a.n ? at : a.n_words;
     if (threadIdx.x < 4) G[threadIdx.x] = a.gens.g[threadIdx.x];
     const bool affine = tail_affine_block(a.tab);  // also orders the G stores before their use
     const bool valid = i < a.n_words;
@@ -1516,8 +1572,10 @@ __device__ __forceinline__ void flush_drop(uint64_t& drop, uint64_t* dst) {
 // waves, and reloads them between two barriers when its next unit belongs
 // to another set.  The last unit of a set may be partial: waves past the
 // set's last head skip it, and the idle lanes of a partly filled wave walk a
-// valid head without binning.
-template <typename T, bool DROP, bool BOUNDED = false>
+// valid head without binning.  Bound by VALU issue (suffixes of six letters),
+// or by the rate of the device's atomics (shorter ones), of which MERGE sends
+// fewer: Maskit's tiling to depth 14 (suffixes of four letters) 94 to 63 us.
+template <typename T, bool DROP, bool BOUNDED = false, bool MERGE = false>
 __global__ __launch_bounds__(kBlock) void render_batch_kernel(const BatchArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     m64* G = (m64*)(smem + a.table_bytes);
@@ -1526,6 +1584,17 @@ __global__ __launch_bounds__(kBlock) void render_batch_kernel(const BatchArgs a)
     // with BOUNDED: the set's node disks and one span queue per wave (bounded_unit)
     NodeDisk<T>* nodes = (NodeDisk<T>*)(smem + a.table_bytes + 4 * sizeof(m64));
     uint16_t* queue = (uint16_t*)(nodes + a.max_nodes) + wid * kQueue;
+
+    // with MERGE: the hash table of the workgroup's runs
+    uint32_t* bins = (uint32_t*)(smem + a.table_bytes + 4 * sizeof(m64));
+    uint32_t* counts = bins + kMergeSlots;
+    if constexpr (MERGE) {
+        for (int i = threadIdx.x; i < kMergeSlots; i += kBlock) {
+            bins[i] = kFreeSlot;
+            counts[i] = 0;
+        }
+        __syncthreads();
+    }
 
     int cur = -1;
     bool affine = true;
@@ -1538,6 +1607,10 @@ __global__ __launch_bounds__(kBlock) void render_batch_kernel(const BatchArgs a)
     Runs<DROP> s = {kOutsideKey, 0, 0};
     uint32_t t_words = 0;
     const KeyRange kr = key_range(a.W, a.H);
+    auto sink = [&] {
+        if constexpr (MERGE) return MergeSink{image, bins, counts, kr};
+        else return GlobalSink{image, kr};
+    };
 
     for (uint64_t unit = blockIdx.x; unit < a.total_units; unit += gridDim.x) {
         // set of this unit: the last set whose first unit is <= unit (uniform over the block)
@@ -1549,22 +1622,28 @@ __global__ __launch_bounds__(kBlock) void render_batch_kernel(const BatchArgs a)
         }
         if (lo != cur) {
             if (cur >= 0) {
-                close_run(s, t_words, GlobalSink{image, kr});
+                close_run(s, t_words, sink());
                 if (DROP) flush_drop(s.drop, dropped);
+                if constexpr (MERGE) {
+                    __syncthreads();
+                    merge_flush(image, bins, counts);   // the barrier below comes before the next run
+                }
             }
             reset_run(s, t_words);
             cur = lo;
             const SetDesc& S = a.sets[cur];
             sp = S.sp;
-            prefix = S.tab.prefix;
-            plast = S.tab.prefix_last;
-            image = S.image;
-            dropped = S.dropped;
+            prefix = as_global(S.tab.prefix);
+            plast = as_global(S.tab.prefix_last);
+            image = as_global(S.image);
+            dropped = as_global(S.dropped);
             base = a.unit_offsets[cur];
             __syncthreads();  // every wave is done with the previous set's table
-            affine = tail_affine_block(S.tab);
+            Tables tab = S.tab;
+            tab.tail_flags = as_global(tab.tail_flags);
+            affine = tail_affine_block(tab);
             const size_t bytes = (size_t)S.n_tail * (affine ? 1 : 2) * sizeof(cpx<T>);
-            const uint4* src = (const uint4*)(affine ? S.tab.tail : S.tail_homog);
+            const uint4* src = as_global((const uint4*)(affine ? S.tab.tail : S.tail_homog));
             for (uint32_t i = threadIdx.x; i < (uint32_t)((bytes + 15) / 16); i += kBlock) ((uint4*)smem)[i] = src[i];
             if (threadIdx.x < 4) G[threadIdx.x] = S.gens.g[threadIdx.x];
             if constexpr (BOUNDED) {
@@ -1591,29 +1670,40 @@ __global__ __launch_bounds__(kBlock) void render_batch_kernel(const BatchArgs a)
                 }
             }
             if (dual) {
-                if (affine) walk_tails<T, true, true>(h, smem, sp.R1, a.W, a.H, image, s, t_words);
-                else walk_tails<T, false, true>(h, smem, sp.R1, a.W, a.H, image, s, t_words);
+                if (affine) walk_tails_s<T, true, true>(h, smem, sp.R1, a.W, a.H, sink(), s, t_words);
+                else walk_tails_s<T, false, true>(h, smem, sp.R1, a.W, a.H, sink(), s, t_words);
             } else {
-                if (affine) walk_tails<T, true, false>(h, smem, sp.R1, a.W, a.H, image, s, t_words);
-                else walk_tails<T, false, false>(h, smem, sp.R1, a.W, a.H, image, s, t_words);
+                if (affine) walk_tails_s<T, true, false>(h, smem, sp.R1, a.W, a.H, sink(), s, t_words);
+                else walk_tails_s<T, false, false>(h, smem, sp.R1, a.W, a.H, sink(), s, t_words);
             }
         } else {
             const bool live = hidx < sp.n_heads;
             if (!live) hidx = sp.n_heads - 1;
-            close_run(s, t_words, GlobalSink{image, kr});
+            close_run(s, t_words, sink());
             reset_run(s, t_words);
             const Head<T> h = compute_head<T>(hidx, sp, prefix, plast, G, a.fold);
-            if (affine) walk_tails<T, true, true, true>(h, smem, sp.R1, a.W, a.H, image, s, t_words, live);
-            else walk_tails<T, false, true, true>(h, smem, sp.R1, a.W, a.H, image, s, t_words, live);
-            if (live) close_run(s, t_words, GlobalSink{image, kr});
+            if (affine) walk_tails_s<T, true, true, true>(h, smem, sp.R1, a.W, a.H, sink(), s, t_words, live);
+            else walk_tails_s<T, false, true, true>(h, smem, sp.R1, a.W, a.H, sink(), s, t_words, live);
+            if (live) close_run(s, t_words, sink());
             reset_run(s, t_words);
         }
     }
     if (cur >= 0) {
-        close_run(s, t_words, GlobalSink{image, kr});
+        close_run(s, t_words, sink());
         if (DROP) flush_drop(s.drop, dropped);
     }
+    if constexpr (MERGE) {
+        __syncthreads();
+        if (cur >= 0) merge_flush(image, bins, counts);
+    }
 }
+
+// Longest suffixes whose runs are merged.  Whole renders, with and without:
+// tilings to depth 14 (four letters) 91 and 124 us, to depth 15 (five) 150
+// and 201 us; at six letters runs are longer and the table's latency shows:
+// 60 sets of depths 9 .. 13 231 and 150 us, ten of depths 11 .. 13 110 and 97.
+// 2^11 slots hold the bins of most units (2^10: 153 us at depth 15).
+constexpr int kMergeTail = 5;
 
 hipError_t launch_render_batch(const BatchJob& job, hipStream_t s) {
     if (job.total_units == 0) return hipSuccess;
@@ -1630,16 +1720,20 @@ hipError_t launch_render_batch(const BatchJob& job, hipStream_t s) {
     const size_t esz = fp64 ? sizeof(cpx<double>) : sizeof(cpx<float>);
     // the largest table's suffix nodes (the table bytes hold its homogeneous form)
     a.max_nodes = job.bounded ? (uint32_t)(job.table_bytes / (2 * esz) / kNodeWords) : 0u;
+    const bool merge = !job.bounded && job.max_tail <= (uint32_t)num_words(kMergeTail);
     const size_t lds = (size_t)job.table_bytes + 4 * sizeof(m64) +
                        (job.bounded ? (size_t)a.max_nodes * (fp64 ? sizeof(NodeDisk<double>) : sizeof(NodeDisk<float>)) +
                                           (kBlock / kWave) * kQueue * 2
-                                    : 0);
+                                    : 0) +
+                       (merge ? 2 * kMergeSlots * sizeof(uint32_t) : 0);
     uint32_t grid = (uint32_t)std::min<uint64_t>(job.total_units, (uint64_t)job.grid_blocks);
     if (grid < 1) grid = 1;
     const bool drop = job.count_dropped != 0;
     void (*kern)(BatchArgs) =
         job.bounded ? (fp64 ? (drop ? render_batch_kernel<double, true, true> : render_batch_kernel<double, false, true>)
                             : (drop ? render_batch_kernel<float, true, true> : render_batch_kernel<float, false, true>))
+        : merge     ? (fp64 ? (drop ? render_batch_kernel<double, true, false, true> : render_batch_kernel<double, false, false, true>)
+                            : (drop ? render_batch_kernel<float, true, false, true> : render_batch_kernel<float, false, false, true>))
                     : (fp64 ? (drop ? render_batch_kernel<double, true> : render_batch_kernel<double, false>)
                             : (drop ? render_batch_kernel<float, true> : render_batch_kernel<float, false>));
     if (lds > 65536) {

@@ -799,3 +799,30 @@ def test_eval_words_at_the_edges_of_their_index_split(depth, tail_len, lane_len)
     b = _z(kl.eval_values(*C2, depth, full.view(np.int64), precision="fp32", **kw))
     assert np.array_equal(a, b[:len(idx)]) and np.array_equal(a, b[len(idx):-1][::-1]) and np.isnan(b[-1])
     assert (np.abs(a - zr) <= 1e-3 * np.maximum(1, np.abs(zr))).all()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("tail_len,size", [(4, (40, 24)), (5, (300, 200)), (4, (3000, 3000)), (5, (3000, 3000)),
+                                           (6, (300, 200))])
+def test_batched_runs_merged_by_bin_equal_single_renders(tail_len, size, precision):
+    """Batches whose suffixes are short enough (five letters) for a
+    workgroup's runs to be added up by bin first: images of a few bins, which
+    every run finds in its table, and of so many that a unit's bins overflow
+    it; sets of several depths, so that workgroups change sets; one letter
+    more for the other side of the rule.  Images and dropped counts are those
+    of the sets rendered one by one with the same suffixes, bit for bit, and a
+    second, accumulating render doubles them."""
+    ta = np.array([1.91 + 0.05j, 2.0, 1.93 + 0.02j, 2.2, 1.95 + 0.05j])
+    tb = np.array([2.0, 2.02 + 0.01j, 2.0, 2.1 - 0.1j, 2.05])
+    depths = [12, 13, 11, 12, 13]
+    win = (-1.5, 1.5, -1.2, 1.2, *size)
+    dropped = torch.zeros(5, dtype=torch.int64, device="cuda")
+    imgs = kl.render_many(ta, tb, depths, win, precision=precision, tail_len=tail_len, dropped=dropped)
+    for i in range(5):
+        d = torch.zeros(1, dtype=torch.int64, device="cuda")
+        one = kl.render(ta[i], tb[i], depths[i], win, precision=precision, tail_len=tail_len, dropped=d)
+        assert torch.equal(imgs[i], one), (i, int((imgs[i] - one).abs().sum()))
+        assert d.item() == dropped[i].item()
+    twice = kl.render_many(ta, tb, depths, win, images=imgs.clone(), precision=precision, tail_len=tail_len,
+                           accumulate=True)
+    assert torch.equal(twice, 2 * imgs)
