@@ -1323,22 +1323,25 @@ int kl_walk_render_ex(const kl_c64* ab, const kl_walk* walk, const kl_window* wi
     if ((rc = make_gens_ab(ab, &G))) return rc;
     hipStream_t s = (hipStream_t)o.stream;
     hipError_t e;
-    if (!o.accumulate) {
-        if ((e = launch_fill_u32(image_out, (uint64_t)window->width * window->height, 0, s)) != hipSuccess)
-            return hip_fail(e, "clear image");
-        if (o.dropped_out && (e = launch_fill_u64(o.dropped_out, 1, 0, s)) != hipSuccess)
-            return hip_fail(e, "clear dropped");
-    }
     WalkJob j = walk_job(G, walk, window, o.precision, kWalkRender);
     j.image = image_out;
     j.W = window->width;
     j.H = window->height;
     j.dropped = o.dropped_out;
-    if (o.hist_mode == KL_HIST_LDS || (o.hist_mode == KL_HIST_AUTO && np >= (1ull << 18) &&
-                                       walk_tiles(j.W, j.H) <= kMaxWalkTiles &&
-                                       walk_region_points(walk->n_steps) <= kWalkBinnedPoints)) {
+    const bool binned = o.hist_mode == KL_HIST_LDS || (o.hist_mode == KL_HIST_AUTO && np >= (1ull << 18) &&
+                                                       walk_tiles(j.W, j.H) <= kMaxWalkTiles &&
+                                                       walk_region_points(walk->n_steps) <= kWalkBinnedPoints);
+    const WalkBinned L = binned ? walk_binned_layout(j) : WalkBinned{};
+    if (!o.accumulate) {
+        // a binned render's first launch touches the image no more than to clear it
+        if (L.blocks) j.clear_bins = (uint64_t)j.W * j.H;
+        else if ((e = launch_fill_u32(image_out, (uint64_t)j.W * j.H, 0, s)) != hipSuccess)
+            return hip_fail(e, "clear image");
+        if (o.dropped_out && (e = launch_fill_u64(o.dropped_out, 1, 0, s)) != hipSuccess)
+            return hip_fail(e, "clear dropped");
+    }
+    if (binned) {
         Temp tmp(s);
-        const WalkBinned L = walk_binned_layout(j);
         void* buf = nullptr;
         if (L.blocks && (e = tmp.tables(&buf, L.bytes)) != hipSuccess) return hip_fail(e, "walk temporaries");
         e = launch_walk_binned(j, L, buf, s);

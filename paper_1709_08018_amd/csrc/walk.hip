@@ -314,6 +314,12 @@ __global__ __launch_bounds__(kWalkBlock) __attribute__((amdgpu_waves_per_eu(kWal
     for (uint32_t t = threadIdx.x; t < kMaxWalkTiles; t += blockDim.x) cnt[0][t] = 0;
     __syncthreads();
     const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    {   // the image is cleared while the walkers start; only the histograms add to it
+        const uint64_t n = (uint64_t)gridDim.x * blockDim.x;
+        const uint64_t n4 = ((uintptr_t)j.image & 15) == 0 ? j.clear_bins / 4 : 0;
+        for (uint64_t i = tid; i < n4; i += n) ((uint4*)j.image)[i] = make_uint4(0, 0, 0, 0);
+        for (uint64_t i = 4 * n4 + tid; i < j.clear_bins; i += n) j.image[i] = 0;
+    }
     const bool active = tid < j.n_walkers;   // the others step along on the first walker's stream
     const uint64_t walker = j.first_walker + (active ? tid : 0);
     const uint32_t n_total = 1 + j.burn_in + j.n_steps;
@@ -590,6 +596,7 @@ hipError_t launch_walk_binned(const WalkJob& j, const WalkBinned& L, void* buf, 
         WalkJob c = j;
         c.first_walker = j.first_walker + b0 * kWalkBlock;
         c.n_walkers = std::min(j.n_walkers - b0 * kWalkBlock, nb * kWalkBlock);
+        if (b0) c.clear_bins = 0;
         if (j.precision == KL_PREC_FP64)
             hipLaunchKernelGGL(walk_bin_kernel<double>, dim3((unsigned)nb), dim3(kWalkBlock), 0, s, c, ids, starts,
                                T_tiles, n_chunks);

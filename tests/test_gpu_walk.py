@@ -282,3 +282,23 @@ def test_large_walk_then_small_renders_share_the_buffer():
         for _ in range(40):
             assert torch.equal(kl.render(wl.C2_TA, wl.C2_TB, 10, win), ref_small)
         assert torch.equal(kl.walk_render(ab, 4, 0, 1 << 20, 0, 40, WIN_M), ref_walk)
+
+
+@pytest.mark.parametrize("n,offset,size", [(1, 0, (333, 77)), (600, 1, (333, 77)), (600, 3, (1001, 1003)),
+                                           (40000, 0, (2896, 2896)), (40000, 2, (5, 3))])
+def test_binned_walk_clears_its_image(n, offset, size):
+    """The binned render clears the image in its first launch: images full of
+    other counts, at every alignment, of more and of fewer bins than the
+    launch has threads; bins beside the image keep their values, and an
+    accumulating render adds to the image as it is."""
+    ab = kl.maskit_generators(wl.MASKIT_MU)
+    win = (-1.05, 1.05, -0.1, 2.0, *size)
+    W, H = size
+    want = kl.walk_render(ab, 5, 2, n, 1, 20, win, hist_mode="runs")
+    buf = torch.full((W * H + 8,), 7, dtype=torch.int32, device="cuda")
+    img = buf[offset:offset + W * H].view(H, W)
+    kl.walk_render(ab, 5, 2, n, 1, 20, win, image=img, hist_mode="lds")
+    assert torch.equal(img, want)
+    assert (buf[:offset] == 7).all() and (buf[offset + W * H:] == 7).all()
+    kl.walk_render(ab, 5, 2, n, 1, 20, win, image=img, hist_mode="lds", accumulate=True)
+    assert torch.equal(img, 2 * want)
