@@ -366,9 +366,12 @@ int kl_walk_eval_ex(const kl_c64 *ab, const kl_walk *walk, const kl_window *wind
  *   KL_HIST_RUNS  one global atomic add per point in the window;
  *   KL_HIST_LDS   each workgroup's points of 8 steps sorted by image tile
  *                 (2^15 bins) in LDS and staged in device temporaries
- *                 (2 bytes a point, in the library's buffer on the null
- *                 stream, else allocated on the stream), then counted
- *                 tile by tile in LDS; images of at most 256 tiles
+ *                 (16 bytes for each walker and block of steps 8 i .. 8 i + 7
+ *                 that it draws in, so 2 bytes a point in long walks and 16
+ *                 for a single one, and 4 bytes a tile for each 512 walkers
+ *                 and block; at most 336 MB a launch; in the library's buffer
+ *                 on the null stream, else allocated on the stream), then
+ *                 counted tile by tile in LDS; images of at most 256 tiles
  *                 (8,388,608 bins), at most 524,288 drawn points a walker;
  *   KL_HIST_AUTO  KL_HIST_LDS from 2^18 points up where it applies, else
  *                 KL_HIST_RUNS.

@@ -1316,9 +1316,8 @@ int kl_walk_render_ex(const kl_c64* ab, const kl_walk* walk, const kl_window* wi
     if (!image_out) return fail(KL_EINVAL, "image_out is NULL");
     if (o.hist_mode == KL_HIST_LDS && walk_tiles(window->width, window->height) > kMaxWalkTiles)
         return fail(KL_EINVAL, "hist_mode KL_HIST_LDS takes images of at most %u x 32768 bins", kMaxWalkTiles);
-    if (o.hist_mode == KL_HIST_LDS && walk_region_points(walk->n_steps) > kWalkBinnedPoints)
-        return fail(KL_EINVAL, "hist_mode KL_HIST_LDS takes at most %llu drawn points per walker",
-                    (unsigned long long)(kWalkBinnedPoints / 256));
+    if (o.hist_mode == KL_HIST_LDS && walk->n_steps > kWalkBinnedSteps)
+        return fail(KL_EINVAL, "hist_mode KL_HIST_LDS takes at most %u drawn points per walker", kWalkBinnedSteps);
     Gens G;
     if ((rc = make_gens_ab(ab, &G))) return rc;
     hipStream_t s = (hipStream_t)o.stream;
@@ -1329,9 +1328,9 @@ int kl_walk_render_ex(const kl_c64* ab, const kl_walk* walk, const kl_window* wi
     j.H = window->height;
     j.dropped = o.dropped_out;
     const bool binned = o.hist_mode == KL_HIST_LDS || (o.hist_mode == KL_HIST_AUTO && np >= (1ull << 18) &&
-                                                       walk_tiles(j.W, j.H) <= kMaxWalkTiles &&
-                                                       walk_region_points(walk->n_steps) <= kWalkBinnedPoints);
-    const WalkBinned L = binned ? walk_binned_layout(j) : WalkBinned{};
+                                                       walk_binned_ok(j.W, j.H, walk->n_steps));
+    const WalkBinned L = binned ? walk_binned_layout(walk->n_walkers, walk->burn_in, walk->n_steps, walk_tiles(j.W, j.H))
+                                : WalkBinned{};
     if (!o.accumulate) {
         // a binned render's first launch touches the image no more than to clear it
         if (L.blocks) j.clear_bins = (uint64_t)j.W * j.H;

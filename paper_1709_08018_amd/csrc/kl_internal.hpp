@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include "kl.h"
+#include "walk_layout.hpp"
 
 namespace kl {
 
@@ -273,17 +274,7 @@ struct WalkJob {
 };
 hipError_t launch_walk(const WalkJob& j, hipStream_t s);
 // Binned walk render: points sorted by image tile of 2^15 bins, counted in
-// LDS; images of at most kMaxWalkTiles tiles, at most kWalkBinnedPoints
-// points staged per launch (walk_region_points(n_steps) per 256 walkers).
-constexpr uint32_t kMaxWalkTiles = 256;
-constexpr uint64_t kWalkBinnedPoints = 1ull << 27;
-uint32_t walk_tiles(uint32_t W, uint32_t H);
-uint64_t walk_region_points(uint32_t n_steps);
-struct WalkBinned {
-    uint64_t blocks;           // workgroups of walkers a launch; 0: nothing to draw
-    size_t off_starts, bytes;
-};
-WalkBinned walk_binned_layout(const WalkJob& j);
+// LDS (walk_layout.hpp: what it takes and its staging).
 hipError_t launch_walk_binned(const WalkJob& j, const WalkBinned& L, void* buf, hipStream_t s);
 
 int device_cu_count();

@@ -270,23 +270,8 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkJob j) {
 }
 
 // ---- binned render
-constexpr uint32_t kWalkTileBits = 15;                    // a tile: 2^15 bins
-constexpr uint32_t kWalkTileBins = 1u << kWalkTileBits;
-// A region holds a workgroup's drawn points of one Philox block, eight steps
-// at most, so that a step's place in its region is known at compile time and
-// its bin and rank stay in registers.  (Sixteen steps a region took 15%
-// longer on 2^30 points, thirty-two 72% longer, and four no shorter.)
-constexpr uint32_t kWalkChunk = 8;
-constexpr uint32_t kWalkBlock = 512;                      // walkers of a workgroup
-constexpr uint32_t kWalkRegion = kWalkBlock * kWalkChunk; // points of a region at most
-
-// regions of a workgroup: the Philox blocks with a drawn step burn_in + 1 .. burn_in + n_steps
-__host__ __device__ inline uint32_t walk_chunks(uint32_t burn_in, uint32_t n_steps) {
-    return (burn_in + n_steps) / kWalkChunk - (burn_in + 1) / kWalkChunk + 1;
-}
-
 // One region per (workgroup, Philox block): its points in the window as
-// offsets within their tiles, tile by tile (ids, kWalkRegion slots a region),
+// offsets within their tiles, tile by tile (ids, kRegion slots a region),
 // and where each tile's offsets start (starts, T + 1 entries a region:
 // starts[T] is the region's count).
 //
@@ -303,12 +288,12 @@ __host__ __device__ inline uint32_t walk_chunks(uint32_t burn_in, uint32_t n_ste
 template <typename T>
 constexpr int kWalkWaves = std::is_same<T, float>::value ? 6 : 5;   // per SIMD, without spills
 
-template <typename T>
-__global__ __launch_bounds__(kWalkBlock) __attribute__((amdgpu_waves_per_eu(kWalkWaves<T>))) void walk_bin_kernel(const WalkJob j, uint16_t* __restrict__ ids,
-                                                       uint32_t* __restrict__ starts, uint32_t T_tiles,
-                                                       uint32_t n_chunks) {
+template <typename T, uint32_t WALKERS>
+__global__ __launch_bounds__(WALKERS) __attribute__((amdgpu_waves_per_eu(kWalkWaves<T>))) void walk_bin_kernel(
+    const WalkJob j, uint16_t* __restrict__ ids, uint32_t* __restrict__ starts, uint32_t T_tiles, uint32_t n_chunks) {
+    constexpr uint32_t kRegion = WALKERS * kWalkChunk;   // slots of a region
     __shared__ WalkMaps<T> m;
-    __shared__ __align__(4) uint16_t sorted[kWalkRegion];
+    __shared__ __align__(4) uint16_t sorted[kRegion];
     __shared__ uint32_t cnt[2][kMaxWalkTiles], base[kMaxWalkTiles + 1];
     load_walk_maps(j, m);
     for (uint32_t t = threadIdx.x; t < kMaxWalkTiles; t += blockDim.x) cnt[0][t] = 0;
@@ -381,7 +366,7 @@ __global__ __launch_bounds__(kWalkBlock) __attribute__((amdgpu_waves_per_eu(kWal
                 sorted[base[bin[i] >> kWalkTileBits] + rank[i]] = (uint16_t)(bin[i] & (kWalkTileBins - 1));
         __syncthreads();
         const uint32_t n2 = (base[T_tiles] + 1) / 2;   // whole dwords: a region's slots are its own
-        uint32_t* out = (uint32_t*)(ids + region * kWalkRegion);
+        uint32_t* out = (uint32_t*)(ids + region * kRegion);
         for (uint32_t i = threadIdx.x; i < n2; i += blockDim.x) out[i] = ((const uint32_t*)sorted)[i];
         uint32_t* st = starts + region * (T_tiles + 1);
         for (uint32_t t = threadIdx.x; t <= T_tiles; t += blockDim.x) st[t] = base[t];
@@ -471,8 +456,8 @@ __device__ __forceinline__ HistShare hist_share(const uint32_t* __restrict__ sta
 // workgroups for every tile, and regions of 256 walkers, 63.
 __global__ __launch_bounds__(1024) void walk_tile_hist_kernel(const uint16_t* __restrict__ ids,
                                                               const uint32_t* __restrict__ starts,
-                                                              uint64_t n_regions, uint32_t T_tiles,
-                                                              uint32_t* __restrict__ image) {
+                                                              uint64_t n_regions, uint32_t region_slots,
+                                                              uint32_t T_tiles, uint32_t* __restrict__ image) {
     __shared__ __align__(16) uint32_t hist[kWalkTileBins];
     const HistShare share = hist_share(starts, n_regions, T_tiles);
     if (share.of == 0) return;
@@ -512,7 +497,7 @@ __global__ __launch_bounds__(1024) void walk_tile_hist_kernel(const uint16_t* __
                 aq[q] = __shfl(a, (int)r, 64);
                 bq[q] = __shfl(b, (int)r, 64);
                 cq[q] = aq[q] / 8 + sub;
-                seg[q] = ids + (base + r) * kWalkRegion;
+                seg[q] = ids + (base + r) * region_slots;
                 v[q] = 8 * cq[q] < bq[q] ? *(const uint4*)(seg[q] + 8 * cq[q]) : make_uint4(0, 0, 0, 0);
             }
 #pragma unroll
@@ -558,55 +543,32 @@ hipError_t launch_walk(const WalkJob& j, hipStream_t s) {
     return hipSuccess;
 }
 
-uint32_t walk_tiles(uint32_t W, uint32_t H) {
-    const uint64_t bins = (uint64_t)W * H;
-    return (uint32_t)((bins + kWalkTileBins - 1) / kWalkTileBins);
-}
-
-uint64_t walk_region_points(uint32_t n_steps) {
-    return 256ull * kWalkChunk * ((n_steps + kWalkChunk - 1) / kWalkChunk);
-}
-
-// The temporaries of a binned render: `blocks` workgroups of walkers a launch,
-// their regions' ids and starts.
-WalkBinned walk_binned_layout(const WalkJob& j) {
-    WalkBinned L{};
-    if (j.n_walkers == 0 || j.n_steps == 0) return L;
-    const uint64_t chunks = walk_chunks(j.burn_in, j.n_steps), total = (j.n_walkers + kWalkBlock - 1) / kWalkBlock;
-    L.blocks = std::min(total, std::max<uint64_t>(1, kWalkBinnedPoints / (kWalkRegion * chunks)));
-    L.off_starts = L.blocks * chunks * kWalkRegion * sizeof(uint16_t);
-    L.bytes = L.off_starts + L.blocks * chunks * (walk_tiles(j.W, j.H) + 1) * sizeof(uint32_t);
-    return L;
-}
-
-// The binned render: walkers in launches whose regions hold at most
-// kWalkBinnedPoints points, each launch binning its walkers' points
-// (walk_bin_kernel) and then counting them tile by tile
-// (walk_tile_hist_kernel), in `buf` (L.bytes bytes).
+// The binned render: walkers in launches of L.blocks workgroups, each launch
+// binning its walkers' points (walk_bin_kernel) and then counting them tile by
+// tile (walk_tile_hist_kernel), in `buf` (L.bytes bytes).
 hipError_t launch_walk_binned(const WalkJob& j, const WalkBinned& L, void* buf, hipStream_t s) {
     if (L.blocks == 0) return hipSuccess;
-    const uint32_t T_tiles = walk_tiles(j.W, j.H), n_chunks = walk_chunks(j.burn_in, j.n_steps);
-    const uint64_t total_blocks = (j.n_walkers + kWalkBlock - 1) / kWalkBlock;
+    const uint32_t T_tiles = walk_tiles(j.W, j.H);
+    const uint64_t total_blocks = (j.n_walkers + L.walkers - 1) / L.walkers;
     uint16_t* ids = (uint16_t*)buf;
     uint32_t* starts = (uint32_t*)((unsigned char*)buf + L.off_starts);
+    const bool fp64 = j.precision == KL_PREC_FP64;
+    void (*bin)(WalkJob, uint16_t*, uint32_t*, uint32_t, uint32_t) =
+        L.walkers == kWalkBlock ? (fp64 ? walk_bin_kernel<double, kWalkBlock> : walk_bin_kernel<float, kWalkBlock>)
+                                : (fp64 ? walk_bin_kernel<double, kWalkBlockSmall> : walk_bin_kernel<float, kWalkBlockSmall>);
     // two workgroups for each CU, or for each tile if that is more
     const unsigned hist_blocks = std::max(2u * (unsigned)device_cu_count(), 2u * T_tiles);
     for (uint64_t b0 = 0; b0 < total_blocks; b0 += L.blocks) {
         const uint64_t nb = std::min(total_blocks - b0, L.blocks);
         WalkJob c = j;
-        c.first_walker = j.first_walker + b0 * kWalkBlock;
-        c.n_walkers = std::min(j.n_walkers - b0 * kWalkBlock, nb * kWalkBlock);
+        c.first_walker = j.first_walker + b0 * L.walkers;
+        c.n_walkers = std::min(j.n_walkers - b0 * L.walkers, nb * L.walkers);
         if (b0) c.clear_bins = 0;
-        if (j.precision == KL_PREC_FP64)
-            hipLaunchKernelGGL(walk_bin_kernel<double>, dim3((unsigned)nb), dim3(kWalkBlock), 0, s, c, ids, starts,
-                               T_tiles, n_chunks);
-        else
-            hipLaunchKernelGGL(walk_bin_kernel<float>, dim3((unsigned)nb), dim3(kWalkBlock), 0, s, c, ids, starts,
-                               T_tiles, n_chunks);
+        hipLaunchKernelGGL(bin, dim3((unsigned)nb), dim3(L.walkers), 0, s, c, ids, starts, T_tiles, L.chunks);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(walk_tile_hist_kernel, dim3(hist_blocks), dim3(1024), 0, s, ids, starts, nb * n_chunks, T_tiles,
-                           j.image);
+        hipLaunchKernelGGL(walk_tile_hist_kernel, dim3(hist_blocks), dim3(1024), 0, s, ids, starts, nb * L.chunks,
+                           L.walkers * kWalkChunk, T_tiles, j.image);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

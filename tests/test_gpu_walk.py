@@ -302,3 +302,17 @@ def test_binned_walk_clears_its_image(n, offset, size):
     assert (buf[:offset] == 7).all() and (buf[offset + W * H:] == 7).all()
     kl.walk_render(ab, 5, 2, n, 1, 20, win, image=img, hist_mode="lds", accumulate=True)
     assert torch.equal(img, 2 * want)
+
+
+@pytest.mark.parametrize("n,burn,steps", [(3, 7, 262144), (1, 0, 262144), (257, 5, 262145), (1, 0, 400000), (2, 6, 524288)])
+def test_longest_binned_walks(n, burn, steps):
+    """Walks around the length from which a workgroup takes 256 walkers, so
+    that its regions fit the staging, and the longest binned ones (drawn steps
+    in 2^16 + 1 blocks of eight), each the automatic choice: the image and
+    dropped count of one atomic per point."""
+    ab = kl.maskit_generators(wl.MASKIT_MU)
+    (a, da), (b, db) = _render_both(ab, 9, 1, n, burn, steps, WIN_M, "fp32")
+    np.testing.assert_array_equal(a, b)
+    assert da == db and int(a.sum()) + da == n * steps
+    auto = kl.as_u32(kl.walk_render(ab, 9, 1, n, burn, steps, WIN_M)).astype(np.int64)
+    np.testing.assert_array_equal(auto, a)

@@ -1,0 +1,69 @@
+"""Host rules of the library that need no device, compiled from their own
+headers (csrc/*.hpp, plain C++) and run on the CPU."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1709_08018_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstring>
+#include <cstdlib>
+#include "walk_layout.hpp"
+using namespace kl;
+int main(int argc, char** argv) {
+    unsigned long long n; unsigned b, s, t;
+    while (scanf("%llu %u %u %u", &n, &b, &s, &t) == 4) {
+        const WalkBinned L = walk_binned_layout(n, b, s, t);
+        printf("%d %u %u %llu %llu %llu\n", (int)walk_binned_ok(1024, 1024, s), L.walkers, L.chunks,
+               (unsigned long long)L.blocks, (unsigned long long)L.off_starts, (unsigned long long)L.bytes);
+    }
+}
+"""
+
+
+def _compile(tmp_path, text):
+    src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    src.write_text(text)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    return str(exe)
+
+
+@pytest.fixture(scope="module")
+def walk_rules(tmp_path_factory):
+    exe = _compile(tmp_path_factory.mktemp("walk_rules"), PROGRAM)
+
+    def ask(cases):
+        text = "".join("%d %d %d %d\n" % c for c in cases)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+        return [tuple(int(x) for x in line.split()) for line in out.splitlines()]
+
+    return ask
+
+
+def test_binned_walks_keep_their_staging_bound(walk_rules):
+    """Every binned walk, up to the longest of 2^19 drawn points from any
+    place in a block of eight, stages at most what 256 walkers of the longest
+    walk take, 2^27 slots of 2 bytes and one region more, whatever the number
+    of walkers; and at least one workgroup a launch."""
+    bound = 2 ** 27 + 2048
+    cases = [(n, burn, steps, tiles) for n in (1, 256, 257, 512, 513, 100000, 2 ** 30)
+             for burn in (0, 1, 6, 7, 8, 13) for tiles in (1, 256)
+             for steps in (1, 2, 8, 64, 1000, 131072, 262136, 262137, 262144, 262145, 400000, 524287, 524288)]
+    for (n, burn, steps, tiles), (ok, walkers, chunks, blocks, ids, total) in zip(cases, walk_rules(cases)):
+        where = (n, burn, steps, tiles)
+        assert ok == 1, where
+        first, last = (burn + 1) // 8, (burn + steps) // 8
+        assert chunks == last - first + 1, where
+        assert 1 <= blocks <= -(-n // walkers), where
+        assert blocks * walkers * 8 * chunks <= bound, where
+        assert ids == 2 * blocks * walkers * 8 * chunks and total == ids + 4 * blocks * chunks * (tiles + 1), where
+
+
+def test_longer_walks_are_not_binned(walk_rules):
+    """Past 2^19 drawn points, up to the most a walk may have, the automatic
+    choice is the direct path."""
+    cases = [(1, 0, s, 32) for s in (524289, 2 ** 31, 2 ** 32 - 8, 2 ** 32 - 7, 2 ** 32 - 2)]
+    assert [r[0] for r in walk_rules(cases)] == [0] * len(cases)
