@@ -1333,7 +1333,7 @@ int kl_walk_render_ex(const kl_c64* ab, const kl_walk* walk, const kl_window* wi
                                 : WalkBinned{};
     if (!o.accumulate) {
         // a binned render's first launch touches the image no more than to clear it
-        if (L.blocks) j.clear_bins = (uint64_t)j.W * j.H;
+        if (L.blocks && walk_clears(L, (uint64_t)j.W * j.H)) j.clear_bins = (uint64_t)j.W * j.H;
         else if ((e = launch_fill_u32(image_out, (uint64_t)j.W * j.H, 0, s)) != hipSuccess)
             return hip_fail(e, "clear image");
         if (o.dropped_out && (e = launch_fill_u64(o.dropped_out, 1, 0, s)) != hipSuccess)

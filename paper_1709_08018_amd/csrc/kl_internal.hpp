@@ -270,7 +270,7 @@ struct WalkJob {
     uint32_t* image;           // render
     uint32_t W, H;
     uint64_t* dropped;         // render: device u64 or null
-    uint64_t clear_bins;       // binned render: bins of the image to clear first (0: the image accumulates)
+    uint64_t clear_bins;       // binned render: bins of the image to clear first (0: none, walk_clears)
 };
 hipError_t launch_walk(const WalkJob& j, hipStream_t s);
 // Binned walk render: points sorted by image tile of 2^15 bins, counted in

@@ -67,4 +67,15 @@ inline WalkBinned walk_binned_layout(uint64_t n_walkers, uint32_t burn_in, uint3
     return L;
 }
 
+// Whether the first launch of walkers also clears the image of `bins` bins,
+// or a launch of its own does: up to 128 bins a thread of the walkers.  The
+// walkers' workgroups clear some 100 GB/s each before they step, a launch of
+// its own the whole image at the device's rate for some 2 us and a gap.  64
+// steps, with the clearing launch and fused: 1024^2 from 16 workgroups (128
+// bins a thread) 53.2 and 52.7 us, from 8 52.7 and 53.9, from one 50.0 and
+// 76.7; 2048^2 from 64 workgroups (128) 65.1 and 63.7, from 32 62.8 and 63.4,
+// from 4 57.6 and 83.0; 2890^2 from 512 (32) 119.4 and 114.6, from 64 (255)
+// 79.9 and 78.6, from 16 75.5 and 84.4, from one 64.4 and 278.
+inline bool walk_clears(const WalkBinned& L, uint64_t bins) { return bins <= 128 * L.blocks * L.walkers; }
+
 }  // namespace kl

@@ -17,8 +17,9 @@ int main(int argc, char** argv) {
     unsigned long long n; unsigned b, s, t;
     while (scanf("%llu %u %u %u", &n, &b, &s, &t) == 4) {
         const WalkBinned L = walk_binned_layout(n, b, s, t);
-        printf("%d %u %u %llu %llu %llu\n", (int)walk_binned_ok(1024, 1024, s), L.walkers, L.chunks,
-               (unsigned long long)L.blocks, (unsigned long long)L.off_starts, (unsigned long long)L.bytes);
+        printf("%d %u %u %llu %llu %llu %d\n", (int)walk_binned_ok(1024, 1024, s), L.walkers, L.chunks,
+               (unsigned long long)L.blocks, (unsigned long long)L.off_starts, (unsigned long long)L.bytes,
+               (int)walk_clears(L, (unsigned long long)t * 32768));
     }
 }
 """
@@ -52,7 +53,7 @@ def test_binned_walks_keep_their_staging_bound(walk_rules):
     cases = [(n, burn, steps, tiles) for n in (1, 256, 257, 512, 513, 100000, 2 ** 30)
              for burn in (0, 1, 6, 7, 8, 13) for tiles in (1, 256)
              for steps in (1, 2, 8, 64, 1000, 131072, 262136, 262137, 262144, 262145, 400000, 524287, 524288)]
-    for (n, burn, steps, tiles), (ok, walkers, chunks, blocks, ids, total) in zip(cases, walk_rules(cases)):
+    for (n, burn, steps, tiles), (ok, walkers, chunks, blocks, ids, total, _) in zip(cases, walk_rules(cases)):
         where = (n, burn, steps, tiles)
         assert ok == 1, where
         first, last = (burn + 1) // 8, (burn + steps) // 8
@@ -67,3 +68,12 @@ def test_longer_walks_are_not_binned(walk_rules):
     choice is the direct path."""
     cases = [(1, 0, s, 32) for s in (524289, 2 ** 31, 2 ** 32 - 8, 2 ** 32 - 7, 2 ** 32 - 2)]
     assert [r[0] for r in walk_rules(cases)] == [0] * len(cases)
+
+
+def test_few_walkers_leave_the_clearing_to_a_launch(walk_rules):
+    """The walkers clear the image themselves only where there are enough of
+    them, 128 bins a thread at most: 3,000 walkers (6 workgroups) do not clear
+    2500 x 2500 bins (191 tiles), nor 512 an image of 255 tiles; 2^20 do."""
+    cases = [(3000, 0, 100, 191), (512, 0, 512, 255), (512, 0, 64, 2), (512, 0, 64, 3), (513, 0, 64, 4),
+             (1 << 20, 0, 64, 32), (1 << 20, 0, 64, 256), (2, 0, 400000, 1), (2, 0, 400000, 2)]
+    assert [r[6] for r in walk_rules(cases)] == [0, 0, 1, 0, 1, 1, 1, 1, 0]
