@@ -49,7 +49,8 @@
  *           on the null stream keep their tables and staged points in one
  *           buffer per device instead (1 MiB growing to at most 192 MiB; up
  *           to 64 MiB held until the process ends, more than that given back
- *           after 32 calls in a row that did not need it), which calls on
+ *           after 32 such calls in a row that did not use it, and kept until
+ *           then, also by a program that makes no further calls), which calls on
  *           other streams, or on another host thread while one holds it, do
  *           not touch.
  * streams   the plain entry points run on the null stream and return after

@@ -14,6 +14,7 @@
 #include <string>
 #include <vector>
 
+#include "host_rules.hpp"
 #include "kl_internal.hpp"
 
 namespace kl {
@@ -213,11 +214,13 @@ static Fold make_fold(const kl_window* w, int head_form) {
 }
 
 // ------------------------------------------------------------------ devices
-// Table buffer that single-set calls on a device's null stream reuse (Temp::tables).
+// Buffer that the calls on a device's null stream reuse for their tables and
+// staged points: renders of one or many sets, evaluations, binned walks
+// (Temp::tables; table_lease decides its size).
 struct TableCache {
     void* base = nullptr;
     size_t bytes = 0;
-    int idle = 0;        // calls in a row that a buffer of kTableCacheKeep bytes would have served
+    int idle = 0;        // table_lease's count
     bool busy = false;   // leased to a call that is still enqueuing its kernels
 };
 
@@ -332,15 +335,6 @@ int plan_split(int depth, int precision, int r_req, int m_req, Split* sp, PlanCo
 }
 
 // ------------------------------------------------------------------ temporaries
-// Largest buffer that the per-device table cache holds, and the size above
-// which it is given back after kTableCacheIdle calls in a row that a buffer of
-// that size would have served.  A walk render of 2^26 points takes 152 MB, a
-// batch of 256 sets of depths 12..18 some 110: mapped and unmapped on each call,
-// as the stream-ordered allocator does around a synchronisation, they cost 420
-// and 400 us beside 200 us and 9.9 ms of kernels.
-constexpr size_t kTableCacheMax = size_t(192) << 20, kTableCacheKeep = size_t(64) << 20;
-constexpr int kTableCacheIdle = 32;
-
 // Stream-ordered temporaries of one call, freed on its stream when the call
 // returns.  tables() lends the call its device's cached table buffer instead
 // when the call runs on the null stream: every user of that buffer enqueues
@@ -366,19 +360,19 @@ struct Temp {
     }
     hipError_t tables(void** p, size_t bytes) {
         int dev = -1;
-        if (s == nullptr && lease < 0 && bytes <= kTableCacheMax && hipGetDevice(&dev) == hipSuccess && dev >= 0 &&
-            dev < kMaxDevices) {
+        if (s == nullptr && lease < 0 && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) {
             std::lock_guard<std::mutex> lk(g_dev_mutex);
             TableCache& c = g_devs[dev].tables;
             if (!c.busy) {
-                c.idle = bytes > kTableCacheKeep ? 0 : std::min(c.idle + 1, kTableCacheIdle);
-                if (c.bytes < bytes || (c.bytes > kTableCacheKeep && c.idle == kTableCacheIdle)) {
-                    if (c.base) (void)hipFreeAsync(c.base, s);
+                const TableLease l = table_lease(c.bytes, bytes, c.idle);
+                if (l.release) {
+                    (void)hipFreeAsync(c.base, s);
                     c.base = nullptr;
                     c.bytes = 0;
-                    const size_t want = std::max(bytes, size_t(1) << 20);
-                    if (hipMallocAsync(&c.base, want, s) == hipSuccess) {
-                        c.bytes = want;
+                }
+                if (l.allocate) {
+                    if (hipMallocAsync(&c.base, l.allocate, s) == hipSuccess) {
+                        c.bytes = l.allocate;
                     } else {
                         // a temporary of the exact size may still fit; clear the
                         // error so that the next launch check does not report it
@@ -386,7 +380,7 @@ struct Temp {
                         (void)hipGetLastError();
                     }
                 }
-                if (c.base) {
+                if (l.lease && c.base) {
                     c.busy = true;
                     lease = dev;
                     *p = c.base;

@@ -25,6 +25,21 @@ int main(int argc, char** argv) {
 """
 
 
+LEASES = r"""
+#include <cstdio>
+#include "host_rules.hpp"
+int main() {
+    unsigned long long held, want;
+    int idle;
+    while (scanf("%llu %llu %d", &held, &want, &idle) == 3) {
+        const kl::TableLease l = kl::table_lease(held, want, idle);
+        printf("%d %d %llu %d\n", (int)l.lease, (int)l.release, (unsigned long long)l.allocate, idle);
+        fflush(stdout);
+    }
+}
+"""
+
+
 def _compile(tmp_path, text):
     src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
     src.write_text(text)
@@ -77,3 +92,42 @@ def test_few_walkers_leave_the_clearing_to_a_launch(walk_rules):
     cases = [(3000, 0, 100, 191), (512, 0, 512, 255), (512, 0, 64, 2), (512, 0, 64, 3), (513, 0, 64, 4),
              (1 << 20, 0, 64, 32), (1 << 20, 0, 64, 256), (2, 0, 400000, 1), (2, 0, 400000, 2)]
     assert [r[6] for r in walk_rules(cases)] == [0, 0, 1, 0, 1, 1, 1, 1, 0]
+
+
+MIB = 1 << 20
+
+
+def test_large_buffer_is_given_back(tmp_path):
+    """The buffer of the null stream's calls: it grows with a call, up to 192
+    MiB; above 64 MiB it is given back by the 32nd call in a row that 64 MiB
+    would have served, or that is above 192 MiB and takes a temporary, and a
+    large call in between starts the count again; 64 MiB and less are kept."""
+    p = subprocess.Popen([_compile(tmp_path, LEASES)], stdin=subprocess.PIPE, stdout=subprocess.PIPE, text=True)
+    state = dict(held=0, idle=0)
+
+    def call(want):
+        p.stdin.write("%d %d %d\n" % (state["held"], want, state["idle"]))
+        p.stdin.flush()
+        lease, release, allocate, state["idle"] = map(int, p.stdout.readline().split())
+        assert lease == (want <= 192 * MIB)
+        assert release <= (state["held"] > 0) and (not allocate or release or not state["held"])
+        state["held"] = allocate or (0 if release else state["held"])
+        assert not lease or state["held"] >= want
+        return state["held"]
+
+    try:
+        assert call(100) == MIB and call(MIB) == MIB and call(MIB + 1) == MIB + 1
+        assert call(64 * MIB) == 64 * MIB and [call(5) for _ in range(100)] == [64 * MIB] * 100
+        for large in (64 * MIB + 1, 150 * MIB, 192 * MIB):
+            for small in (5, 64 * MIB, 192 * MIB + 1, 1 << 40):
+                assert call(large) == large
+                assert [call(small) for _ in range(31)] == [large] * 31
+                assert call(64 * MIB + 1) == large                        # used: the count starts again
+                assert [call(small) for _ in range(31)] == [large] * 31
+                after = 0 if small > 192 * MIB else max(small, MIB)
+                assert call(small) == after
+                assert [call(5) for _ in range(40)] == [max(after, MIB)] * 40
+                assert call(192 * MIB + 1) == max(after, MIB)             # a temporary; what is small stays
+    finally:
+        p.stdin.close()
+        p.wait()
