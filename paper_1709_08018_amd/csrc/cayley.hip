@@ -138,10 +138,6 @@ __device__ inline void cayley_word(const CayleyJob& a, const CayleyHead& h, c64 
     }
 }
 
-// consecutive words per thread in a render: enough threads to fill the grid,
-// runs no shorter than 16 words and no longer than 256
-constexpr int kCayleyRunMin = 16, kCayleyRunMax = 256;
-
 // symbol j (0-based, x - 1) of a word packed 3 bits each into lo (0..20) and hi (21..39)
 __device__ __forceinline__ int packed_symbol(uint64_t lo, uint64_t hi, int j) {
     return (int)((j < 21 ? lo >> (3 * j) : hi >> (3 * (j - 21))) & 7u);
@@ -191,18 +187,13 @@ __device__ inline void cayley_counts(const uint8_t* TB, uint8_t* A, uint64_t* C,
 // symbols are packed 3 bits each (x - 1) into two registers.
 //
 // Decode, eval, and renders of words shorter than r (launch_cayley sends a
-// render's words of depth >= r to cayley_head_kernel below).
-// Words of depth d >= r are evaluated as head . tail, the tail being the
-// last r symbols.  The tail read from state 0 ends in some state; the word
-// is regular when the head reads from that state, i.e. the state is in the
-// head's good set.  Every regular word of length r is a candidate tail: a
-// table in LDS holds them in lexicographic order with their end states and
-// their points (the maps of the tail applied right to left to the seed, FP64
-// homogeneous).  The words of one head are then consecutive in index order
-// and run over the candidate tails whose end state the head accepts, so a
-// thread unranks the first word of its run once, keeps the head's product
-// (FP64, left to right), and steps through the table: one Moebius map of a
-// table point per word.  Shorter words are walked right to left in full.
+// render's words of depth >= r to cayley_head_kernel below), a word a thread.
+// An evaluated word (its depth is at least r) is head . tail, the tail being the
+// last r symbols, as the head kernel forms it.  Every regular word of length r is a
+// candidate tail: a table in LDS holds their points (the maps of the tail
+// applied right to left to the seed, FP64 homogeneous) in lexicographic order.
+// The word's value is its head's product (FP64, left to right) at its tail's
+// point.  A render's shorter words are walked right to left in full.
 template <int MODE>
 __global__ __launch_bounds__(256) void cayley_kernel(const CayleyJob a) {
     __shared__ uint64_t C[KL_MAX_DEPTH + 1][kCayleyMaxStates];
@@ -210,13 +201,13 @@ __global__ __launch_bounds__(256) void cayley_kernel(const CayleyJob a) {
     __shared__ uint8_t NX[kCayleyMaxSets * kCayleyMaxSymbols];
     __shared__ uint16_t SETS[kCayleyMaxSets];
     __shared__ m64 G[kCayleyMaxSymbols];
-    __shared__ c64 TU[MODE == kCayleyDecode ? 1 : kCayleyMaxTails], TV[MODE == kCayleyDecode ? 1 : kCayleyMaxTails];
-    __shared__ uint8_t TS[MODE == kCayleyDecode ? 1 : kCayleyMaxTails];
+    constexpr bool kTails = MODE == kCayleyEval;
+    __shared__ c64 TU[kTails ? kCayleyHeadTails : 1], TV[kTails ? kCayleyHeadTails : 1];
     __shared__ uint8_t TB[kCayleyMaxStates * (kCayleyMaxSymbols + 1)];
     __shared__ uint8_t A[kCayleyMaxStates * kCayleyMaxStates];
     __shared__ uint64_t DS[KL_MAX_DEPTH + 2];
     const int S = a.S, m = a.m, M = a.n_sets, D = a.max_depth;
-    const int r = MODE == kCayleyDecode ? 0 : a.r;
+    const int r = kTails ? a.r : 0;
     for (int i = threadIdx.x; i < M * m; i += blockDim.x) NX[i] = a.next_set[i];
     for (int i = threadIdx.x; i < M; i += blockDim.x) SETS[i] = a.sets[i];
     for (int i = threadIdx.x; i < m; i += blockDim.x) G[i] = a.maps[i];
@@ -234,15 +225,12 @@ __global__ __launch_bounds__(256) void cayley_kernel(const CayleyJob a) {
     __syncthreads();
 
     // Unrank word `local` of length d (lexicographic, first symbol most
-    // significant) from good set g0; symbol j chosen among the candidates
-    // by the counts of their completions.  With hl >= 0 also the good set
-    // after the first hl symbols and their product.
-    auto unrank = [&](uint64_t local, int d, int g0, int hl, uint64_t& lo, uint64_t& hi, int& gh, m64& Mh,
-                      uint64_t k) {
-        int g = g0;
+    // significant); symbol j chosen among the candidates by the counts of
+    // their completions.  Mh becomes the product of the first hl symbols.
+    auto unrank = [&](uint64_t local, int d, int hl, uint64_t& lo, uint64_t& hi, m64& Mh, uint64_t k) {
+        int g = 0;
         lo = hi = 0;
         for (int j = 0; j < d; ++j) {
-            if (j == hl) gh = g;
             const uint64_t* row = CM[d - j - 1];
             int x = 1, gx = 0;
             for (; x <= m; ++x) {
@@ -280,16 +268,12 @@ __global__ __launch_bounds__(256) void cayley_kernel(const CayleyJob a) {
         }
     };
 
-    if (r > 0) {
+    if constexpr (kTails) {
         // the tail table: regular words of length r in lexicographic order
         for (int t = threadIdx.x; t < a.n_tails; t += blockDim.x) {
             uint64_t lo, hi;
-            int gh = 0;
             m64 unused;
-            unrank((uint64_t)t, r, 0, -1, lo, hi, gh, unused, 0);
-            int s = 0;
-            for (int j = r - 1; j >= 0; --j) s = TB[s * (m + 1) + packed_symbol(lo, hi, j) + 1];
-            TS[t] = (uint8_t)s;
+            unrank((uint64_t)t, r, 0, lo, hi, unused, 0);
             c64 u, v;
             seed_point(packed_symbol(lo, hi, r - 1), u, v);
             walk(lo, hi, 0, r, u, v);
@@ -301,95 +285,55 @@ __global__ __launch_bounds__(256) void cayley_kernel(const CayleyJob a) {
     }
 
     uint64_t drop = 0;
-    uint32_t run_key = kCayleyOutside, run_len = 0;
-    auto emit = [&](uint64_t k, double px, double py) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < a.count; k += stride) {
+        int d = D;
+        uint64_t local;
+        if (MODE == kCayleyEval) {
+            local = a.idx[k];
+            if (local >= DS[1]) {
+                a.z_out[k] = {__builtin_nan(""), __builtin_nan("")};
+                continue;
+            }
+        } else {
+            const uint64_t i = a.first + k;
+            d = a.min_depth;
+            while (i >= DS[d - a.min_depth + 1]) ++d;
+            local = i - DS[d - a.min_depth];
+        }
+        const int hl = kTails ? d - r : 0;   // head length (r <= D = d)
+        uint64_t lo, hi;
+        m64 Mh = {{1.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {1.0, 0.0}};
+        unrank(local, d, hl, lo, hi, Mh, k);
+        if (MODE == kCayleyDecode) continue;
+        double px, py;
+        if constexpr (kTails) {
+            // rank of the tail among the regular words of length r
+            int t = 0, g = 0;
+            for (int j = 0; j < r; ++j) {
+                const int y = packed_symbol(lo, hi, hl + j) + 1;
+                const uint64_t* row = CM[r - j - 1];
+                for (int x = 1; x < y; ++x) t += (int)row[NX[g * m + x - 1]];
+                g = NX[g * m + y - 1];
+            }
+            cayley_word(a, cayley_head(a, Mh), TU[t], TV[t], px, py);
+        } else {
+            c64 u, v;
+            seed_point(packed_symbol(lo, hi, d - 1), u, v);
+            walk(lo, hi, 0, d, u, v);
+            cayley_pixel(a, u, v, px, py);
+        }
         if (MODE == kCayleyEval) {
             a.z_out[k] = {px, py};
         } else {
-            const uint32_t key = cayley_bin(px, py, a.W, a.H);
-            if (key != run_key) {
-                if (run_key == kCayleyOutside) drop += run_len;
-                else if (run_len) atomicAdd(a.image + run_key, run_len);
-                run_key = key;
-                run_len = 0;
-            }
-            ++run_len;
-        }
-    };
-    const uint64_t per = MODE == kCayleyRender ? (uint64_t)a.run : 1;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x * per;
-    for (uint64_t k0 = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * per; k0 < a.count; k0 += stride) {
-        const uint64_t k1 = k0 + per < a.count ? k0 + per : a.count;
-        uint64_t k = k0;
-        while (k < k1) {
-            int d = D;
-            uint64_t local;
-            if (MODE == kCayleyEval) {
-                local = a.idx[k];
-                if (local >= DS[1]) {
-                    a.z_out[k] = {__builtin_nan(""), __builtin_nan("")};
-                    ++k;
-                    continue;
-                }
-            } else {
-                const uint64_t i = a.first + k;
-                d = a.min_depth;
-                while (i >= DS[d - a.min_depth + 1]) ++d;
-                local = i - DS[d - a.min_depth];
-            }
-            const int hl = (r > 0 && d >= r) ? d - r : -1;   // head length, -1: walk in full
-            uint64_t lo, hi;
-            int gh = 0;
-            m64 Mh = {{1.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {1.0, 0.0}};
-            unrank(local, d, 0, hl, lo, hi, gh, Mh, k);
-            if (MODE == kCayleyDecode) {
-                ++k;
-                continue;
-            }
-            if (hl < 0) {
-                c64 u, v;
-                seed_point(packed_symbol(lo, hi, d - 1), u, v);
-                walk(lo, hi, 0, d, u, v);
-                double px, py;
-                cayley_pixel(a, u, v, px, py);
-                emit(k, px, py);
-                ++k;
-                continue;
-            }
-            // rank of the tail among the regular words of length r
-            int t = 0;
-            {
-                int g = 0;
-                for (int j = 0; j < r; ++j) {
-                    const int y = packed_symbol(lo, hi, hl + j) + 1;
-                    const uint64_t* row = CM[r - j - 1];
-                    for (int x = 1; x < y; ++x) t += (int)row[NX[g * m + x - 1]];
-                    g = NX[g * m + y - 1];
-                }
-            }
-            const uint32_t accept = SETS[gh];   // end states after which the head reads
-            const CayleyHead ch = cayley_head(a, Mh);
-            while (true) {
-                double px, py;
-                cayley_word(a, ch, TU[t], TV[t], px, py);
-                emit(k, px, py);
-                ++k;
-                if (MODE == kCayleyEval || k >= k1) break;
-                do {
-                    ++t;
-                } while (t < a.n_tails && !((accept >> TS[t]) & 1u));
-                if (t >= a.n_tails) break;   // the head's words end here
-            }
+            const uint32_t bin = cayley_bin(px, py, a.W, a.H);
+            if (bin == kCayleyOutside) ++drop;
+            else atomicAdd(a.image + bin, 1u);
         }
     }
-    if (MODE == kCayleyRender) {
-        if (run_key == kCayleyOutside) drop += run_len;
-        else if (run_len) atomicAdd(a.image + run_key, run_len);
-        if (a.dropped) {
-            for (int off = kWave / 2; off > 0; off >>= 1) drop += __shfl_down(drop, off, kWave);
-            if ((threadIdx.x & (kWave - 1)) == 0 && drop)
-                atomicAdd((unsigned long long*)a.dropped, (unsigned long long)drop);
-        }
+    if (MODE == kCayleyRender && a.dropped) {
+        for (int off = kWave / 2; off > 0; off >>= 1) drop += __shfl_down(drop, off, kWave);
+        if ((threadIdx.x & (kWave - 1)) == 0 && drop) atomicAdd((unsigned long long*)a.dropped, (unsigned long long)drop);
     }
 }
 
@@ -757,10 +701,9 @@ __global__ __launch_bounds__(kCayleyHeadBlock) void cayley_head_kernel(const Cay
 hipError_t launch_cayley(const CayleyJob& job, int mode, hipStream_t s) {
     if (job.count == 0) return hipSuccess;
     CayleyJob j = job;
-    const uint64_t threads = 256ull * (uint64_t)std::max(1, j.grid_blocks);
-    j.run = (int)std::min<uint64_t>(kCayleyRunMax, std::max<uint64_t>(kCayleyRunMin, j.count / threads));
-    if (mode == kCayleyRender && j.r > 0) {
-        // words of depths >= r go one head per thread; shorter words keep the per-word path
+    const unsigned grid = (unsigned)std::max(1, j.grid_blocks);
+    if (mode == kCayleyRender) {
+        // words of depths >= r go one head per thread
         const uint64_t B = j.r > j.min_depth ? j.depth_start[j.r - j.min_depth] : 0;   // first word of depth r
         const uint64_t end = j.first + j.count;
         if (end > B) {
@@ -780,29 +723,19 @@ hipError_t launch_cayley(const CayleyJob& job, int mode, hipStream_t s) {
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
                     if (e != hipSuccess) return e;
                 }
-                hipLaunchKernelGGL(cayley_head_kernel, dim3((unsigned)std::max(1, j.grid_blocks)), dim3(kCayleyHeadBlock),
-                                   lds, s, h, h.n_sets, h.max_depth, h.n_tails, h.n_seeds);
+                hipLaunchKernelGGL(cayley_head_kernel, dim3(grid), dim3(kCayleyHeadBlock), lds, s, h, h.n_sets, h.max_depth,
+                                   h.n_tails, h.n_seeds);
                 hipError_t e = hipGetLastError();
                 if (e != hipSuccess) return e;
             }
         }
         if (j.first >= B) return hipSuccess;
-        // the words shorter than r, each walked in full by a thread of its own
-        // (no tail table)
-        j.count = (end < B ? end : B) - j.first;
-        j.r = 0;
-        j.n_tails = 0;
-        j.run = 1;
-        const uint64_t blocks = std::min<uint64_t>((j.count + 255) / 256, (uint64_t)std::max(1, j.grid_blocks));
-        hipLaunchKernelGGL(cayley_kernel<kCayleyRender>, dim3((unsigned)blocks, (unsigned)j.n_seeds), dim3(256), 0, s, j);
-        return hipGetLastError();
+        j.count = std::min(end, B) - j.first;   // the words shorter than r
     }
-    const uint64_t per = mode == kCayleyRender ? (uint64_t)j.run : 1;
-    uint64_t blocks = (j.count + 256 * per - 1) / (256 * per);
-    blocks = std::min<uint64_t>(blocks, (uint64_t)std::max(1, j.grid_blocks));
-    if (mode == kCayleyDecode) hipLaunchKernelGGL(cayley_kernel<kCayleyDecode>, dim3((unsigned)blocks), dim3(256), 0, s, j);
-    else if (mode == kCayleyEval) hipLaunchKernelGGL(cayley_kernel<kCayleyEval>, dim3((unsigned)blocks), dim3(256), 0, s, j);
-    else hipLaunchKernelGGL(cayley_kernel<kCayleyRender>, dim3((unsigned)blocks), dim3(256), 0, s, j);
+    const unsigned blocks = (unsigned)std::min<uint64_t>((j.count + 255) / 256, grid);
+    if (mode == kCayleyDecode) hipLaunchKernelGGL(cayley_kernel<kCayleyDecode>, dim3(blocks), dim3(256), 0, s, j);
+    else if (mode == kCayleyEval) hipLaunchKernelGGL(cayley_kernel<kCayleyEval>, dim3(blocks), dim3(256), 0, s, j);
+    else hipLaunchKernelGGL(cayley_kernel<kCayleyRender>, dim3(blocks, (unsigned)j.n_seeds), dim3(256), 0, s, j);
     return hipGetLastError();
 }
 

@@ -215,8 +215,7 @@ hipError_t launch_perword_batch(const PerWordBatchJob& job, hipStream_t s);
 constexpr int kCayleyMaxStates = 16;
 constexpr int kCayleyMaxSymbols = 8;
 constexpr int kCayleyMaxSets = 64;      // good-state sets reachable from the set of all states
-constexpr int kCayleyMaxTails = 1024;   // entries of the tail table
-// The tail table's size in use: a render goes one head per thread, so
+// Entries of the tail table at most: a render goes one head per thread, so
 // shorter tails give more heads to spread over the GPU (the once-punctured
 // torus table: 324 tails of 5 symbols, three times the heads of 972 tails of
 // 6, at 0.31 against 0.42 ms for depth 16), while longer tails spread each
@@ -248,10 +247,9 @@ struct CayleyJob {
     const uint64_t* idx;                // eval: count indices of words of max_depth
     c64* z_out;                         // eval
     int grid_blocks;
-    // head/tail evaluation of words of depth >= r (r = 0: none): a table of the
-    // n_tails regular words of length r, their end states and their points
+    // head/tail evaluation of words of depth >= r >= 1: a table of the n_tails
+    // regular words of length r, their end states and their points
     int r, n_tails;
-    int run;                            // render: consecutive words per thread
 };
 hipError_t launch_cayley(const CayleyJob& j, int mode, hipStream_t s);
 

@@ -284,3 +284,30 @@ def test_head_slices_ranges_and_seeds(case, depth):
             own, drop = _bins(p[first:first + count, 0], p[first:first + count, 1], win)
             np.testing.assert_array_equal(img.astype(np.int64), own, err_msg=f"{seed} {first} {count}")
             assert int(dropped.item()) == drop
+
+
+@pytest.mark.parametrize("min_depth,depth", [(2, 2), (1, 3), (3, 4), (5, 5), (1, 6)])
+def test_largest_table_ranges_and_seeds(min_depth, depth):
+    """The largest table at its own depths: words shorter than the tails
+    (three symbols), which each seed draws in a row of the same launch, and
+    ranges that start among them, from one seed and from all eight, against
+    the histogram of the words' own evaluated bins."""
+    table, maps = _largest_table()
+    t = kl.Cayley(table, maps)
+    win = (-1.7, 1.9, -1.3, 2.2, 211, 187)
+    seeds = list(range(2, 2 + table.shape[1] - 1))
+    p = {}
+    for s in ["own", *seeds]:
+        parts = [kl.cayley_eval(t, d, np.arange(kl.cayley_num_words(t, d), dtype=np.uint64), window=win, seed=s)
+                 for d in range(min_depth, depth + 1)]
+        p[s] = torch.cat(parts).cpu().numpy()
+    n = len(p["own"])
+    for first, count in [(0, n), (1, n - 1), (n // 5, n // 2), (n - 1, 1)]:
+        for s, group in [("own", ["own"]), (seeds[-1], [seeds[-1]]), ("all", seeds)]:
+            dropped = torch.zeros(1, dtype=torch.int64, device="cuda")
+            img = kl.as_u32(kl.cayley_render(t, depth, win, min_depth=min_depth, first=first, count=count, seed=s,
+                                             dropped=dropped)).astype(np.int64)
+            q = np.concatenate([p[g][first:first + count] for g in group])
+            own, drop = _bins(q[:, 0], q[:, 1], win)
+            np.testing.assert_array_equal(img, own, err_msg=f"{s} {first} {count}")
+            assert int(dropped.item()) == drop
