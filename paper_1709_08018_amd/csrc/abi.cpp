@@ -875,12 +875,13 @@ struct SetSpec {
 // The descriptors are uploaded from host memory; the call waits for those
 // copies (not for the renders) before it returns.
 static int render_sets(const std::vector<SetSpec>& specs, const kl_window* w, const kl_opts& o, int wpc,
-                       uint32_t* image, uint64_t bins, uint64_t n_dropped, hipStream_t s) {
+                       uint32_t* image, uint64_t bins, uint64_t n_dropped, bool tiling, hipStream_t s) {
     const int nb = (int)specs.size();
     if (nb == 0) return KL_OK;
     const size_t esz = o.precision == KL_PREC_FP64 ? sizeof(c64) : sizeof(c32);
     uint64_t n_prefix = 0, n_tail = 0;
     uint32_t max_prefix = 0, max_tail = 0;
+    int letters = 0;
     for (const SetSpec& q : specs) {
         const uint32_t np = q.sp.k ? (uint32_t)num_words(q.sp.k) : 0;
         const uint32_t nt = (uint32_t)num_words(q.sp.r);
@@ -888,6 +889,7 @@ static int render_sets(const std::vector<SetSpec>& specs, const kl_window* w, co
         n_tail += nt;
         max_prefix = std::max(max_prefix, np);
         max_tail = std::max(max_tail, nt);
+        letters = std::max(letters, q.sp.r);
     }
     // every temporary in one buffer: the descriptors (uploaded together) then
     // the tables; on the null stream the device's cached one, where they fit
@@ -990,6 +992,7 @@ static int render_sets(const std::vector<SetSpec>& specs, const kl_window* w, co
     job.force_homog = o.suffix_form;
     job.count_dropped = o.dropped_out != nullptr;
     job.bounded = o.block_bounds;
+    job.merge = batch_merges(o.precision == KL_PREC_FP64, letters, tiling, (uint64_t)w->width * w->height, h_off.back());
     if (!o.accumulate) {
         job.clear_image = image;
         job.clear_bins = bins;
@@ -1047,7 +1050,7 @@ static int render_tiling(const Gens& G, int depth, const kl_window* w, uint32_t*
             if (!wpc && d == depth) wpc = od.waves_per_cu;
             specs.push_back({G, sp, sd, image, o.dropped_out});
         }
-    return render_sets(specs, w, o, wpc, image, (uint64_t)w->width * w->height, 1, s);
+    return render_sets(specs, w, o, wpc, image, (uint64_t)w->width * w->height, 1, true, s);
 }
 
 // The render itself, once every argument has been checked.  KL_SEED_ALL is
@@ -1684,7 +1687,7 @@ static int render_many_run(int n, const kl_c64* ta, const kl_c64* tb, const int*
         specs[i] = {gens[i], splits[i], seed_index(o), images_out + bins * i, o.dropped_out ? o.dropped_out + i : nullptr};
         if (!wpc && persistent_ok(splits[i])) wpc = per[i].waves_per_cu;
     }
-    return render_sets(specs, window, o, wpc, images_out, bins * (uint64_t)n, (uint64_t)n, s);
+    return render_sets(specs, window, o, wpc, images_out, bins * (uint64_t)n, (uint64_t)n, false, s);
 }
 
 // Median time of a batched render with plans bp (one untimed run first).

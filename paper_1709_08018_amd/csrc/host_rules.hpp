@@ -3,6 +3,7 @@
 #pragma once
 
 #include <stddef.h>
+#include <stdint.h>
 
 #include <algorithm>
 
@@ -37,6 +38,29 @@ inline TableLease table_lease(size_t held, size_t want, int& idle) {
     if (!fits) return {false, tired, 0};
     if (held < want || tired) return {true, held > 0, std::max(want, kTableCacheMin)};
     return {true, false, 0};
+}
+
+// ------------------------------------------------------------------ batched renders
+// Whether a batched render whose longest suffixes have `letters` letters adds
+// up its runs by bin in LDS first (kernels.hip, MergeSink); `bins` an image,
+// `tiling` all sets into one, `units` of 256 heads in all.  A run then waits for the table where a global
+// atomic would not be waited for, and fewer atomics leave the chip.  With
+// six letters runs are long and few: 60 sets of depths 9 .. 13 231 us merged
+// and 150 not, ten of depths 11 .. 13 110 and 97.  With five, FP32 (five
+// waves a SIMD) gains where the atomics are many: Maskit's tilings to depth 15
+// at 300^2 / 1024^2 / 4096^2 137 / 148 / 294 us merged and 158 / 201 / 377 not,
+// two sets of depth 17 172 and 252, though sets of few units lose up to a
+// fifth (40 of depths 11 .. 13 at 1024^2 116 and 92).  FP64 (three waves) has
+// less to run while it waits: the tilings to depth 16 at 512^2 / 1024^2 /
+// 2048^2 432 / 467 / 495 us merged and 377 / 392 / 452 not, to depth 15 at
+// 512^2 198 and 176, forty sets 144 and 110; only images that exceed the caches
+// favour merging (2900^2 / 4096^2 / 8192^2, depth 16: 510 / 527 / 663 and
+// 530 / 622 / 927; depth 15: 242 / 294 / 478 and 325 / 393 / 558), so it is kept
+// for those of 2^23 bins up, where units are few (5,500 at depth 16; depth 18,
+// five letters, 12,400 units: at 4096^2 849 and 771).  With four and fewer letters both gain: depth 14
+// 100 and 138 us, in FP64 106 and 136.
+inline bool batch_merges(bool fp64, int letters, bool tiling, uint64_t bins, uint64_t units) {
+    return letters <= 4 || (letters == 5 && (!fp64 || (tiling && bins >= (uint64_t(1) << 23) && units < 8192)));
 }
 
 }  // namespace kl

@@ -583,6 +583,8 @@ struct GlobalSink {
 // (merge_flush); a run that finds both of its slots taken goes to the image.
 // Device-wide atomics all leave the XCD's L2, some 18 G a second, and a
 // unit's runs close a bin 2.9 times on average in Maskit's tiling to depth 14.
+// 2^11 slots hold the bins of most units (tiling to depth 15, five letters:
+// 150 us, with 2^10 slots 153).  batch_merges says which batches merge.
 constexpr int kMergeLog = 11, kMergeSlots = 1 << kMergeLog;
 constexpr uint32_t kFreeSlot = 0xFFFFFFFFu;   // no bin: images hold fewer than 2^32 - 1 bins
 
@@ -1698,13 +1700,6 @@ __global__ __launch_bounds__(kBlock) void render_batch_kernel(const BatchArgs a)
     }
 }
 
-// Longest suffixes whose runs are merged.  Whole renders, with and without:
-// tilings to depth 14 (four letters) 91 and 124 us, to depth 15 (five) 150
-// and 201 us; at six letters runs are longer and the table's latency shows:
-// 60 sets of depths 9 .. 13 231 and 150 us, ten of depths 11 .. 13 110 and 97.
-// 2^11 slots hold the bins of most units (2^10: 153 us at depth 15).
-constexpr int kMergeTail = 5;
-
 hipError_t launch_render_batch(const BatchJob& job, hipStream_t s) {
     if (job.total_units == 0) return hipSuccess;
     BatchArgs a;
@@ -1720,7 +1715,7 @@ hipError_t launch_render_batch(const BatchJob& job, hipStream_t s) {
     const size_t esz = fp64 ? sizeof(cpx<double>) : sizeof(cpx<float>);
     // the largest table's suffix nodes (the table bytes hold its homogeneous form)
     a.max_nodes = job.bounded ? (uint32_t)(job.table_bytes / (2 * esz) / kNodeWords) : 0u;
-    const bool merge = !job.bounded && job.max_tail <= (uint32_t)num_words(kMergeTail);
+    const bool merge = !job.bounded && job.merge;
     const size_t lds = (size_t)job.table_bytes + 4 * sizeof(m64) +
                        (job.bounded ? (size_t)a.max_nodes * (fp64 ? sizeof(NodeDisk<double>) : sizeof(NodeDisk<float>)) +
                                           (kBlock / kWave) * kQueue * 2

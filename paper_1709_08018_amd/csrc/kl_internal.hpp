@@ -188,6 +188,7 @@ struct BatchJob {
     int force_homog;
     int count_dropped;             // the sets' dropped counters are set
     int bounded;                   // block bounds in the persistent batch kernel (kl_opts::block_bounds)
+    int merge;                     // runs are added up by bin in LDS (batch_merges); not with bounded
     uint32_t* clear_image;         // cleared by the set-up launch, or null (accumulating render)
     uint64_t clear_bins;
     uint64_t* clear_dropped;       // n_dropped counters cleared with the image, or null

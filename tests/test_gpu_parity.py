@@ -826,3 +826,18 @@ def test_batched_runs_merged_by_bin_equal_single_renders(tail_len, size, precisi
     twice = kl.render_many(ta, tb, depths, win, images=imgs.clone(), precision=precision, tail_len=tail_len,
                            accumulate=True)
     assert torch.equal(twice, 2 * imgs)
+
+
+@pytest.mark.parametrize("size", [(2896, 2896), (2897, 2896)])
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_tilings_of_five_letters_either_side_of_the_merge(precision, size):
+    """Tilings with suffixes of five letters into images on both sides of 2^23
+    bins, from which FP64 runs too are added up by bin: the image and dropped
+    count of the depths rendered one by one with the same suffixes."""
+    depth, mind, win = 13, 9, (-1.5, 1.2, -1.1, 1.5, *size)
+    dropped = torch.zeros(1, dtype=torch.int64, device="cuda")
+    img = kl.render(*C2, depth, win, precision=precision, min_depth=mind, tail_len=5, dropped=dropped)
+    acc, dacc = kl.new_image(win), torch.zeros(1, dtype=torch.int64, device="cuda")
+    for d in range(mind, depth + 1):
+        kl.render(*C2, d, win, image=acc, precision=precision, accumulate=d > mind, tail_len=5, dropped=dacc)
+    assert torch.equal(img, acc) and dropped.item() == dacc.item()

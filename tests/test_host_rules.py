@@ -40,6 +40,18 @@ int main() {
 """
 
 
+MERGES = r"""
+#include <cstdio>
+#include "host_rules.hpp"
+int main() {
+    unsigned long long bins, units;
+    int fp64, letters, tiling;
+    while (scanf("%d %d %d %llu %llu", &fp64, &letters, &tiling, &bins, &units) == 5)
+        printf("%d\n", (int)kl::batch_merges(fp64, letters, tiling, bins, units));
+}
+"""
+
+
 def _compile(tmp_path, text):
     src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
     src.write_text(text)
@@ -131,3 +143,18 @@ def test_large_buffer_is_given_back(tmp_path):
     finally:
         p.stdin.close()
         p.wait()
+
+
+def test_batches_that_merge_their_runs(tmp_path):
+    """Runs are merged up to four letters; with five in FP32, and in FP64 in
+    tilings of 2^23 bins up and fewer than 8,192 units alone (forty sets of
+    five letters and the tiling to depth 16 took longer merged); never with
+    six."""
+    cases = [(p, r, t, b, u) for p in (0, 1) for r in range(1, 9) for t in (0, 1)
+             for b in (1, 1 << 20, (1 << 23) - 1, 1 << 23) for u in (1, 8191, 8192)]
+    exe = _compile(tmp_path, MERGES)
+    out = subprocess.run([exe], input="".join("%d %d %d %d %d\n" % c for c in cases), capture_output=True, text=True,
+                         check=True).stdout.split()
+    for (p, r, t, b, u), got in zip(cases, out):
+        want = r <= 4 or (r == 5 and (p == 0 or (t == 1 and b >= 1 << 23 and u < 8192)))
+        assert got == str(int(want)), (p, r, t, b, u)
