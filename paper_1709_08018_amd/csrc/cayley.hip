@@ -441,7 +441,10 @@ __device__ __forceinline__ void choose_symbol(const uint64_t* n, const uint64_t*
 // workgroup builds the tables above in LDS.
 //
 // What bounds it: at depth 16 of the once-punctured torus table (57.4 M
-// words) the words' FP64 instructions, some 25 a word; at shallow depths the
+// words) two thirds of its 36 instructions a wave-word are the words' FP64
+// ones, one third the heads' ranking and products, whose LDS reads and long
+// chains leave waves waiting a third of their time (half of the issue slots
+// are used: 16 waves a CU do not hide them); at shallow depths the
 // chain of dependent LDS reads that builds the tables, hence the counts by
 // shuffles, the symbols' counts read together, the job copied to LDS in one
 // load, and one wave a good set for the tail lists.  Table 2 at depth 16:

@@ -51,7 +51,9 @@ __device__ void build_next6(uint16_t* next6) {
 // Byte path (any depth, any destination): one word per thread, staged as
 // bytes, 256 words a tile, written as one contiguous byte range.  It serves
 // depths 1 .. 3 (36 words at most) and destinations that are not 16-byte
-// aligned.
+// aligned, where the bytes of a word straddle the wide stores: every word but a
+// few of depth 13 29.3 us (aligned, by the packed path, 9.8), 2^26 words of depth
+// 18 782 us (224).
 __device__ __forceinline__ void put_letters(uint64_t& lo, uint64_t& hi, int pos, uint64_t bits) {
     const int sh = 2 * pos;   // pos <= 39, bits < 2^12
     if (sh < 64) {

@@ -1336,14 +1336,15 @@ hipError_t launch_perword_batch(const PerWordBatchJob& job, hipStream_t s) {
 }
 
 // One word a thread, its index asked for before the tables' form is known.
-// What bounds it: the instructions of a word's head (some 300, and 45 a lane
-// letter, two thirds of them FP64), then the gathers of its prefix product
-// and suffix.  Divisions therefore take precomputed inverses, and lane
-// letters are split off in 32 bits (u < 3^m <= 3^20).  2^20 words: 23.8 us
-// at depth 18, 39.5 at depth 30 (three and fifteen lane letters), 10^5 words
-// of depth 38 32.4, set-up included; with 64-bit divisions 24.3, 43.7 and
-// 41.5.  Four lanes reading one product together and turning it over in LDS
-// gained nothing (24.1, 41.9, 33.3).
+// What bounds it: at depth 18 the issue of a word's 375 instructions (a head's
+// some 240, and 45 a lane letter, two thirds of them FP64) takes 10 of the
+// kernel's 18 us; waves wait 40% of their time, for the gathers of a word's
+// prefix product and suffix and for its chain of products.  Divisions
+// therefore take precomputed inverses, and lane letters are split off in 32
+// bits (u < 3^m <= 3^20).  2^20 words: 23.8 us at depth 18, 39.5 at depth 30
+// (three and fifteen lane letters), 10^5 words of depth 38 32.4, set-up
+// included; with 64-bit divisions 24.3, 43.7 and 41.5.  Four lanes reading one
+// product together and turning it over in LDS gained nothing (24.1, 41.9, 33.3).
 template <typename T>
 __global__ __launch_bounds__(256) void eval_kernel(const PerWordArgs a) {
     __shared__ m64 G[4];
@@ -1507,7 +1508,7 @@ namespace kl {
 // set) and prefix table (prefix_blocks), then the clearing of the images and
 // the dropped counters.  What bounds it: the writes, and the chain of FP64
 // products of a prefix, each step picking its letter's matrix from LDS.  256
-// sets of depths 12..18, 512 x 512 each (268 MB of images): 83 us; as three
+// sets of depths 12..18, 512 x 512 each (268 MB of images): 87 us; as three
 // launches, with a per-lane copy of the generators, 35 (images) + 179
 // (prefixes) + 34 (suffixes).  The 56 sets of a tiling to depth 14: 6.4
 // against 4.4 + 13.3 + 5.6 us.

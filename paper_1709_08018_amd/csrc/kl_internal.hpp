@@ -216,11 +216,13 @@ hipError_t launch_perword_batch(const PerWordBatchJob& job, hipStream_t s);
 constexpr int kCayleyMaxStates = 16;
 constexpr int kCayleyMaxSymbols = 8;
 constexpr int kCayleyMaxSets = 64;      // good-state sets reachable from the set of all states
-// Entries of the tail table at most: a render goes one head per thread, so
-// shorter tails give more heads to spread over the GPU (the once-punctured
-// torus table: 324 tails of 5 symbols, three times the heads of 972 tails of
-// 6, at 0.31 against 0.42 ms for depth 16), while longer tails spread each
-// head's ranking over more words.
+// Entries of the tail table at most.  Every workgroup builds the table and its
+// lists, and a render goes one head per thread, so that shorter tails cost less
+// before the first word and give more heads to spread over the GPU; longer ones
+// spread each head's ranking over more words.  The once-punctured torus table
+// with 324 tails of 5 symbols / 972 of 6: 16.4 / 25.1 us at depth 7, 22.0 /
+// 37.5 at 11, 47.7 / 53.6 at 15, 90.5 / 98.8 at 16; depths 1 to 10 from four
+// seeds 45 / 98.  The modular group's tails end at 12 symbols either way.
 constexpr int kCayleyHeadTails = 400;
 constexpr int kCayleyMaxTail = 12;      // its longest tails
 enum { kCayleyDecode = 0, kCayleyEval = 1, kCayleyRender = 2 };

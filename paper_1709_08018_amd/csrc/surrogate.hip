@@ -157,7 +157,7 @@ __global__ void predict_occupancy_kernel(const float* z, uint64_t n, uint8_t* o)
 // one reciprocal: with e = e^-|x| and s = e / (2 + e),
 //   H(sigmoid(x)) = log(1 + e) + |x| e / (1 + e),   log(1 + e) = 2 atanh(s),
 // the atanh by its power series to s^15 (s <= 1/3: truncated below 2e-9 of
-// its value).  512 sets: 11.9 us; with four waves a set, log1pf, and a
+// its value).  512 sets: 10.9 us; with four waves a set, log1pf, and a
 // second exponential 43 us, with sixteen waves and log1pf 27 us.
 __device__ __forceinline__ float binary_entropy(float x) {
     const float a = fabsf(x), e = expf(-a), p = 1.f + e, q = 2.f + e, pq = p * q;
@@ -254,11 +254,13 @@ __global__ void iou_kernel(const float* __restrict__ z, const uint8_t* __restric
 // keep the LDS of a workgroup at 71 KB, so two share a CU and fill each
 // other's waits, and a small batch spreads over four times the CUs; one
 // workgroup a set (140 KB) had 40 barriers a set and began each with the
-// loads of the linear layers.  512 sets: 42.5 + 5.2 us (strips, linear
-// layers), before 55.9 + 4.7 us; one set: 9.5 + 3.9 against 25.5 + 3.7 us.
+// loads of the linear layers.  512 sets: 37.1 + 4.7 us (strips, linear
+// layers; traced in a long run of calls), before 55.9 + 4.7 us; one set: 8.3 +
+// 3.7 against 25.5 + 3.7 us.
 // Four waves with their weights in registers (250) read an operand row once
 // for both column phases and twice over the rows; eight waves of 128
-// registers, one phase each, read LDS 2.4 times as much and took 61 us.
+// registers, one phase each, read LDS 2.4 times as much and took 61 us where
+// these, with to_bf16 in integer steps still, took 53.
 constexpr int kFwdThreads = 256;                      // 4 waves
 constexpr int kY1S = 64 + 8, kY2S = 32 + 8;           // bf16 per pixel: 16-byte rows, padded against bank conflicts
 constexpr int kY2Bytes = 10 * 34 * kY2S * 2;          // rows 8 s - 1 .. 8 s + 8, x = -1 .. 32, the ends zero

@@ -517,8 +517,9 @@ __global__ __launch_bounds__(512) void conv34_kernel(const TrainArgs a) {
 // (masked) takes the 16 taps of one channel per matrix instruction, weights
 // read four channels ahead; the K3 gradient stays in registers over a
 // workgroup's units.  Bound by memory (70 MB at 128 sets) and its latency,
-// hence two workgroups a CU: 24.8 us, 28.3 us with one (188 registers), 39 us
-// with all weights held in registers, which spill.
+// hence two workgroups a CU, whose 128 registers cost 20 bytes of scratch a
+// lane: 24.8 us, 28.3 us with one (188 registers, none), 39 us with all weights
+// held in registers (172-264 bytes of scratch).
 constexpr int kD3W = 34;                      // dwords of a dy3 plane row: entry X + 1, X = -1 .. 66
 constexpr int kD3P = 18 * kD3W;               // dwords of a plane
 constexpr int kY2T = 256 + 8;
@@ -827,8 +828,7 @@ struct Segment {
 constexpr int kSegments = 11;
 struct FinishArgs {
     Segment seg[kSegments];
-    int w2_blocks, w1_blocks;   // after the segments' blocks: W2 (4 tiles a block), then W1
-    int seg_blocks;
+    int seg_blocks;             // W2 (4 tiles a block) and W1 come after them
 };
 
 __global__ __launch_bounds__(256) void finish_kernel(const TrainArgs a, const FinishArgs f, float* G, const Adam adam) {

@@ -281,10 +281,12 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkJob j) {
 // cleared while the other is read.  What bounds it: VALU issue (some 90
 // instructions a point, 28 of them the Philox rounds, whose 64-bit products
 // issue at a quarter of the rate; sums with carries in place of their chained
-// addends took 7% longer).  2^26 points in FP32: 153-161 us; with the bins
-// staged in LDS eight words apart (8-way bank conflicts), a second atomic and
-// five barriers 189.  Workgroups of 256 walkers take 7% less, but their regions
-// are half as long and the histogram kernel pays for it (64 us against 51).
+// addends took 7% longer).  2^26 points in FP32: 137 us (traced in a long run
+// of calls, with the histogram's 50 the call's 187); with the bins staged in
+// LDS eight words apart (8-way bank conflicts), a second atomic and five
+// barriers 189.  Workgroups of 256 walkers, which walks of some 2^18 steps take
+// (walk_binned_layout), need 7% less here, but their regions are half as long
+// and the histogram kernel pays for it (64 us against 50).
 template <typename T>
 constexpr int kWalkWaves = std::is_same<T, float>::value ? 6 : 5;   // per SIMD, without spills
 
@@ -452,7 +454,7 @@ __device__ __forceinline__ HistShare hist_share(const uint32_t* __restrict__ sta
 // One tile over a share of the regions: every offset counted in an LDS
 // histogram, then each non-zero bin added to the image.  What bounds it: the
 // latency of the offsets' loads and the LDS atomics, sixteen waves a CU (the
-// histogram takes 128 KB).  2^26 points: 51 us; with an equal number of
+// histogram takes 128 KB).  2^26 points: 50 us; with an equal number of
 // workgroups for every tile, and regions of 256 walkers, 63.
 __global__ __launch_bounds__(1024) void walk_tile_hist_kernel(const uint16_t* __restrict__ ids,
                                                               const uint32_t* __restrict__ starts,
