@@ -456,10 +456,12 @@ __device__ __forceinline__ HistShare hist_share(const uint32_t* __restrict__ sta
 // latency of the offsets' loads and the LDS atomics, sixteen waves a CU (the
 // histogram takes 128 KB).  2^26 points: 50 us; with an equal number of
 // workgroups for every tile, and regions of 256 walkers, 63.
+template <uint32_t WALKERS>
 __global__ __launch_bounds__(1024) void walk_tile_hist_kernel(const uint16_t* __restrict__ ids,
                                                               const uint32_t* __restrict__ starts,
-                                                              uint64_t n_regions, uint32_t region_slots,
-                                                              uint32_t T_tiles, uint32_t* __restrict__ image) {
+                                                              uint64_t n_regions, uint32_t T_tiles,
+                                                              uint32_t* __restrict__ image) {
+    constexpr uint32_t kRegion = WALKERS * kWalkChunk;
     __shared__ __align__(16) uint32_t hist[kWalkTileBins];
     const HistShare share = hist_share(starts, n_regions, T_tiles);
     if (share.of == 0) return;
@@ -499,7 +501,7 @@ __global__ __launch_bounds__(1024) void walk_tile_hist_kernel(const uint16_t* __
                 aq[q] = __shfl(a, (int)r, 64);
                 bq[q] = __shfl(b, (int)r, 64);
                 cq[q] = aq[q] / 8 + sub;
-                seg[q] = ids + (base + r) * region_slots;
+                seg[q] = ids + (base + r) * kRegion;
                 v[q] = 8 * cq[q] < bq[q] ? *(const uint4*)(seg[q] + 8 * cq[q]) : make_uint4(0, 0, 0, 0);
             }
 #pragma unroll
@@ -558,6 +560,8 @@ hipError_t launch_walk_binned(const WalkJob& j, const WalkBinned& L, void* buf, 
     void (*bin)(WalkJob, uint16_t*, uint32_t*, uint32_t, uint32_t) =
         L.walkers == kWalkBlock ? (fp64 ? walk_bin_kernel<double, kWalkBlock> : walk_bin_kernel<float, kWalkBlock>)
                                 : (fp64 ? walk_bin_kernel<double, kWalkBlockSmall> : walk_bin_kernel<float, kWalkBlockSmall>);
+    void (*hist)(const uint16_t*, const uint32_t*, uint64_t, uint32_t, uint32_t*) =
+        L.walkers == kWalkBlock ? walk_tile_hist_kernel<kWalkBlock> : walk_tile_hist_kernel<kWalkBlockSmall>;
     // two workgroups for each CU, or for each tile if that is more
     const unsigned hist_blocks = std::max(2u * (unsigned)device_cu_count(), 2u * T_tiles);
     for (uint64_t b0 = 0; b0 < total_blocks; b0 += L.blocks) {
@@ -569,8 +573,7 @@ hipError_t launch_walk_binned(const WalkJob& j, const WalkBinned& L, void* buf, 
         hipLaunchKernelGGL(bin, dim3((unsigned)nb), dim3(L.walkers), 0, s, c, ids, starts, T_tiles, L.chunks);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(walk_tile_hist_kernel, dim3(hist_blocks), dim3(1024), 0, s, ids, starts, nb * L.chunks,
-                           L.walkers * kWalkChunk, T_tiles, j.image);
+        hipLaunchKernelGGL(hist, dim3(hist_blocks), dim3(1024), 0, s, ids, starts, nb * L.chunks, T_tiles, j.image);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
