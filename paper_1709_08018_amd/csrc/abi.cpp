@@ -301,7 +301,8 @@ int plan_split(int depth, int precision, int r_req, int m_req, Split* sp, PlanCo
         // depths of a tiling, which go in one batched launch whose units
         // of 256 heads are dealt round robin: mixing 4- and 6-letter tails
         // there leaves units of unequal work (the tiling of Maskit's group
-        // to depth 14 took 0.25 ms against 0.215 ms with 6 letters throughout).
+        // to depth 14 takes 197 us so, 187 us with 6 letters throughout; see
+        // tiling_opts).
         if (ctx == kPlanSingle && depth >= 13 && depth <= 16) r = depth <= 14 ? 4 : 5;
         // the deepest words need a longer tail: k <= 14 and m <= 20
         r = std::max(r, std::min(kMaxTail, depth - kMaxLane - kMaxPrefix));
@@ -1134,9 +1135,9 @@ static int eval_run(const Gens& G, const Split& sp, const uint64_t* idx, uint64_
 // takes its deepest depth's tail -- the tail a render of that depth alone
 // would take -- at every depth long enough for it, so that the units of its
 // batched launch carry equal work and its index ranges split their words
-// the same way.  (The tiling of Maskit's group to depth 14, 4-letter tails
-// throughout: 0.18 ms, against 0.215 ms with 6 letters throughout and
-// 0.25 ms with 4 letters at depths 13-14 only.)
+// the same way.  (The tilings of Maskit's group to depths 14 / 16, 4- and
+// 5-letter tails throughout: 100 / 294 us, against 187 / 323 us with 6 letters
+// throughout and 197 / 361 us with each depth's own.)
 // That applies where the two differ (deepest depths 13-16) and no tuned
 // plan covers the deepest depth; tuned plans keep their depths' splits.
 static kl_opts tiling_opts(const kl_opts& o, int min_depth, int depth, const kl_window* w) {

@@ -95,9 +95,9 @@ int set_error(int code, const char* fmt, ...);  // records kl_last_error(), retu
 // (min_depth < depth, whole or by index ranges); or one set of a batched
 // render of many parameter sets.  Prefix tables of at most 9, 6 and 8
 // letters respectively: a tiling builds one table for every depth and seed
-// in one launch, and smaller tables pay there (the Maskit tiling to depth
-// 14: 0.160 against 0.182 ms with 9 letters; the depth-16 tiling of the
-// quasi-Fuchsian group: 0.153 against 0.167 ms).  A word's value depends
+// in one launch, and smaller tables pay there (the Maskit tilings to depths 14
+// / 16 / 17: 100.5 / 293 / 558 us against 101.8 / 297 / 564 with 9 letters; a
+// batch of 256 sets is the same with 8 and 9).  A word's value depends
 // on the tail only, not on how the head divides into prefix and lane
 // letters.
 enum PlanContext { kPlanSingle, kPlanTiling, kPlanBatch };
